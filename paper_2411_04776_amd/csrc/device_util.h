@@ -24,10 +24,61 @@ __device__ __forceinline__ gptr<T> glob(T *p)
     return (gptr<T>)p;
 }
 
+// One 32-bit step of a 64-lane butterfly: lanes exchange over distance O
+// without the LDS crossbar (a __shfl of a double is two ds_bpermute of about
+// 130 cycles each; these are VALU moves). For O <= 8 the row rotation reads
+// lane i - O, which after the wider steps holds lane i + O's value.
+template <int O>
+__device__ __forceinline__ void lane_pair(uint32_t x, uint32_t &a, uint32_t &b)
+{
+    if constexpr (O == 32) {
+        auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        a = r[0];
+        b = r[1];
+    } else if constexpr (O == 16) {
+        auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        a = x;
+        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + O, 0xf, 0xf, false);
+    }
+}
+template <int O>
+__device__ __forceinline__ double lane_add(double v)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(v);
+    uint32_t a0, b0, a1, b1;
+    lane_pair<O>((uint32_t)x, a0, b0);
+    lane_pair<O>((uint32_t)(x >> 32), a1, b1);
+    return __longlong_as_double((long long)((uint64_t)a1 << 32 | a0)) +
+           __longlong_as_double((long long)((uint64_t)b1 << 32 | b0));
+}
+
+// the value of another lane of the quad (CTRL 0xb1: lane ^ 1, 0x4e: lane ^ 2)
+template <int CTRL>
+__device__ __forceinline__ double quad_other(double v)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// a value that every lane holds, as a wavefront-uniform (scalar) one
+__device__ __forceinline__ double wave_first(double v)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// Sum over the wavefront, the same value in every lane: the tree of
+// distances 32, 16, ..., 1.
 __device__ __forceinline__ double wave_sum(double v)
 {
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_down(v, o, kWave);
-    return v;
+    return lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(lane_add<16>(lane_add<32>(v))))));
 }
 __device__ __forceinline__ double wave_max(double v)
 {
@@ -79,87 +130,31 @@ __device__ inline double block_sum_all(double v) { return block_reduce_all<0>(v,
 __device__ inline double block_max_all(double v) { return block_reduce_all<1>(v, -INFINITY); }
 __device__ inline double block_min_all(double v) { return block_reduce_all<2>(v, INFINITY); }
 
-// Sum of partials[0..n) in a fixed order; identical in every block.
-__device__ inline double reduce_partials(const double *partials, int n)
+// Vector sum over the block (blockDim.x a multiple of 64, at most kBlock) in
+// a fixed order; every thread gets the result.
+template <int NC>
+__device__ __forceinline__ void block_sum_vec(double v[NC])
 {
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) acc += partials[i];
-    return block_sum_all(acc);
-}
-
-// The same sum computed by one wavefront alone, without block barriers: lane
-// l adds partials l, l + 64, ... in order, then a fixed shuffle tree. Every
-// wavefront of every block gets the identical value.
-__device__ inline double wave_reduce_partials(const double *partials, int n)
-{
-    int lane = threadIdx.x & (kWave - 1);
-    double acc = 0.0;
-    for (int i = lane; i < n; i += kWave) acc += partials[i];
-    acc = wave_sum(acc);
-    return __shfl(acc, 0, kWave);
-}
-
-// wave_reduce_partials with eight loads in flight per lane: the same
-// additions in the same order (bit-identical), one memory round trip per
-// 512 partials instead of one per 64 (a scene of 128k vertices has ~2000).
-__device__ inline double wave_reduce_partials_u8(const double *partials, int n)
-{
-    constexpr int kU = 8;
-    int lane = threadIdx.x & (kWave - 1);
-    double acc = 0.0;
-    for (int base = lane; base < n; base += kU * kWave) {
-        double b[kU];
+    __shared__ double sh[kBlock / kWave][NC];
+    int lane = threadIdx.x % kWave, w = threadIdx.x / kWave, nw = blockDim.x / kWave;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            int i = base + u * kWave;
-            b[u] = i < n ? partials[i] : 0.0;
-        }
+    for (int c = 0; c < NC; ++c) v[c] = wave_sum(v[c]);
+    if (nw == 1) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (base + u * kWave < n) acc += b[u];
+        for (int c = 0; c < NC; ++c) v[c] = __shfl(v[c], 0, kWave);
+        return;
     }
-    acc = wave_sum(acc);
-    return __shfl(acc, 0, kWave);
-}
-
-// The same sum in two parts, for a kernel that can issue the loads before
-// other dependent loads: wave_partials_load fetches a lane's first U entries,
-// wave_partials_sum adds them and the rest (four loads ahead of the adds) in
-// the same order, so the value is bit-identical to wave_reduce_partials. The
-// PCG update kernel keeps the plain loop, which measured faster there.
-template <int U>
-__device__ __forceinline__ void wave_partials_load(const double *partials, int n, double (&a)[U])
-{
-    int lane = threadIdx.x & (kWave - 1);
+    if (lane == 0)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        int i = lane + u * kWave;
-        a[u] = i < n ? partials[i] : 0.0;
+        for (int c = 0; c < NC; ++c) sh[w][c] = v[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        double t = 0.0;
+        for (int k = 0; k < nw; ++k) t += sh[k][c];
+        v[c] = t;
     }
-}
-
-template <int U>
-__device__ __forceinline__ double wave_partials_sum(const double *partials, int n, const double (&a)[U])
-{
-    constexpr int kU = 4;
-    int lane = threadIdx.x & (kWave - 1);
-    double acc = 0.0;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (lane + u * kWave < n) acc += a[u];
-    for (int base = lane + U * kWave; base < n; base += kU * kWave) {
-        double b[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            int i = base + u * kWave;
-            b[u] = i < n ? partials[i] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (base + u * kWave < n) acc += b[u];
-    }
-    acc = wave_sum(acc);
-    return __shfl(acc, 0, kWave);
+    __syncthreads();
 }
 
 // ---- compensated (double-double style) sums for energies ----------------

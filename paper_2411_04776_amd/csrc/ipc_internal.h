@@ -16,9 +16,10 @@
 //     = one wavefront, padded to its longest row, stored component-major in
 //     the slice (value[(slot*9+c)*64 + lane]); slot 0 of a row is its diagonal;
 //   contact pairs: structure of arrays over active pairs (4 vertex ids, 12
-//     gradient and 144 Hessian components); in SpMV each pair forms its own
-//     H_p d_p and the rows gather those through incidence lists sorted by row
-//     and pair index (no float atomics anywhere).
+//     gradient components), the 144 Hessian components of a pair together;
+//     their blocks are merged per matrix row and column once per assembly
+//     (k_contact_rows), sorted by column, each block summed in pair order (no
+//     float atomics anywhere), and the SpMV applies the merged blocks.
 // In the mixed form the element Hessians and gradients, matrix values,
 // preconditioner, assembled gradient and PCG vectors are FP32 (dot products
 // accumulate in FP64); positions, Dm^-1, distances, CCD and energies stay FP64.
@@ -45,10 +46,11 @@ constexpr int kSlice = 64;        // rows per BELL slice (one wavefront)
 constexpr int kBlock = 256;       // threads per block for streaming kernels
 constexpr int kSpmvStreams = 2;   // partial sums per SpMV row (slots k, k + 2, ...), added in stream order
 constexpr int kRowsPerBlock = 64; // matrix rows per SpMV block (PCG A), a thread or two lanes each
-constexpr int kPairsPerBlock = 64;  // contact pairs per pair block of PCG A
+constexpr int kRowTeam = 16;      // lanes that share a contact row's blocks
+constexpr int kRowLong = 64;      // contact rows of more blocks take a wavefront
+constexpr int kRowSeg = 680;      // incidence entries of a contact row merged at a time (three columns each, sorted in LDS)
 constexpr int64_t kSpmvOneLaneRows = 65536;  // lists with at least this many rows: one thread per row
 constexpr int kScanTile = 1024;   // elements per scan tile
-constexpr int kHeavyRow = 24;     // incidence rows longer than this get a block of their own
 constexpr int kQueryKeep = 4;     // pairs a query lane keeps from the count pass for the fill pass
 constexpr int kLanesQ = 8;        // broad-phase lanes per query primitive (they split its buckets' entries)
 constexpr int kMasLevels = 3;     // aggregate levels of the multilevel preconditioner
@@ -56,9 +58,15 @@ constexpr int kMasCapM = 256;     // members of a preconditioner group (one bloc
 constexpr int kMasCapA = 256;     // aggregates of all levels in a group
 constexpr int kMasTarget = 256;   // groups are packed with top-level aggregates up to this many members
 
+constexpr int kTeamMax = 256;     // workgroups of a resident PCG team (one per CU)
+constexpr int kTeamSlots = 8;     // matrix slots of a row half kept in registers (two threads per row)
+constexpr int kTeamHalo = 4;      // column ids a thread keeps in registers
+constexpr int kTeamLds = 160 * 1024;  // LDS of a CU
+constexpr int kChunkRows = 512;    // contact rows a resident team's member takes (more: the launched form)
+
 // kernels timed by the optional profiler
 enum ProfKernel {
-    kProfPcgA = 0,        // SpMV + fused direction update (PCG A)
+    kProfPcgA = 0,        // SpMV + fused direction update (PCG A); a whole resident PCG solve
     kProfPcgB = 1,        // PCG vector update + preconditioner (PCG B)
     kProfElastic = 2,     // Neo-Hookean element kernel
     kProfAssemble = 3,    // gradient + matrix gather
@@ -74,7 +82,10 @@ struct PcgState {
     int32_t iters;
     double stop;
     double rzv[2];  // r.z of the previous iterations by parity, written once by the SpMV kernel's block 0
+    uint32_t join;  // resident team: members arrived, or kTeamAbort (cleared by the assembly before the solve)
+    uint32_t pad;
 };
+constexpr uint32_t kTeamAbort = 0x80000000u;
 
 // Per-scene values produced on the device and read back once per phase for
 // the whole list (one copy for all scenes).
@@ -86,11 +97,13 @@ struct SceneOut {
     int32_t bad;          // non-finite positions seen by the broad phase
     int32_t infeasible;   // energy: a tet with J <= 0 or a pair with d <= 0
     int32_t pcg_done, pcg_iters;
-    int32_t n_heavy;      // incidence rows with more than kHeavyRow entries
+    int32_t n_crow;       // matrix rows with contact entries
     int32_t n_pair;       // pairs in the active arrays: n_act barrier pairs, then the friction pairs
     int32_t pcg_early;    // PCG launches past this iteration check the done flag before any load
                           // (7/8 of the slot's last solve, written by the device; a heuristic only:
                           // a finished solve's launches write nothing either way)
+    int32_t n_cblk;       // contact blocks of all rows
+    int32_t pcg_fail;     // a resident team gave up a wait: the solve is run again by the launched form
     double pinf;          // max |p| over free DOFs
     double alpha_ccd;
     double energy;
@@ -145,18 +158,25 @@ struct SceneDev {
     int32_t *pt_idx;               // surface point index of a vertex (-1: not on the surface)
     // active pairs
     int32_t *act_idx, *act_v;
-    void *act_g, *act_H, *act_y;   // act_y: per-pair products H_p d_p (PCG), 12 per pair, pair-major
+    void *act_g, *act_H;
     int64_t act_cap;
-    double *pcg_pair;              // per-block d.(H_c d) partials of the pair blocks
     // lagged friction set of the step (pairs active at x^t): 4 vertex ids,
     // closest-point coefficients, unit normal, normal-force magnitude
     int32_t *fric_v;
     double *fric_c, *fric_nrm, *fric_lam;
     int64_t fric_cap;
     int32_t n_fric;
+    // contact rows: incidence lists of the pairs' free vertices (CSR, c_list =
+    // pair*4 + slot), the rows that have entries, and per row the merged 3x3
+    // blocks of its off-diagonal columns (the row's blocks start at 3 c_ptr[row])
     int32_t *c_ptr, *c_cnt, *c_list, *c_row, *c_tmp;
-    int32_t *hflag, *heavy_idx, *heavy_rows;  // heavy incidence rows: flag, index (scan), list
-    double *hdiag;                            // 9 contact diagonal sums per heavy row
+    int32_t *c_rows;               // rows with entries (in no particular order)
+    int32_t *c_n;                  // blocks of a row (rows with entries)
+    int32_t *c_col;                // column of a block
+    void *c_val;                   // its 9 values
+    void *c_q;                     // contact part of q (PCG), 4 values per vertex
+    double *pcg_cpart;             // its d.q partial per chunk
+    double *c_grad, *c_diag;       // per vertex: contact gradient (3) and diagonal block (9)
     // multilevel additive preconditioner: nested aggregates of the free gel
     // vertices (level 0 = cells of twice the mean edge, doubling per level);
     // aggregates are numbered level-major (global id = mas_off[l] + local id).
@@ -179,7 +199,18 @@ struct SceneDev {
     int mas_nother;                  // vertices outside the aggregates (fixed gel, indenter)
     int32_t *mas_other;              // their ids, ascending
     int32_t *mas_vpos;               // member position of each vertex, -1 outside
-    int pcg_nvp;                     // PCG update blocks before the heavy rows (and their r.z partials)
+    int pcg_nvp;                     // PCG update blocks (and their r.z partials)
+    // PCG sums and the resident team (k_pcg_team.hip): a chunk is team_nt / 2
+    // matrix rows, team_nt / 256 update units; both forms of the solver add each chunk's partials first, then the chunks
+    int team_T;                      // chunks (the team's workgroups)
+    int team_nt;                     // threads of a workgroup
+    int team_fit;                    // 1: the solve can run in one resident launch
+    int team_H, team_A;              // largest column list of a chunk, aggregates of a group (LDS sizes)
+    int team_spin;                   // polls a member waits for its team to form
+    int32_t *team_hptr, *team_hlist; // columns of each chunk's rows (ascending vertex ids)
+    uint16_t *team_lcol;             // BELL column as an index into its chunk's list
+    void *team_z, *team_q;           // z and q of the resident form, 4 values per vertex
+    unsigned long long *team_ll;     // tagged partials: d.q of every chunk, then r.z (two words each)
     // PCG
     void *r, *z, *dA, *dB, *q, *sol;
     double *pcg_part;
@@ -240,6 +271,8 @@ struct Tuning {
     double pcg_first_chunk = 0.875;                 // first PCG chunk: this fraction of the previous solve's count
     double pcg_later_chunk = 0.25;                  // later chunks: this fraction of the remaining count (at least 8)
     double pcg_list_quantile = 0.25;                // in a list: the quantile of the scenes' remaining counts used
+    int team = 1;                                   // 1: solves that fit run in one resident launch
+    int team_spin = 1 << 14;                        // polls a member waits for its team to form
     int from_file = 0;                              // 1 if read from a tuning file
 };
 Tuning tuning_for(int n_verts);  // the tuning file's entry for a scene of n_verts vertices
@@ -364,7 +397,7 @@ enum PhaseKind {
     kPhBody,      // tets + vertices
     kPhEntry,     // stored BELL entries
     kPhSlice,     // SpMV row blocks (kRowsPerBlock rows each)
-    kPhPcgA,      // SpMV row blocks, then pair blocks (PCG A)
+    kPhPcgA,      // SpMV row blocks, then a block per chunk for its contact rows (PCG A)
     kPhPts, kPhEdges, kPhTris, kPhSurf, kPhInd,
     kPhQPts, kPhQEdges,  // broad-phase queries: kLanesQ threads per point / edge
     kPhPrims,     // point, then edge, then triangle blocks
@@ -375,12 +408,13 @@ enum PhaseKind {
     kPhCandSw,    // swept candidates
     kPhAct,       // active pairs, one 64-thread block each
     kPhActT,      // active pairs, kBlock threads
+    kPhCrow,      // contact rows, a block each (in turn when there are more than blocks)
     kPhEnt,       // incidence entries (4 per active pair), kBlock threads
     kPhFric,      // friction pairs, kBlock threads
-    kPhVertH,     // vertex blocks, then one block per heavy incidence row
     kPhMas,       // preconditioner diagonal: a wavefront per level-0 aggregate, a block per coarser one
     kPhMasG,      // preconditioner groups (a block each)
-    kPhPcgB,      // PCG update: groups, vertex blocks, then a block per heavy incidence row
+    kPhPcgB,      // PCG update: groups, then vertex blocks
+    kPhTeam0, kPhTeam1, kPhTeam2, kPhTeam3,  // resident PCG teams: narrow, wide, narrow of one workgroup, wide of one
     kPhOne,       // one block per scene
     kPhTilesT, kPhTilesE, kPhTilesQ, kPhTilesC, kPhTilesA,  // scan tiles
     kPhKinds
@@ -493,14 +527,15 @@ void run_energy(Batch &b, bool trial);
 void launch_energy_body(Batch &b, bool trial);
 
 void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap);
-// per-scene upper bound on heavy incidence rows, from the active-pair count
-inline int heavy_bound(int64_t n_act, int n) { return n_act > 0 ? (int)std::min<int64_t>(n, 4 * n_act / (kHeavyRow + 1) + 1) : 0; }
-void set_heavy_phase(Batch &b);  // kPhVertH from the last read-back active-pair counts
+// resident solves of the scenes with on[i] (host)
+void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on);
+int team_narrow(size_t real);  // threads of a team's narrow workgroups (wide: twice that)
+size_t team_lds_bytes(int nt, int H, int A, size_t real);
+void team_prepare_device();  // dynamic-LDS limit of the team kernels on the current device
 void run_pinf(Batch &b);
 void launch_hess_apply(Batch &b);  // y (S.q) = H v (S.dB)
 
-enum ScanWhich { kScanTri = 0, kScanEdge = 1, kScanQuery = 2, kScanContact = 3, kScanActive = 4, kScanHeavy = 5,
-                 kScanSwFilter = 6 };
+enum ScanWhich { kScanTri = 0, kScanEdge = 1, kScanQuery = 2, kScanContact = 3, kScanActive = 4, kScanSwFilter = 5 };
 // len[s] < 0: scene s sits out; query_sw selects the swept-candidate total
 void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, const std::vector<int64_t> &len, int query_sw = 0);
 

@@ -816,7 +816,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
             int p = e / 12, q = e % 12;
             double val = wb2 * (gs_of(p) * inv2d) * (gs_of(q) * inv2d);
             if (fixed[v[p / 3]] || fixed[v[q / 3]]) val = 0.0;
-            act_H[(int64_t)e * act_cap + k] = (R)val;
+            act_H[144 * k + e] = (R)val;
         }
         return;
     }
@@ -945,7 +945,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
             int i = e / 12, j = e % 12;
             double val = negr ? A[e] : A0[e];
             if (fixed[v[i / 3]] || fixed[v[j / 3]]) val = 0.0;
-            act_H[(int64_t)e * act_cap + k] = (R)val;
+            act_H[144 * k + e] = (R)val;
         }
         if (lane < 12 && fixed[v[lane / 3]]) act_g[(int64_t)lane * act_cap + k] = R(0);
         return;
@@ -1028,7 +1028,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         }
         // Dirichlet vertices drop out (their identity rows live in the elastic matrix)
         if (fixed[v[i / 3]] || fixed[v[j / 3]]) val = 0.0;
-        act_H[(int64_t)e * act_cap + k] = (R)val;
+        act_H[144 * k + e] = (R)val;
     }
     if (lane < 12 && fixed[v[lane / 3]]) act_g[(int64_t)lane * act_cap + k] = R(0);
 }
@@ -1036,8 +1036,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
 
 // Incidence lists of the active pairs' free vertices: a counting pass, a scan
 // into c_ptr, then a fill in arbitrary order (c_tmp) and a rank pass that
-// puts every row's entries in pair order. Rows with more than kHeavyRow
-// entries are flagged and listed (their sums get a block each).
+// puts every row's entries in pair order and lists the rows.
 template <bool FILL>
 __global__ void k_incidence(Launch L)
 {
@@ -1056,22 +1055,6 @@ __global__ void k_incidence(Launch L)
     }
 }
 
-__global__ void k_heavy_flags(Launch L)
-{
-    int lb, s = scene_of_block(L, lb);
-    const SceneDev &S = *L.sc[s];
-    int i = lb * blockDim.x + threadIdx.x;
-    if (i < S.n) S.hflag[i] = S.c_ptr[i + 1] - S.c_ptr[i] > kHeavyRow ? 1 : 0;
-}
-
-__global__ void k_heavy_rows(Launch L)
-{
-    int lb, s = scene_of_block(L, lb);
-    const SceneDev &S = *L.sc[s];
-    int i = lb * blockDim.x + threadIdx.x;
-    if (i < S.n && S.hflag[i]) S.heavy_rows[S.heavy_idx[i]] = i;
-}
-
 // entry t goes to its row's segment at the rank of its key (pair*4 + slot)
 __global__ void k_incidence_rank(Launch L)
 {
@@ -1084,6 +1067,124 @@ __global__ void k_incidence_rank(Launch L)
     int key = S.c_tmp[t], rank = 0;
     for (int u = e0; u < e1; ++u) rank += S.c_tmp[u] < key ? 1 : 0;
     S.c_list[e0 + rank] = key;
+    if (rank == 0) S.c_rows[atomicAdd(&L.out[s].n_crow, 1)] = v;
+}
+
+// Contact rows, a block each: the row's contact gradient and diagonal block
+// summed over its incidence entries, and its off-diagonal blocks merged by
+// column. A dense contact patch gives a row 10 to 400 entries with three
+// other vertices each but only some 20 distinct columns, so the SpMV applies
+// ten to fifty times fewer blocks than pair by pair. The (column, entry)
+// keys of up to kRowSeg entries are sorted in LDS; a column's entries are
+// then one run, in pair order, and a thread per block component adds them in
+// FP64. A row longer than that is merged segment by segment (a column may
+// then have a block per segment).
+constexpr int kRowKeys = 2048;
+static_assert(3 * kRowSeg <= kRowKeys, "a segment's keys fit");
+template <class R>
+__global__ void __launch_bounds__(kBlock) k_contact_rows(Launch L)
+{
+    __shared__ unsigned long long key[kRowKeys];
+    __shared__ int first[kRowKeys + 1];  // first key of each distinct column
+    __shared__ double part[kBlock / 12][12];
+    __shared__ int wsum[kBlock / kWave];
+    int lb, s = scene_of_block(L, lb);
+    const SceneDev &S = *L.sc[s];
+    const R *ag = as<R>(S.act_g), *aH = as<R>(S.act_H);
+    R *cv = as<R>(S.c_val);
+    const int64_t cap = S.act_cap;
+    const int tid = (int)threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int nrow = L.out[s].n_crow, nblk = blocks_of(L, s);
+    int blocks = 0;
+    for (int i = lb; i < nrow; i += nblk) {
+        const int row = S.c_rows[i], e0 = S.c_ptr[row], ne = S.c_ptr[row + 1] - e0;
+        // gradient (components 0..2) and diagonal block (3..11): entries split
+        // over the groups of 12 threads, the groups' sums added in order
+        constexpr int G = kBlock / 12;
+        if (tid < 12 * G) {
+            const int c = tid % 12, g = tid / 12;
+            double acc = 0.0;
+            for (int e = g; e < ne; e += G) {
+                const int src = S.c_list[e0 + e], a = src & 3;
+                const int64_t p = src >> 2;
+                acc += c < 3 ? (double)ag[(int64_t)(3 * a + c) * cap + p]
+                             : (double)aH[144 * p + (3 * a + (c - 3) / 3) * 12 + 3 * a + (c - 3) % 3];
+            }
+            part[g][c] = acc;
+        }
+        __syncthreads();
+        if (tid < 12) {
+            double t = 0.0;
+            for (int g = 0; g < G; ++g) t += part[g][tid];
+            if (tid < 3)
+                S.c_grad[3 * (int64_t)row + tid] = t;
+            else
+                S.c_diag[9 * (int64_t)row + tid - 3] = t;
+        }
+        int out = 0;  // blocks of the row so far
+        for (int seg = 0; seg < ne; seg += kRowSeg) {
+            const int m = 3 * min(kRowSeg, ne - seg);
+            int n2 = 4;
+            while (n2 < m) n2 <<= 1;
+            for (int t = tid; t < n2; t += kBlock) {
+                unsigned long long k = ~0ull;
+                if (t < m) {
+                    const int src = S.c_list[e0 + seg + t / 3], a = src & 3, o = t % 3;
+                    const int col = S.act_v[(int64_t)(o + (o >= a ? 1 : 0)) * cap + (src >> 2)];
+                    if (!S.fixed[col]) k = (unsigned long long)(uint32_t)col << 32 | (uint32_t)t;
+                }
+                key[t] = k;
+            }
+            __syncthreads();
+            for (int w = 2; w <= n2; w <<= 1)  // bitonic sort, ascending
+                for (int h = w >> 1; h > 0; h >>= 1) {
+                    for (int t = tid; t < n2 / 2; t += kBlock) {
+                        const int lo = 2 * t - (t & (h - 1)), hi = lo + h;
+                        const unsigned long long x = key[lo], y = key[hi];
+                        if ((x > y) == ((lo & w) == 0)) {
+                            key[lo] = y;
+                            key[hi] = x;
+                        }
+                    }
+                    __syncthreads();
+                }
+            // distinct columns: where a key's column differs from the one before
+            int nu = 0;
+            for (int base = 0; base < n2; base += kBlock) {
+                const int t = base + tid;
+                const unsigned long long k = t < n2 ? key[t] : ~0ull;
+                const bool head = k != ~0ull && (t == 0 || (key[t - 1] >> 32) != (k >> 32));
+                const unsigned long long bal = __ballot(head);
+                if (lane == 0) wsum[wave] = __popcll(bal);
+                __syncthreads();
+                int before = nu, all = nu;
+                for (int v = 0; v < kBlock / kWave; ++v) {
+                    if (v < wave) before += wsum[v];
+                    all += wsum[v];
+                }
+                if (head) first[before + __popcll(bal & ((1ull << lane) - 1))] = t;
+                nu = all;
+                __syncthreads();
+            }
+            for (int j = tid; j < nu; j += kBlock) S.c_col[3 * (int64_t)e0 + out + j] = (int)(key[first[j]] >> 32);
+            for (int x = tid; x < 9 * nu; x += kBlock) {
+                const int j = x / 9, c = x - 9 * j;
+                const unsigned long long col = key[first[j]] >> 32;
+                double acc = 0.0;
+                for (int t = first[j]; t < n2 && (key[t] >> 32) == col; ++t) {
+                    const int q = (int)(uint32_t)key[t], src = S.c_list[e0 + seg + q / 3], a = src & 3, o = q % 3;
+                    const int b = o + (o >= a ? 1 : 0);
+                    acc += (double)aH[144 * (int64_t)(src >> 2) + (3 * a + c / 3) * 12 + 3 * b + c % 3];
+                }
+                cv[9 * (3 * (int64_t)e0 + out + j) + c] = (R)acc;
+            }
+            out += nu;
+            __syncthreads();
+        }
+        if (tid == 0) S.c_n[row] = out;
+        blocks += out;
+    }
+    if (tid == 0 && blocks) atomicAdd(&L.out[s].n_cblk, blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,7 +1289,7 @@ __global__ void __launch_bounds__(kBlock) k_friction(Launch L)
             for (int b = 0; b < 4; ++b)
                 for (int k = 0; k < 3; ++k) {
                     double h = (fx[a] || fx[b]) ? 0.0 : ml * c[a] * c[b] * M[3 * i + k];
-                    act_H[(int64_t)((3 * a + i) * 12 + 3 * b + k) * cap + q] = (R)h;
+                    act_H[144 * q + (3 * a + i) * 12 + 3 * b + k] = (R)h;
                 }
 }
 
@@ -1196,7 +1297,10 @@ __global__ void k_set_npair(Launch one)
 {
     int lb, s = scene_of_block(one, lb);
     const SceneDev &S = *one.sc[s];
-    if (threadIdx.x == 0) one.out[s].n_pair = one.out[s].n_act + S.n_fric;
+    if (threadIdx.x == 0) {
+        one.out[s].n_pair = one.out[s].n_act + S.n_fric;
+        one.out[s].n_crow = one.out[s].n_cblk = 0;  // counted by the incidence passes that follow
+    }
 }
 
 // friction energy partials, after the body and barrier partials
@@ -1579,26 +1683,18 @@ void launch_contact_incidence(Batch &b)
     IPC_LAUNCH(b, k_zero, kPhTilesC, kBlock, 2);
     IPC_LAUNCH(b, k_incidence<false>, kPhActT, kBlock);
     segmented_scan(b, kScanContact, kPhTilesC, len);
-    IPC_LAUNCH(b, k_heavy_flags, kPhVert, kBlock);
-    segmented_scan(b, kScanHeavy, kPhTilesC, len);
-    IPC_LAUNCH(b, k_heavy_rows, kPhVert, kBlock);
     b.set_phase(kPhTilesC, nz);
     IPC_LAUNCH(b, k_zero, kPhTilesC, kBlock, 2);
     IPC_LAUNCH(b, k_incidence<true>, kPhActT, kBlock);
     IPC_LAUNCH(b, k_incidence_rank, kPhEnt, kBlock);
-    set_heavy_phase(b);
-}
-
-void set_heavy_phase(Batch &b)
-{
-    size_t ns = b.sc.size();
-    std::vector<int32_t> nh(ns);
-    for (size_t i = 0; i < ns; ++i) {
-        bool on = b.h_off[kPhVert][i + 1] > b.h_off[kPhVert][i];
-        const SceneDev &H = b.sc[i]->h;
-        nh[i] = on ? H.nb_vert + heavy_bound(pair_count(*b.sc[i], b.h_out[i]), H.n) : 0;
-    }
-    b.set_phase(kPhVertH, nh);
+    std::vector<int32_t> nr(ns);
+    for (size_t i = 0; i < ns; ++i)  // at most an entry a row; 1,024 blocks take rows in turn
+        nr[i] = na[i] ? (int32_t)std::min<int64_t>(4 * pair_count(*b.sc[i], b.h_out[i]), 1024) : 0;
+    b.set_phase(kPhCrow, nr);
+    if (mixed(b))
+        IPC_LAUNCH(b, k_contact_rows<float>, kPhCrow, kBlock);
+    else
+        IPC_LAUNCH(b, k_contact_rows<double>, kPhCrow, kBlock);
 }
 
 void launch_friction_lag(Batch &b)

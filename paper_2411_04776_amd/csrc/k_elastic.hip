@@ -20,7 +20,6 @@
 // Element outputs are written SoA (component-major) and summed per matrix
 // block / per vertex by gather kernels in a fixed order: no float atomics.
 #include "device_util.h"
-#include "incidence.h"
 #include "ipc_internal.h"
 
 namespace ipcg {
@@ -287,10 +286,8 @@ __global__ void __launch_bounds__(kBlock) k_elastic_elements(Launch L)
 }
 
 // Gradient gather: one thread per vertex; elastic element gradients in
-// vertex-incidence (tet) order, then inertia / kinematic target, then the sum
-// of the vertex's active contact pairs in pair order. Sums in FP64,
-// stored in R. A heavy incidence row gets a block of its own after the vertex
-// blocks, which also sums the contact diagonal blocks of that row (hdiag).
+// vertex-incidence (tet) order, then inertia / kinematic target, then the
+// vertex's contact gradient (k_contact_rows). Sums in FP64, stored in R.
 template <class R>
 __device__ __forceinline__ void vertex_gradient(const SceneDev &S, int i, double g[3])
 {
@@ -311,49 +308,34 @@ __device__ __forceinline__ void vertex_gradient(const SceneDev &S, int i, double
     }
 }
 
+// contact entries of a matrix row
+__device__ __forceinline__ bool has_contact(const SceneDev &S, int row) { return S.c_ptr[row + 1] > S.c_ptr[row]; }
+
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_assemble_gradient(Launch L)
 {
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
-    const R *ag = as<R>(S.act_g), *aH = as<R>(S.act_H);
-    const int64_t cap = S.act_cap;
     R *grad = as<R>(S.grad);
-    if (lb < S.nb_vert) {
-        int i = lb * blockDim.x + threadIdx.x;
-        if (i >= S.n || S.hflag[i]) return;
-        double g[3] = {0.0, 0.0, 0.0};
-        if (!S.fixed[i]) {
-            double gc[3] = {0.0, 0.0, 0.0};
-            thread_row_sums<3>(S, i, [&](int p, int a, int c) { return (double)ag[(int64_t)(a * 3 + c) * cap + p]; }, gc);
-            vertex_gradient<R>(S, i, g);
-            for (int c = 0; c < 3; ++c) g[c] += gc[c];
-        }
-        for (int c = 0; c < 3; ++c) grad[3 * i + c] = (R)g[c];
-    } else {
-        int j = lb - S.nb_vert;
-        if (j >= L.out[s].n_heavy) return;
-        int row = S.heavy_rows[j];  // never a fixed vertex: those have no incidence entries
-        double gc[12];
-        block_row_sums<12>(S, row,
-                           [&](int p, int a, int c) {
-                               if (c < 3) return (double)ag[(int64_t)(a * 3 + c) * cap + p];
-                               int ii = (c - 3) / 3, jj = (c - 3) % 3;
-                               return (double)aH[(int64_t)((3 * a + ii) * 12 + 3 * a + jj) * cap + p];
-                           },
-                           gc);
-        if (threadIdx.x == 0) {
-            double g[3] = {0.0, 0.0, 0.0};
-            vertex_gradient<R>(S, row, g);
-            for (int c = 0; c < 3; ++c) grad[3 * row + c] = (R)(g[c] + gc[c]);
-            for (int c = 0; c < 9; ++c) S.hdiag[9 * (int64_t)j + c] = gc[3 + c];
-        }
+    if (lb == 0 && threadIdx.x == 0) {  // the solve that follows starts from a clean state
+        S.pcg->join = 0;
+        L.out[s].pcg_done = L.out[s].pcg_iters = L.out[s].pcg_fail = 0;
+        L.out[s].pinf = 0.0;
     }
+    int i = lb * blockDim.x + threadIdx.x;
+    if (i >= S.n) return;
+    double g[3] = {0.0, 0.0, 0.0};
+    if (!S.fixed[i]) {
+        vertex_gradient<R>(S, i, g);
+        if (has_contact(S, i))
+            for (int c = 0; c < 3; ++c) g[c] += S.c_grad[3 * (int64_t)i + c];
+    }
+    for (int c = 0; c < 3; ++c) grad[3 * i + c] = (R)g[c];
 }
 
 // Matrix gather: one thread per stored BELL block. Sums the element blocks
 // listed for this (row, col) in tet order; the diagonal block also takes the
-// inertia / target term and the contact diagonal blocks, and writes the
+// inertia / target term and the contact diagonal block, and writes the
 // inverse used by the block-Jacobi preconditioner. Fixed rows/cols become
 // identity / zero.
 template <class R>
@@ -374,25 +356,7 @@ __global__ void __launch_bounds__(kBlock) k_assemble_bell(Launch L)
     int row = lo * kSlice + lane;
     int k = (int)(slot - S.slice_ptr[lo]);
     int col = S.bcol[slot_lane];
-    const R *eH = as<R>(S.eH), *aH = as<R>(S.act_H);
-    // contact diagonal blocks (slot 0 is the diagonal)
-    double cd[9];
-    for (int c = 0; c < 9; ++c) cd[c] = 0.0;
-    if (k == 0 && row < S.n) {
-        const int64_t cap = S.act_cap;
-        if (S.hflag[row]) {  // summed by the row's own block in the gradient kernel
-            for (int c = 0; c < 9; ++c) cd[c] = S.hdiag[9 * (int64_t)S.heavy_idx[row] + c];
-        } else {
-            // one entry's nine loads at a time: four entries in flight held
-            // registers for half of the kernel's resident wavefronts, and
-            // only the diagonal lanes of contact rows take this path
-            auto dblk = [&](int p, int a, int c) {
-                int i = c / 3, j = c % 3;
-                return (double)aH[(int64_t)((3 * a + i) * 12 + 3 * a + j) * cap + p];
-            };
-            thread_row_sums<9, decltype(dblk), 1>(S, row, dblk, cd);
-        }
-    }
+    const R *eH = as<R>(S.eH);
     double A[9];
     for (int c = 0; c < 9; ++c) A[c] = 0.0;
     if (col >= 0) {
@@ -414,7 +378,8 @@ __global__ void __launch_bounds__(kBlock) k_assemble_bell(Launch L)
             A[0] += dk;
             A[4] += dk;
             A[8] += dk;
-            for (int c = 0; c < 9; ++c) A[c] += cd[c];
+            if (has_contact(S, row))
+                for (int c = 0; c < 9; ++c) A[c] += S.c_diag[9 * (int64_t)row + c];
         }
         if (S.fixed[row] || S.fixed[col]) {
             for (int c = 0; c < 9; ++c) A[c] = 0.0;
@@ -533,10 +498,10 @@ void launch_assemble(Batch &b)
     hipEvent_t ev[2];
     b.prof_begin(kProfAssemble, ev);
     if (mixed(b)) {
-        IPC_LAUNCH(b, k_assemble_gradient<float>, kPhVertH, kBlock);
+        IPC_LAUNCH(b, k_assemble_gradient<float>, kPhVert, kBlock);
         IPC_LAUNCH(b, k_assemble_bell<float>, kPhEntry, kBlock);
     } else {
-        IPC_LAUNCH(b, k_assemble_gradient<double>, kPhVertH, kBlock);
+        IPC_LAUNCH(b, k_assemble_gradient<double>, kPhVert, kBlock);
         IPC_LAUNCH(b, k_assemble_bell<double>, kPhEntry, kBlock);
     }
     launch_mas_diag(b);

@@ -8,14 +8,11 @@
 //          the previous iteration in a fixed order (all agree bit for bit;
 //          no block barrier before the real work) and decides the stop;
 //          block 0 keeps r.z for the next launches; a row block then forms d = z + beta
-//          d_prev for its rows and for the columns it gathers and applies the
-//          elastic BELL matrix (eight lanes per row), a pair block applies
-//          each active pair's off-diagonal blocks to its own four vertices;
-//          both write their d.q partials;
+//          d_prev for its rows and for the columns it gathers, applies the
+//          elastic BELL matrix and the merged contact blocks, and writes its
+//          d.q partial;
 //   B(it): every wavefront reduces the scene's d.q partials, alpha = rz / dq,
-//          each wavefront adds its rows' incident pair products to q
-//          (segmented over the incidence lists), then p += alpha d,
-//          r -= alpha q, z = M^-1 r and the r.z partials.
+//          then p += alpha d, r -= alpha q, z = M^-1 r and the r.z partials.
 // Kernel boundaries cost ~3 us on MI355X against 8-28 us for a cooperative
 // grid-wide barrier, so an iteration is two launches rather than one
 // persistent kernel. The host launches chunks of iterations and reads the
@@ -24,8 +21,8 @@
 #include <algorithm>
 
 #include "device_util.h"
-#include "incidence.h"
 #include "ipc_internal.h"
+#include "pcg_sums.h"
 
 namespace ipcg {
 
@@ -36,15 +33,11 @@ __device__ __forceinline__ R *as(void *p)
 }
 
 // partial-sum layout in pcg_part: [d.q of the row blocks: nb_rows][r.z slot 0][r.z slot 1], an
-// r.z slot holding the pcg_nvp update-block partials then one per heavy row (n + 1 room);
-// the pair blocks' d.(H_c d) partials live in pcg_pair
+// r.z slot holding the pcg_nvp update-block partials
 __device__ __forceinline__ double *rz_slot(const SceneDev &S, int it)
 {
-    return S.pcg_part + S.nb_rows + (size_t)(it & 1) * ((size_t)S.pcg_nvp + S.n + 1);
+    return S.pcg_part + S.nb_rows + (size_t)(it & 1) * (size_t)S.pcg_nvp;
 }
-
-// pair blocks of PCG A for n pairs
-__device__ __forceinline__ int pair_blocks(int64_t n) { return (int)((n + kPairsPerBlock - 1) / kPairsPerBlock); }
 
 // Partial product of one BELL row: stream `part` of the row's kSpmvStreams
 // takes slots part, part + kSpmvStreams, ... The vector applied is
@@ -62,16 +55,17 @@ __device__ __forceinline__ void bell_row_part(const SceneDev &S, int row, int pa
     for (int slot = s0 + part; slot < s1; slot += kSpmvStreams) {
         int col = bcol[(int64_t)slot * kSlice + lane];
         if (col >= 0) {
-            const R *A = bval + (int64_t)slot * 9 * kSlice + lane;
+            const R *from = bval + (int64_t)slot * 9 * kSlice + lane;
+            R A[9];
+#pragma unroll
+            for (int e = 0; e < 9; ++e) A[e] = from[e * kSlice];
             R v0 = z[3 * col], v1 = z[3 * col + 1], v2 = z[3 * col + 2];
             if (beta_on) {
                 v0 += beta * dold[3 * col];
                 v1 += beta * dold[3 * col + 1];
                 v2 += beta * dold[3 * col + 2];
             }
-            y0 += A[0 * kSlice] * v0 + A[1 * kSlice] * v1 + A[2 * kSlice] * v2;
-            y1 += A[3 * kSlice] * v0 + A[4 * kSlice] * v1 + A[5 * kSlice] * v2;
-            y2 += A[6 * kSlice] * v0 + A[7 * kSlice] * v1 + A[8 * kSlice] * v2;
+            block_fma(A, v0, v1, v2, y0, y1, y2);
         }
     }
     y[0] = y0;
@@ -99,14 +93,10 @@ __device__ __forceinline__ void bell_row_part2(const SceneDev &S, int row, int p
 #pragma unroll
             for (int k = 0; k < 9; ++k) m[k] = A[k * kSlice];
             R v0 = z[3 * col], v1 = z[3 * col + 1], v2 = z[3 * col + 2];
-            a0 += m[0] * v0 + m[1] * v1 + m[2] * v2;
-            a1 += m[3] * v0 + m[4] * v1 + m[5] * v2;
-            a2 += m[6] * v0 + m[7] * v1 + m[8] * v2;
+            block_fma(m, v0, v1, v2, a0, a1, a2);
             if (two) {
                 R w0 = dold[3 * col], w1 = dold[3 * col + 1], w2 = dold[3 * col + 2];
-                b0 += m[0] * w0 + m[1] * w1 + m[2] * w2;
-                b1 += m[3] * w0 + m[4] * w1 + m[5] * w2;
-                b2 += m[6] * w0 + m[7] * w1 + m[8] * w2;
+                block_fma(m, w0, w1, w2, b0, b1, b2);
             }
         }
     }
@@ -146,14 +136,10 @@ __device__ __forceinline__ void bell_row_both(const SceneDev &S, int row, const 
 #pragma unroll
             for (int e = 0; e < 9; ++e) m[e] = __builtin_nontemporal_load(A + e * kSlice);  // read once per launch
             R v0 = z[3 * col[k]], v1 = z[3 * col[k] + 1], v2 = z[3 * col[k] + 2];
-            a[k][0] += m[0] * v0 + m[1] * v1 + m[2] * v2;
-            a[k][1] += m[3] * v0 + m[4] * v1 + m[5] * v2;
-            a[k][2] += m[6] * v0 + m[7] * v1 + m[8] * v2;
+            block_fma(m, v0, v1, v2, a[k][0], a[k][1], a[k][2]);
             if (two) {
                 R w0 = dold[3 * col[k]], w1 = dold[3 * col[k] + 1], w2 = dold[3 * col[k] + 2];
-                c[k][0] += m[0] * w0 + m[1] * w1 + m[2] * w2;
-                c[k][1] += m[3] * w0 + m[4] * w1 + m[5] * w2;
-                c[k][2] += m[6] * w0 + m[7] * w1 + m[8] * w2;
+                block_fma(m, w0, w1, w2, c[k][0], c[k][1], c[k][2]);
             }
         }
     }
@@ -166,81 +152,43 @@ __device__ __forceinline__ void bell_row_both(const SceneDev &S, int row, const 
         }
 }
 
-// One active pair: y_a = sum over b != a of H_ab d_b for its four slots
-// (the diagonal blocks live in the BELL diagonal), stored per pair for the
-// row gather; returns sum_a d_a . y_a.
-template <class R>
-__device__ __forceinline__ double pair_apply(const SceneDev &S, int64_t p, const R *__restrict__ z,
-                                             const R *__restrict__ dold, R beta, bool beta_on)
-{
-    const int64_t cap = S.act_cap;
-    const R *__restrict__ H = as<R>(S.act_H);
-    R *__restrict__ Y = as<R>(S.act_y);
-    R d[4][3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        int v = S.act_v[(int64_t)a * cap + p];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) d[a][c] = beta_on ? z[3 * v + c] + beta * dold[3 * v + c] : z[3 * v + c];
-    }
-    double dy = 0.0;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        double y[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            if (b == a) continue;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const R *h = H + (int64_t)((3 * a + i) * 12 + 3 * b) * cap + p;
-                y[i] += (double)(h[0] * d[b][0] + h[cap] * d[b][1] + h[2 * cap] * d[b][2]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            R yv = (R)y[i];
-            Y[12 * p + 3 * a + i] = yv;  // a pair's 12 products together: a row gathers 3 adjacent values
-            dy += (double)d[a][i] * (double)yv;
-        }
-    }
-    return dy;
-}
-
-// PCG A(it): a row block first applies the BELL matrix to z and to d_prev
-// (no scalar needed), then every wavefront reduces the r.z partials, decides
-// the stop and forms beta; the row block finishes d = z + beta d_prev and
-// q = K_el d for its rows, a pair block applies each active pair's
-// off-diagonal blocks to its own four vertices; both write d.q partials.
+// PCG A(it): every wavefront reduces the r.z partials, decides the stop and
+// forms beta; a row block forms its rows' d = z + beta d_prev and q = K_el d,
+// a chunk block the contact part of q for its chunk's contact rows; both
+// write a d.q partial. A scene that also fits the
+// resident form applies the matrix to d, as that form does; a larger one
+// applies it to z and to d_prev before beta is known.
 // LPR lanes per row (1: a thread runs both slot streams, for coalesced rows in
 // large lists; 2: a lane per stream, for latency): the arithmetic is the same
-// (streams added in order, the block's d.q summed by one wavefront over its 64
-// rows or pairs), so a scene gets the same bits in either form.
+// (streams added in order, each 32 rows' d.q summed by one fixed tree, the
+// halves of a block added), so a scene gets the same bits in either form.
+constexpr int kPassRows = 256;  // contact rows of a chunk handled at a time (a multiple of the wavefront)
 template <class R, int LPR>
 __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it, int early)
 {
     constexpr int NP = kSpmvStreams / LPR;  // streams per thread
-    __shared__ double sdq[kRowsPerBlock];
+    __shared__ double sdq[2], cdot[kPassRows];
+    __shared__ CRow clist[kPassRows];
+    __shared__ int ccnt[kRowsPerBlock * LPR / kWave];
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
     // launches past the expected count of this scene's solve: a finished solve costs nothing
     if ((early || it > L.out[s].pcg_early) && S.pcg->done) return;
-    // the previous launch's r.z partials load before the matrix rows
-    const int nrz = S.pcg_nvp + L.out[s].n_heavy;
-    double rzp[2];
-    wave_partials_load<2>(rz_slot(S, it - 1), nrz, rzp);
     const R *z = as<R>(S.z);
     const R *dold = as<R>((it & 1) ? S.dB : S.dA);
-    const bool bon = it > 1;
+    const bool bon = it > 1, on_d = S.team_fit != 0;
     const int t = (int)threadIdx.x, rloc = t / LPR, part0 = t % LPR;
-    int row = lb * kRowsPerBlock + rloc;
-    bool rows = lb < S.nb_rows;
-    bool live = rows && row < S.n;
+    const int row = lb * kRowsPerBlock + rloc;
+    const bool live = lb < S.nb_rows && row < S.n;
     double yz[NP][3], yd[NP][3];
 #pragma unroll
     for (int q = 0; q < NP; ++q)
 #pragma unroll
         for (int c = 0; c < 3; ++c) yz[q][c] = yd[q][c] = 0.0;
-    if (live) {
+    const int lane = t & (kWave - 1);
+    double rzp[2];
+    if (!on_d) flat_load<2>(rz_slot(S, it - 1), S.pcg_nvp, lane, kWave, rzp);
+    if (live && !on_d) {
         if constexpr (NP == 2)
             bell_row_both<R>(S, row, z, dold, bon, yz, yd);
         else
@@ -248,9 +196,10 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
     }
     if (S.pcg->done) return;
     double beta = 0.0;
+    const double rz_cur = on_d ? sum_rz(S, rz_slot(S, it - 1))
+                               : wave_sum(flat_sum<2>(rz_slot(S, it - 1), S.pcg_nvp, lane, kWave, rzp));
     if (it == 1) {
-        double rz0 = wave_partials_sum<2>(rz_slot(S, 0), nrz, rzp);
-        if (!(rz0 > 0.0)) {
+        if (!(rz_cur > 0.0)) {
             if (lb == 0 && t == 0) {
                 S.pcg->done = 1;
                 S.pcg->iters = 0;
@@ -260,11 +209,10 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
             return;
         }
         if (lb == 0 && t == 0) {
-            S.pcg->stop = S.pcg_tol2 * rz0;
-            S.pcg->rzv[1] = rz0;
+            S.pcg->stop = S.pcg_tol2 * rz_cur;
+            S.pcg->rzv[1] = rz_cur;
         }
     } else {
-        double rz_cur = wave_partials_sum<2>(rz_slot(S, it - 1), nrz, rzp);
         bool conv = rz_cur <= S.pcg->stop;
         if (conv || it > S.pcg_maxit) {  // converged, or the scene's iteration cap is spent
             if (lb == 0 && t == 0) {
@@ -281,68 +229,69 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
         beta = rz_cur / rz_prev;
         if (lb == 0 && t == 0) S.pcg->rzv[it & 1] = rz_cur;
     }
-    R rb = (R)beta;
-    double dq = 0.0;
-    if (rows) {
-        R *dnew = as<R>((it & 1) ? S.dA : S.dB);
-        R *q = as<R>(S.q);
-        double y[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            y[c] = yz[0][c] + beta * yd[0][c];
-#pragma unroll
-            for (int k = 1; k < NP; ++k) y[c] += yz[k][c] + beta * yd[k][c];
-            if (LPR == 2) y[c] += __shfl_xor(y[c], 1, kWave);
-        }
-        if (live && part0 == 0) {
-            for (int c = 0; c < 3; ++c) {
-                R dv = bon ? z[3 * row + c] + rb * dold[3 * row + c] : z[3 * row + c];
-                R qv = (R)y[c];
-                dnew[3 * row + c] = dv;
-                q[3 * row + c] = qv;
-                dq += (double)dv * (double)qv;
-            }
-        }
-        if (LPR == 2) {
-            if (part0 == 0) sdq[rloc] = dq;
+    const R rb = (R)beta;
+    if (lb >= S.nb_rows) {  // the chunk's contact rows
+        constexpr int NT = kRowsPerBlock * LPR;
+        const int c = lb - S.nb_rows;
+        auto dir = [&](int v, R (&d)[3]) {
+            for (int k = 0; k < 3; ++k) d[k] = bon ? z[3 * v + k] + rb * dold[3 * v + k] : z[3 * v + k];
+        };
+        auto put = [&](int v, const R (&y)[3]) {
+            for (int k = 0; k < 3; ++k) as<R>(S.c_q)[4 * (int64_t)v + k] = y[k];
+        };
+        double t_dq = 0.0;
+        for (int skip = 0;; skip += kPassRows) {
+            const int n = chunk_contact_rows<NT, kPassRows>(S, c, skip, clist, ccnt), m = min(n, kPassRows);
+            const auto cc = glob((const int32_t *)S.c_col);
+            contact_rows<NT, R>(glob((const R *)as<R>(S.c_val)), cc, clist, m, t, contact_first(cc, clist, m, t), dir, put,
+                                cdot);
             __syncthreads();
-            if (t < kWave) dq = sdq[t];
+            contact_dots(cdot, m, t_dq);
+            if (n <= kPassRows) break;
+            __syncthreads();
         }
-        if (t < kWave) {
-            dq = wave_sum(dq);
-            if (t == 0) S.pcg_part[lb] = dq;
+        t_dq = wave_sum(t_dq);
+        if (t == 0) S.pcg_cpart[c] = t_dq;
+        return;
+    }
+    double dq = 0.0;
+    R *dnew = as<R>((it & 1) ? S.dA : S.dB);
+    R *q = as<R>(S.q);
+    if (live && on_d) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) bell_row_part<R>(S, row, part0 + k, z, dold, rb, bon, yz[k]);
+    }
+    double y[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        y[c] = yz[0][c] + beta * yd[0][c];
+#pragma unroll
+        for (int k = 1; k < NP; ++k) y[c] += yz[k][c] + beta * yd[k][c];
+        if (LPR == 2) y[c] += __shfl_xor(y[c], 1, kWave);
+    }
+    if (live && part0 == 0) {
+        for (int c = 0; c < 3; ++c) {
+            R dv = bon ? z[3 * row + c] + rb * dold[3 * row + c] : z[3 * row + c];
+            R qv = (R)y[c];
+            dnew[3 * row + c] = dv;
+            q[3 * row + c] = qv;
+            dq += (double)dv * (double)qv;
         }
+    }
+    if (LPR == 2) {
+        dq = wave_sum(dq);  // 32 rows
+        if (t % kWave == 0) sdq[t / kWave] = dq;
+        __syncthreads();
+        if (t == 0) S.pcg_part[lb] = sdq[0] + sdq[1];
     } else {
-        int pb = lb - S.nb_rows;
-        int64_t p = (int64_t)pb * kPairsPerBlock + t;
-        if (t < kPairsPerBlock && p < L.out[s].n_pair) dq = pair_apply<R>(S, p, z, dold, rb, bon);
-        if (t < kWave) {
-            dq = wave_sum(dq);
-            if (t == 0) S.pcg_pair[pb] = dq;
-        }
+        dq = half_wave_sum(dq);
+        dq += __shfl(dq, 32, kWave);
+        if (t == 0) S.pcg_part[lb] = dq;
     }
 }
 
-// the incident pairs' (H_p d_p)_i of a light row, by one thread (two entries
-// in flight: the update kernel holds a vertex's PCG state meanwhile, and its
-// register count sets how many blocks a CU keeps resident)
-template <class R>
-__device__ __forceinline__ void contact_row_light(const SceneDev &S, int row, double qc[3])
-{
-    const R *Y = as<R>(S.act_y);
-    auto val = [&](int p, int a, int c) { return (double)Y[12 * (int64_t)p + 3 * a + c]; };
-    thread_row_sums<3, decltype(val), 2>(S, row, val, qc);
-}
-
-// the same sum for one heavy row, by the whole block
-template <class R>
-__device__ __forceinline__ void contact_row_heavy(const SceneDev &S, int row, double qc[3])
-{
-    const R *Y = as<R>(S.act_y);
-    block_row_sums<3>(S, row, [&](int p, int a, int c) { return (double)Y[12 * (int64_t)p + 3 * a + c]; }, qc);
-}
-
-// one vertex's state for the update, loaded before alpha is known
+// one vertex's state for the update, loaded before alpha is known (q: both
+// its elastic and its contact part)
 template <class R>
 struct VertexPcg {
     R q[3], d[3], p[3], r[3], M[9];
@@ -359,20 +308,20 @@ __device__ __forceinline__ void pcg_vertex_load(const SceneDev &S, int i, const 
         v.p[c] = sol[3 * i + c];
         v.r[c] = r[3 * i + c];
     }
+    if (glob(S.c_ptr)[i + 1] > glob(S.c_ptr)[i])
+        for (int c = 0; c < 3; ++c) v.q[c] += glob(as<R>(S.c_q))[4 * (int64_t)i + c];
     for (int k = 0; k < 9; ++k) v.M[k] = Mi[9 * i + k];
 }
 
-// p += alpha d, r -= alpha q (q = K_el d + contact sum), z = M^-1 r; returns r.z
+// p += alpha d, r -= alpha q, z = M^-1 r; returns r.z
 template <class R>
-__device__ __forceinline__ double pcg_vertex_update(const SceneDev &S, int i, R alpha, const VertexPcg<R> &v,
-                                                    const double qc[3])
+__device__ __forceinline__ double pcg_vertex_update(const SceneDev &S, int i, R alpha, const VertexPcg<R> &v)
 {
     const auto sol = glob(as<R>(S.sol)), r = glob(as<R>(S.r)), z = glob(as<R>(S.z));
     R ri[3];
     for (int c = 0; c < 3; ++c) {
-        R qv = (R)((double)v.q[c] + qc[c]);
         sol[3 * i + c] = v.p[c] + alpha * v.d[c];
-        ri[c] = v.r[c] - alpha * qv;
+        ri[c] = v.r[c] - alpha * v.q[c];
         r[3 * i + c] = ri[c];
     }
     double rz = 0.0;
@@ -476,72 +425,36 @@ __global__ void __launch_bounds__(kBlock) k_mas_invert(Launch L)
 }
 
 // ---- PCG B(it) --------------------------------------------------------------
-// Blocks of a scene: [preconditioner groups | vertex blocks | a block per heavy
-// incidence row]. With the multilevel preconditioner the vertex blocks cover
+// Blocks of a scene: [preconditioner groups | vertex blocks]. With the
+// multilevel preconditioner the vertex blocks cover
 // the vertices outside the aggregates; without it, every vertex. Every block
 // loads its vertices' data and contact sums first, then alpha from the d.q
 // partials, then p += alpha d, r -= alpha q, z = D^-1 r (plus, in a group,
 // the aggregate corrections) and its r.z partial. B(0) starts the solve
 // from p = 0, r = -g instead.
 
-// alpha = r.z / d.q for iteration it, d.q from the A launch's partials (its
-// SpMV blocks, then its pair blocks) summed by the whole block: thread t adds
-// partials t, t + 256, ... in order, a wavefront tree, then the wavefronts in
-// order, so every block of the scene forms the same value. dq_issue loads a
-// thread's first partials, the scene's done flag and r.z of iteration it - 1
-// before the block's vertex loads; dq_stage adds them (and any rest) after
-// those and leaves the wavefront sums in LDS; dq_alpha, after a block
-// barrier, forms alpha.
-constexpr int kDqU = 4;   // SpMV-block partials per thread in flight (1024: a scene of 65k vertices; the rest after)
-constexpr int kDqUP = 1;  // pair-block partials per thread in flight
-struct DqIssue {
-    double part[kDqU], pair[kDqUP];
-    double rz;
-    int done;
-};
-
-__device__ __forceinline__ void dq_issue(const Launch &L, const SceneDev &S, int s, int it, DqIssue &q)
-{
-    const int t = (int)threadIdx.x, npart = S.nb_rows, npair = pair_blocks(L.out[s].n_pair);
-#pragma unroll
-    for (int u = 0; u < kDqU; ++u) q.part[u] = t + u * kBlock < npart ? glob(S.pcg_part)[t + u * kBlock] : 0.0;
-#pragma unroll
-    for (int u = 0; u < kDqUP; ++u) q.pair[u] = t + u * kBlock < npair ? glob(S.pcg_pair)[t + u * kBlock] : 0.0;
-    q.rz = glob(S.pcg)->rzv[it & 1];  // stored by A(it)
-    q.done = glob(S.pcg)->done;
-}
-
-__device__ __forceinline__ void dq_stage(const Launch &L, const SceneDev &S, int s, const DqIssue &q,
-                                         double (&sh)[kBlock / kWave][2])
-{
-    const int t = (int)threadIdx.x, npart = S.nb_rows, npair = pair_blocks(L.out[s].n_pair);
-    double a = 0.0, b = 0.0;
-#pragma unroll
-    for (int u = 0; u < kDqU; ++u)
-        if (t + u * kBlock < npart) a += q.part[u];
-    for (int i = t + kDqU * kBlock; i < npart; i += kBlock) a += glob(S.pcg_part)[i];
-#pragma unroll
-    for (int u = 0; u < kDqUP; ++u)
-        if (t + u * kBlock < npair) b += q.pair[u];
-    for (int i = t + kDqUP * kBlock; i < npair; i += kBlock) b += glob(S.pcg_pair)[i];
-    a = wave_sum(a);
-    b = wave_sum(b);
-    if ((t & (kWave - 1)) == 0) {
-        sh[t / kWave][0] = a;
-        sh[t / kWave][1] = b;
-    }
-}
-
+// alpha = r.z / d.q of iteration it, d.q from the A launch's partials; every
+// wavefront forms the same value
+// in a scene without a resident form the whole block sums them, its first
+// loads (pcg_alpha_load) issued before the vertices' data
 template <class R>
-__device__ __forceinline__ R dq_alpha(const DqIssue &q, const double (&sh)[kBlock / kWave][2])
+__device__ __forceinline__ R pcg_alpha(const SceneDev &S, bool contact, int it, const double (&a)[4])
 {
-    double a = 0.0, b = 0.0;
-#pragma unroll
-    for (int w = 0; w < kBlock / kWave; ++w) {
-        a += sh[w][0];
-        b += sh[w][1];
+    double dq;
+    if (S.team_fit) {
+        dq = sum_dq(S, contact);
+    } else {
+        const int t = (int)threadIdx.x;
+        dq = flat_sum<4>(S.pcg_part, S.nb_rows, t, kBlock, a);
+        if (contact)
+            for (int c = t; c < S.team_T; c += kBlock) dq += glob(S.pcg_cpart)[c];
+        dq = block_sum_all(dq);
     }
-    return (R)(q.rz / (a + b));
+    return (R)(glob(S.pcg)->rzv[it & 1] / dq);
+}
+__device__ __forceinline__ void pcg_alpha_load(const SceneDev &S, double (&a)[4])
+{
+    if (!S.team_fit) flat_load<4>(S.pcg_part, S.nb_rows, (int)threadIdx.x, kBlock, a);
 }
 
 // start of the solve for vertex i: r = -g, p = 0, z = D^-1 r; returns r.z
@@ -566,16 +479,16 @@ __device__ __forceinline__ double pcg_vertex_start(const SceneDev &S, int i, R z
 // LDS of an update block: the group's members' r, contact sums and
 // corrections, the aggregate sums, the list of rows for the teams, and the
 // group's level ranges (block-uniform; read in the level loop)
+template <class R>
 struct BShared {
-    double rm[kMasCapM][3];
+    R rm[kMasCapM][3];
     double ra[kMasCapA][3];
-    RowList rl;
-    int32_t lv[kMasLevels][4];  // first aggregate, end, LDS base, offset of the level's aggregates
-    double dq[kBlock / kWave][2];
+    int32_t lv[kMasLevels][2];  // LDS base and number of the level's aggregates
+    int32_t first[kMasLevels];  // and the first one's id in its level
 };
 
 template <class R>
-__device__ void pcg_B_vertices(const Launch &L, const SceneDev &S, int s, int vb, int it, int lb, BShared &sh)
+__device__ void pcg_B_vertices(const Launch &L, const SceneDev &S, int s, int vb, int it, int lb, BShared<R> &sh)
 {
     int k = vb * blockDim.x + threadIdx.x;
     int i = S.mas_levels > 0 ? (k < S.mas_nother ? S.mas_other[k] : -1) : (k < S.n ? k : -1);
@@ -589,65 +502,18 @@ __device__ void pcg_B_vertices(const Launch &L, const SceneDev &S, int s, int vb
         }
     } else {
         const R *dcur = as<R>((it & 1) ? S.dA : S.dB);
-        const auto Y = glob(as<R>(S.act_y));
-        auto yv = [&](int p, int a, int c) { return (double)Y[12 * (int64_t)p + 3 * a + c]; };
-        const bool contact = L.out[s].n_pair > 0;  // the same for the whole scene
-        if (contact) {
-            if (threadIdx.x == 0) sh.rl.count = 0;
-            __syncthreads();
-        }
-        DqIssue dqi;
-        dq_issue(L, S, s, it, dqi);
-        bool own = i >= 0 && !glob(S.hflag)[i];  // a heavy row has a block of its own
+        const int done = glob(S.pcg)->done;
+        const bool own = i >= 0;
+        double dqa[4];
+        pcg_alpha_load(S, dqa);
         VertexPcg<R> v;
-        double qc[3] = {0.0, 0.0, 0.0};
-        bool listed = false;
-        if (own) {
-            pcg_vertex_load<R>(S, i, dcur, v);
-            if (contact) listed = row_sum_or_list(S, i, (int)threadIdx.x, yv, qc, sh.rl);
-        }
-        if (dqi.done) return;
-        dq_stage(L, S, s, dqi, sh.dq);
-        __syncthreads();
-        if (contact) {
-            team_row_sums(S, sh.rl, yv, [&](int d, const double (&q)[3]) {
-                for (int c = 0; c < 3; ++c) sh.rm[d][c] = q[c];
-            });
-            __syncthreads();
-            if (listed)
-                for (int c = 0; c < 3; ++c) qc[c] = sh.rm[threadIdx.x][c];
-        }
-        R alpha = dq_alpha<R>(dqi, sh.dq);
-        if (own) rz = pcg_vertex_update<R>(S, i, alpha, v, qc);
+        if (own) pcg_vertex_load<R>(S, i, dcur, v);
+        if (done) return;
+        const R alpha = pcg_alpha<R>(S, L.out[s].n_crow > 0, it, dqa);
+        if (own) rz = pcg_vertex_update<R>(S, i, alpha, v);
     }
     rz = block_sum_all(rz);
     if (threadIdx.x == 0) glob(rz_slot(S, it))[lb] = rz;
-}
-
-template <class R>
-__device__ void pcg_B_heavy(const Launch &L, const SceneDev &S, int s, int j, int it, BShared &sh)
-{
-    if (j >= L.out[s].n_heavy) return;
-    int row = S.heavy_rows[j];
-    // B(0) and the aggregate members (updated by their group) leave a zero partial
-    if (it == 0 || (S.mas_levels > 0 && S.mas_vpos[row] >= 0)) {
-        if (threadIdx.x == 0) rz_slot(S, it)[S.pcg_nvp + j] = 0.0;
-        return;
-    }
-    const R *dcur = as<R>((it & 1) ? S.dA : S.dB);
-    DqIssue dqi;
-    dq_issue(L, S, s, it, dqi);
-    double qc[3];
-    contact_row_heavy<R>(S, row, qc);
-    if (dqi.done) return;
-    dq_stage(L, S, s, dqi, sh.dq);
-    __syncthreads();
-    R alpha = dq_alpha<R>(dqi, sh.dq);
-    if (threadIdx.x == 0) {
-        VertexPcg<R> v;
-        pcg_vertex_load<R>(S, row, dcur, v);
-        rz_slot(S, it)[S.pcg_nvp + j] = pcg_vertex_update<R>(S, row, alpha, v, qc);
-    }
 }
 
 // a[l] of a per-level register array at a run-time level: selects, so the
@@ -669,7 +535,7 @@ constexpr int kMasSlots = kMasCapM / kBlock;  // members per thread of a group b
 // members' index data is loaded at the start, beside their vertex data; the
 // aggregates' member ranges and inverses where they are used.
 template <class R>
-__device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, int it, BShared &sh)
+__device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, int it, BShared<R> &sh)
 {
     const int nl = S.mas_levels;
     const int tid = (int)threadIdx.x;
@@ -693,10 +559,9 @@ __device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, 
         }
     }
     if (tid < kMasLevels) {  // the level loop reads these from LDS (block-uniform)
-        sh.lv[tid][0] = lvl(ga0, tid);
-        sh.lv[tid][1] = lvl(ga1, tid);
-        sh.lv[tid][2] = lvl(gbase, tid);
-        sh.lv[tid][3] = S.mas_off[tid];
+        sh.lv[tid][0] = lvl(gbase, tid);
+        sh.lv[tid][1] = lvl(ga1, tid) - lvl(ga0, tid);
+        sh.first[tid] = lvl(ga0, tid);
     }
     int vid[kMasSlots], loc[kMasSlots][kMasLevels];
     R zo[kMasSlots][3];
@@ -715,105 +580,57 @@ __device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, 
             if (vid[j] >= 0) {
                 R ri[3];
                 rz += pcg_vertex_start<R>(S, vid[j], zo[j], ri);
-                for (int c = 0; c < 3; ++c) sh.rm[tid + j * kBlock][c] = (double)ri[c];
+                for (int c = 0; c < 3; ++c) sh.rm[tid + j * kBlock][c] = ri[c];
             }
     } else {
-        const bool contact = L.out[s].n_pair > 0;  // the same for the whole scene
-        const auto Y = glob(as<R>(S.act_y));
-        auto yv = [&](int p, int a, int c) { return (double)Y[12 * (int64_t)p + 3 * a + c]; };
-        if (contact) {
-            if (tid == 0) sh.rl.count = 0;
-            __syncthreads();
-        }
-        DqIssue dqi;
-        dq_issue(L, S, s, it, dqi);
+        const int done = glob(S.pcg)->done;
         const R *dcur = as<R>((it & 1) ? S.dA : S.dB);
+        double dqa[4];
+        pcg_alpha_load(S, dqa);
         VertexPcg<R> v[kMasSlots];
-        double qc[kMasSlots][3];
-        bool listed[kMasSlots];
 #pragma unroll
-        for (int j = 0; j < kMasSlots; ++j) {
-            listed[j] = false;
-            qc[j][0] = qc[j][1] = qc[j][2] = 0.0;
-            if (vid[j] >= 0) {
-                pcg_vertex_load<R>(S, vid[j], dcur, v[j]);
-                if (contact) listed[j] = row_sum_or_list(S, vid[j], tid + j * kBlock, yv, qc[j], sh.rl);
-            }
-        }
-        if (dqi.done) return;
-        dq_stage(L, S, s, dqi, sh.dq);
-        __syncthreads();
-        if (contact) {
-            team_row_sums(S, sh.rl, yv, [&](int d, const double (&q)[3]) {
-                for (int c = 0; c < 3; ++c) sh.rm[d][c] = q[c];
-            });
-            __syncthreads();
-        }
-        R alpha = dq_alpha<R>(dqi, sh.dq);
+        for (int j = 0; j < kMasSlots; ++j)
+            if (vid[j] >= 0) pcg_vertex_load<R>(S, vid[j], dcur, v[j]);
+        if (done) return;
+        const R alpha = pcg_alpha<R>(S, L.out[s].n_crow > 0, it, dqa);
         const auto sol = glob(as<R>(S.sol)), r = glob(as<R>(S.r));
 #pragma unroll
         for (int j = 0; j < kMasSlots; ++j) {
             if (vid[j] < 0) continue;
             int i = vid[j], pos = tid + j * kBlock;
-            if (listed[j])
-                for (int c = 0; c < 3; ++c) qc[j][c] = sh.rm[pos][c];
             R ri[3];
             for (int c = 0; c < 3; ++c) {
-                R qv = (R)((double)v[j].q[c] + qc[j][c]);
                 sol[3 * i + c] = v[j].p[c] + alpha * v[j].d[c];
-                ri[c] = v[j].r[c] - alpha * qv;
+                ri[c] = v[j].r[c] - alpha * v[j].q[c];
                 r[3 * i + c] = ri[c];
             }
             for (int a = 0; a < 3; ++a) {
                 zo[j][a] = v[j].M[3 * a] * ri[0] + v[j].M[3 * a + 1] * ri[1] + v[j].M[3 * a + 2] * ri[2];
                 rz += (double)ri[a] * (double)zo[j][a];
             }
-            for (int c = 0; c < 3; ++c) sh.rm[pos][c] = (double)ri[c];
+            for (int c = 0; c < 3; ++c) sh.rm[pos][c] = ri[c];
         }
     }
     __syncthreads();
-    // restriction and coarse solves, a barrier per level: the sums of level l
-    // are formed while the corrections of level l - 1 are (not unrolled: the
-    // unrolled form held every level's state in registers at once)
-#pragma unroll 1
-    for (int l = 0; l <= kMasLevels; ++l) {
-        if (l > nl) break;
-        if (l > 0) {
-            const int pl = l - 1;
-            const int g0 = sh.lv[pl][0], g1 = sh.lv[pl][1], gb = sh.lv[pl][2];
-            for (int a = g0 + tid; a < g1; a += kBlock) {
-                int lc = gb + a - g0;
-                R D[9];
-                const int64_t g = (int64_t)sh.lv[pl][3] + a;
-#pragma unroll
-                for (int c = 0; c < 9; ++c) D[c] = glob(Di)[9 * g + c];
-                R sa[3] = {(R)sh.ra[lc][0], (R)sh.ra[lc][1], (R)sh.ra[lc][2]};
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    R e = D[3 * q] * sa[0] + D[3 * q + 1] * sa[1] + D[3 * q + 2] * sa[2];
-                    sh.rm[lc][q] = (double)e;
-                    rz += sh.ra[lc][q] * (double)e;
-                }
-            }
+    auto range = [&](int l, int a) {
+        const int64_t g = (int64_t)S.mas_off[l] + sh.first[l] + a;
+        const int off = l == 0 ? -k0 : sh.lv[l - 1][0] - sh.first[l - 1];
+        return (uint32_t)(glob(S.mas_mb)[g] + off) | (uint32_t)(glob(S.mas_me)[g] + off) << 16;
+    };
+    mas_restrict(sh.lv[0][0], sh.lv[0][1], sh.rm, sh.ra, tid, kBlock, [&](int, int a) { return range(0, a); });
+    __syncthreads();
+    if (tid < kWave)
+        for (int l = 1; l < nl; ++l) {
+            mas_restrict(sh.lv[l][0], sh.lv[l][1], sh.ra, sh.ra, tid, kWave, [&](int, int a) { return range(l, a); });
+            wave_lds_fence();
         }
-        if (l < nl) {
-            const int g0 = sh.lv[l][0], g1 = sh.lv[l][1], gb = sh.lv[l][2];
-            const int c0 = l > 0 ? sh.lv[l - 1][0] : 0, cb = l > 0 ? sh.lv[l - 1][2] : 0;
-            for (int a = g0 + tid; a < g1; a += kBlock) {
-                const int64_t g = (int64_t)sh.lv[l][3] + a;
-                const int j0 = glob(S.mas_mb)[g], j1 = glob(S.mas_me)[g];
-                double acc[3] = {0.0, 0.0, 0.0};
-                for (int j = j0; j < j1; ++j) {
-                    const double *src = l == 0 ? sh.rm[j - k0] : sh.ra[cb + j - c0];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) acc[c] += src[c];
-                }
-#pragma unroll
-                for (int c = 0; c < 3; ++c) sh.ra[gb + a - g0][c] = acc[c];
-            }
-        }
-        __syncthreads();
-    }
+    __syncthreads();
+    rz += mas_correct<R>(sh.lv[nl - 1][0] + sh.lv[nl - 1][1], sh.rm, sh.ra, tid, [&](int q, int k) {
+        int l = 0;
+        while (l + 1 < nl && q >= sh.lv[l + 1][0]) ++l;
+        return glob(Di)[9 * ((int64_t)S.mas_off[l] + sh.first[l] + q - sh.lv[l][0]) + k];
+    });
+    __syncthreads();
     // prolongation: z = D^-1 r + the corrections of the member's aggregates
     const auto z = glob(as<R>(S.z));
 #pragma unroll
@@ -824,7 +641,7 @@ __device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, 
         for (int l = 0; l < kMasLevels; ++l) {
             if (l >= nl) break;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) zi[c] += sh.rm[loc[j][l]][c];
+            for (int c = 0; c < 3; ++c) zi[c] += (double)sh.rm[loc[j][l]][c];
         }
 #pragma unroll
         for (int c = 0; c < 3; ++c) z[3 * vid[j] + c] = (R)zi[c];
@@ -846,64 +663,37 @@ __global__ void __launch_bounds__(kBlock) k_pcg_B(Launch L, int it, int early)
         L.out[s].pcg_done = 0;
         L.out[s].pcg_iters = 0;
     }
-    __shared__ BShared sh;
+    __shared__ BShared<R> sh;
     const int ngrp = S.mas_levels > 0 ? S.mas_ng : 0;
     if (lb < ngrp)
         pcg_B_group<R>(L, S, s, lb, it, sh);
-    else if (lb < S.pcg_nvp)
-        pcg_B_vertices<R>(L, S, s, lb - ngrp, it, lb, sh);
     else
-        pcg_B_heavy<R>(L, S, s, lb - S.pcg_nvp, it, sh);
+        pcg_B_vertices<R>(L, S, s, lb - ngrp, it, lb, sh);
 }
 
-// y = H v for the test hook (v in S.dB, y in S.q), in the PCG's three parts:
-// pair products, BELL rows, then the incident pair products per row
-template <class R>
-__global__ void __launch_bounds__(kBlock) k_spmv_pairs(Launch L)
-{
-    int lb, s = scene_of_block(L, lb);
-    const SceneDev &S = *L.sc[s];
-    int64_t p = (int64_t)lb * blockDim.x + threadIdx.x;
-    if (p < L.out[s].n_pair) (void)pair_apply<R>(S, p, as<R>(S.dB), nullptr, R(0), false);
-}
-
+// y = H v for the test hook (v in S.dB, y in S.q): a thread per row, both slot
+// streams, then the row's contact blocks
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_spmv_rows(Launch L)
 {
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
-    const R *v = as<R>(S.dB);
+    const R *v = as<R>(S.dB), *cv = as<R>(S.c_val);
     R *y = as<R>(S.q);
-    int row = lb * kRowsPerBlock + (int)threadIdx.x;  // a thread per row, both slot streams
+    int row = lb * kRowsPerBlock + (int)threadIdx.x;
     if (row >= S.n) return;
     double o[3] = {0.0, 0.0, 0.0}, o1[3];
     bell_row_part<R>(S, row, 0, v, nullptr, R(0), false, o);
     bell_row_part<R>(S, row, 1, v, nullptr, R(0), false, o1);
-    for (int c = 0; c < 3; ++c) y[3 * row + c] = (R)(o[c] + o1[c]);
-}
-
-template <class R>
-__global__ void __launch_bounds__(kBlock) k_spmv_contact(Launch L)
-{
-    int lb, s = scene_of_block(L, lb);
-    const SceneDev &S = *L.sc[s];
-    R *y = as<R>(S.q);
-    if (lb < S.nb_vert) {
-        int i = lb * blockDim.x + threadIdx.x;
-        if (i < S.n && !S.hflag[i]) {
-            double qc[3] = {0.0, 0.0, 0.0};
-            contact_row_light<R>(S, i, qc);
-            for (int c = 0; c < 3; ++c) y[3 * i + c] = (R)((double)y[3 * i + c] + qc[c]);
+    for (int c = 0; c < 3; ++c) o[c] += o1[c];
+    if (S.c_ptr[row + 1] > S.c_ptr[row]) {
+        const int64_t base = 3 * (int64_t)S.c_ptr[row];
+        for (int j = 0; j < S.c_n[row]; ++j) {
+            const R *h = cv + 9 * (base + j), *d = v + 3 * (int64_t)S.c_col[base + j];
+            for (int i = 0; i < 3; ++i) o[i] += (double)(h[3 * i] * d[0] + h[3 * i + 1] * d[1] + h[3 * i + 2] * d[2]);
         }
-    } else {
-        int j = lb - S.nb_vert;
-        if (j >= L.out[s].n_heavy) return;
-        int row = S.heavy_rows[j];
-        double qc[3];
-        contact_row_heavy<R>(S, row, qc);
-        if (threadIdx.x == 0)
-            for (int c = 0; c < 3; ++c) y[3 * row + c] = (R)((double)y[3 * row + c] + qc[c]);
     }
+    for (int c = 0; c < 3; ++c) y[3 * row + c] = (R)o[c];
 }
 
 // ---- per-vertex kernels ------------------------------------------------------
@@ -1095,7 +885,6 @@ __device__ __forceinline__ ScanSel scan_sel(const SceneDev &S, const SceneOut &O
     case kScanEdge: return {S.ht_count[1], S.ht_start[1], (int64_t)1 << S.ht_bits[1]};
     case kScanQuery: return {S.q_count, S.q_off, (int64_t)S.n_pts + S.n_edges};
     case kScanContact: return {S.c_cnt, S.c_ptr, (int64_t)S.n};
-    case kScanHeavy: return {S.hflag, S.heavy_idx, (int64_t)S.n};
     case kScanSwFilter: return {S.sw_flag, S.sw_off, S.n_sw_prev};
     default: return {S.act_flag, S.act_off, (int64_t)O.n_cand};
     }
@@ -1165,7 +954,6 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(Launch one, Launch tiles, i
                 O.n_cand = carry;
         }
         if (which == kScanActive) O.n_act = carry;
-        if (which == kScanHeavy) O.n_heavy = carry;
         if (which == kScanSwFilter) O.n_cand = carry;
     }
 }
@@ -1280,32 +1068,95 @@ void launch_mas_diag(Batch &b)
 
 void launch_hess_apply(Batch &b)
 {
-    // pair phase as set by the incidence build of the same assembly
-    if (mixed(b)) {
-        IPC_LAUNCH(b, k_spmv_pairs<float>, kPhActT, kBlock);
+    if (mixed(b))
         IPC_LAUNCH(b, k_spmv_rows<float>, kPhSlice, kRowsPerBlock);
-        IPC_LAUNCH(b, k_spmv_contact<float>, kPhVertH, kBlock);
-    } else {
-        IPC_LAUNCH(b, k_spmv_pairs<double>, kPhActT, kBlock);
+    else
         IPC_LAUNCH(b, k_spmv_rows<double>, kPhSlice, kRowsPerBlock);
-        IPC_LAUNCH(b, k_spmv_contact<double>, kPhVertH, kBlock);
-    }
 }
 
 // PCG for every scene with blocks in the kPhVert map (the active-pair counts
-// come from the last read-back of the narrow phase).
+// come from the last read-back of the narrow phase): the scenes whose team
+// fits in one resident launch, the others (and a team that did not form)
+// iteration by iteration.
+static void run_pcg_launched(Batch &b, const std::vector<uint8_t> &on, std::vector<int> &iters, std::vector<int> &hit_cap);
+
+// algorithmic bytes of one scene in one A launch: every stored 3x3 block
+// (values and column) once, the merged contact blocks among them; per vertex
+// the z and d gathers, the d and q writes and its row pointer
+static double pcg_bytes_a(const Scene &s, const SceneOut &o)
+{
+    const double rs = s.prm.precision == IPC_MIXED ? 4.0 : 8.0;
+    return (9 * rs + 4) * ((double)s.nnzb + (double)o.n_cblk) + (12 * rs + 4) * (double)s.h.n;
+}
+// and of one B launch: per vertex q, d, p, r and the 3x3 inverse read and
+// p, r, z written (30 reals); per preconditioner member its vertex id and
+// three level ids; the SpMV blocks' d.q partials
+static double pcg_bytes_b(const Scene &s, const SceneOut &o)
+{
+    const double rs = s.prm.precision == IPC_MIXED ? 4.0 : 8.0;
+    return 30 * rs * (double)s.h.n + 16.0 * (s.h.mas_levels > 0 ? (double)s.h.mas_nf : 0.0) + 8.0 * (double)s.h.nb_rows;
+}
+
 void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
+{
+    const size_t ns = b.sc.size();
+    std::vector<uint8_t> team(ns, 0), rest(ns, 0);
+    bool any_team = false, any_rest = false;
+    for (size_t i = 0; i < ns; ++i) {
+        if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
+        const SceneDev &h = b.sc[i]->h;
+        const int64_t crows = std::min<int64_t>(4 * pair_count(*b.sc[i], b.h_out[i]) / std::max(h.team_T, 1) + 1, h.n);
+        const bool t = h.team_fit && b.sc[i]->tune.team && crows <= kChunkRows;
+        (t ? team : rest)[i] = 1;
+        (t ? any_team : any_rest) = true;
+    }
+    iters.assign(ns, 0);
+    hit_cap.assign(ns, 0);
+    if (any_team) {
+        hipEvent_t ev[2];
+        if (b.prof()) b.prof_begin(kProfPcgA, ev);
+        launch_pcg_team(b, team);
+        const size_t timed = b.ev_pending.size();
+        if (b.prof()) b.prof_end(kProfPcgA, ev);
+        b.read_out();
+        double bytes = 0.0, peak = 0.0;
+        for (size_t i = 0; i < ns; ++i) {
+            if (!team[i]) continue;
+            const SceneOut &o = b.h_out[i];
+            if (!o.pcg_done || o.pcg_fail) {
+                rest[i] = 1;
+                any_rest = true;
+                continue;
+            }
+            iters[i] = o.pcg_iters;
+            hit_cap[i] = o.pcg_done != 1;
+            b.sc[i]->last_pcg_iters = o.pcg_iters;
+            if (b.prof()) {
+                bytes += (pcg_bytes_a(*b.sc[i], o) + pcg_bytes_b(*b.sc[i], o)) * o.pcg_iters;
+                peak += pcg_bytes_a(*b.sc[i], o);
+            }
+        }
+        if (b.prof()) {
+            b.ev_pending[timed].bytes = bytes;
+            b.ev_pending[timed].big = peak >= kProfBigBytes;
+            b.prof_totals(kProfPcgA, 1, bytes);
+            b.prof_collect();
+        }
+    }
+    if (any_rest) run_pcg_launched(b, rest, iters, hit_cap);
+}
+
+static void run_pcg_launched(Batch &b, const std::vector<uint8_t> &on, std::vector<int> &iters, std::vector<int> &hit_cap)
 {
     size_t ns = b.sc.size();
     bool mx = mixed(b);
-    std::vector<int32_t> nab(ns, 0);
-    for (size_t i = 0; i < ns; ++i)
-        if (b.h_off[kPhVert][i + 1] > b.h_off[kPhVert][i]) nab[i] = b.sc[i]->h.nb_rows + nblocks(pair_count(*b.sc[i], b.h_out[i]), kPairsPerBlock);
+    std::vector<int32_t> nab(ns, 0), nbb(ns, 0);
+    for (size_t i = 0; i < ns; ++i) {
+        if (!on[i]) continue;
+        nab[i] = b.sc[i]->h.nb_rows + (pair_count(*b.sc[i], b.h_out[i]) > 0 ? b.sc[i]->h.team_T : 0);
+        nbb[i] = b.sc[i]->h.pcg_nvp;
+    }
     b.set_phase(kPhPcgA, nab);
-    set_heavy_phase(b);
-    std::vector<int32_t> nbb(ns, 0);
-    for (size_t i = 0; i < ns; ++i)
-        if (nab[i] > 0) nbb[i] = b.sc[i]->h.pcg_nvp + heavy_bound(pair_count(*b.sc[i], b.h_out[i]), b.sc[i]->h.n);
     b.set_phase(kPhPcgB, nbb);
     if (mx)
         IPC_LAUNCH(b, k_pcg_B<float>, kPhPcgB, kBlock, 0, 0);
@@ -1313,31 +1164,16 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         IPC_LAUNCH(b, k_pcg_B<double>, kPhPcgB, kBlock, 0, 0);
     int maxit = 0, last = 0;
     for (size_t i = 0; i < ns; ++i) {
-        if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
+        if (!on[i]) continue;
         const Scene &s = *b.sc[i];
         maxit = std::max(maxit, s.h.pcg_maxit);
         last = std::max(last, s.last_pcg_iters);
     }
-    iters.assign(ns, 0);
-    hit_cap.assign(ns, 0);
-    // algorithmic bytes of one scene in one A launch: every stored 3x3 block
-    // (values and column) once; per vertex the z and d gathers, the d and q
-    // writes and its row pointer; per pair its off-diagonal blocks and ids
-    // and of one B launch: per vertex q, d, p, r and the 3x3 inverse read and
-    // p, r, z written (30 reals); per incidence entry (4 per pair) its index
-    // and 3 pair-product values; per preconditioner member its vertex id and
-    // three level ids; the SpMV blocks' d.q partials
     std::vector<double> scene_bytes(ns, 0.0), scene_bytes_b(ns, 0.0);
-    {
-        const double rs = mx ? 4.0 : 8.0;
-        for (size_t i = 0; i < ns; ++i) {
-            if (nab[i] == 0) continue;
-            const Scene &s = *b.sc[i];
-            const double np_ = (double)pair_count(s, b.h_out[i]);
-            scene_bytes[i] = (9 * rs + 4) * (double)s.nnzb + (12 * rs + 4) * (double)s.h.n + (108 * rs + 16) * np_;
-            scene_bytes_b[i] = 30 * rs * (double)s.h.n + 4 * (4 + 3 * rs) * np_ +
-                               16.0 * (s.h.mas_levels > 0 ? (double)s.h.mas_nf : 0.0) + 8.0 * (double)s.h.nb_rows;
-        }
+    for (size_t i = 0; i < ns; ++i) {
+        if (!on[i]) continue;
+        scene_bytes[i] = pcg_bytes_a(*b.sc[i], b.h_out[i]);
+        scene_bytes_b[i] = pcg_bytes_b(*b.sc[i], b.h_out[i]);
     }
     // Timed A launches of a chunk get their bytes once the chunk's flags are
     // back: a scene counts in the launch of iteration it when its solve was
@@ -1347,7 +1183,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
     auto launch_bytes = [&](const std::vector<double> &sb, int it_) {
         double v = 0.0;
         for (size_t i = 0; i < ns; ++i) {
-            if (sb[i] == 0.0) continue;
+            if (!on[i] || sb[i] == 0.0) continue;
             if (!b.h_out[i].pcg_done || it_ <= b.h_out[i].pcg_iters) v += sb[i];
         }
         return v;
@@ -1400,7 +1236,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         double ba = 0.0, bb = 0.0;
         for (int j = it0; j < it1; ++j)
             for (size_t i = 0; i < ns; ++i) {
-                if (nab[i] == 0) continue;
+                if (!on[i] || nab[i] == 0) continue;
                 if (!b.h_out[i].pcg_done || j <= b.h_out[i].pcg_iters) {
                     ba += scene_bytes[i];
                     bb += scene_bytes_b[i];
@@ -1449,7 +1285,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         b.prof_collect();
         bool all = true;
         for (size_t i = 0; i < ns; ++i)
-            if (b.h_off[kPhVert][i + 1] > b.h_off[kPhVert][i] && !b.h_out[i].pcg_done) all = false;
+            if (on[i] && !b.h_out[i].pcg_done) all = false;
         if (all) break;
         chunk = next_chunk(tn.pcg_later_chunk);
         early = 1;
@@ -1466,7 +1302,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         }
     }
     for (size_t i = 0; i < ns; ++i) {
-        if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
+        if (!on[i]) continue;
         iters[i] = b.h_out[i].pcg_done ? b.h_out[i].pcg_iters : b.sc[i]->h.pcg_maxit;
         hit_cap[i] = b.h_out[i].pcg_done != 1;
         b.sc[i]->last_pcg_iters = iters[i];

@@ -114,6 +114,8 @@ std::vector<TuneClass> parse_tuning(const std::string &text)
             else if (key == "pcg_first_chunk") c.t.pcg_first_chunk = std::max(0.0, std::min(4.0, v));
             else if (key == "pcg_later_chunk") c.t.pcg_later_chunk = std::max(0.0, std::min(4.0, v));
             else if (key == "pcg_list_quantile") c.t.pcg_list_quantile = std::max(0.0, std::min(1.0, v));
+            else if (key == "team") c.t.team = v != 0.0;
+            else if (key == "team_spin") c.t.team_spin = std::max(0, std::min(1 << 24, (int)v));
             q = (size_t)(end - body.c_str());
         }
         c.t.from_file = 1;
@@ -403,21 +405,22 @@ void grow_active(Scene &s, int64_t need)
     Staged st(s);
     int32_t *ni = st.get<int32_t>(nc), *nv = st.get<int32_t>(4 * (size_t)nc);
     void *ng = st.get_bytes(12 * (size_t)nc * rs), *nh = st.get_bytes(144 * (size_t)nc * rs);
-    void *ny = st.get_bytes(12 * (size_t)nc * rs);
-    double *npp = st.get<double>((size_t)nblocks(nc, kPairsPerBlock) + 1);
+    void *ncv = st.get_bytes(9 * 12 * (size_t)nc * rs);
     int32_t *nl = st.get<int32_t>(4 * (size_t)nc), *nr = st.get<int32_t>(4 * (size_t)nc);
-    int32_t *nt = st.get<int32_t>(4 * (size_t)nc);
+    int32_t *nt = st.get<int32_t>(4 * (size_t)nc), *ncr = st.get<int32_t>(4 * (size_t)nc);
+    int32_t *ncc = st.get<int32_t>(12 * (size_t)nc);
     st.commit();
-    for (void *old : {(void *)H.act_idx, (void *)H.act_v, H.act_g, H.act_H, H.act_y, (void *)H.pcg_pair,
-                      (void *)H.c_list, (void *)H.c_row, (void *)H.c_tmp})
+    for (void *old : {(void *)H.act_idx, (void *)H.act_v, H.act_g, H.act_H, (void *)H.c_list, (void *)H.c_row,
+                      (void *)H.c_tmp, (void *)H.c_rows, (void *)H.c_col, H.c_val})
         dfree(s, old);
     H.c_tmp = nt;
+    H.c_rows = ncr;
+    H.c_col = ncc;
+    H.c_val = ncv;
     H.act_idx = ni;
     H.act_v = nv;
     H.act_g = ng;
     H.act_H = nh;
-    H.act_y = ny;
-    H.pcg_pair = npp;
     H.c_list = nl;
     H.c_row = nr;
     H.act_cap = nc;
@@ -622,6 +625,71 @@ static void build_multilevel(SceneDev &H, int mas_target, const ipc_scene_desc &
             }
             M.dptr.push_back((int32_t)M.dsrc.size());
         }
+}
+
+// Chunks of the PCG solve and, where the scene's team fits (one workgroup per
+// CU, its columns and preconditioner data in LDS), the chunks' column lists
+// for the resident form. Wide workgroups where a narrow team would pass
+// kTeamWide members (the exchange grows with the team: 2.2 us a sum at 64
+// members, 2.5 at 128, 3.1 at 256).
+constexpr int kTeamWide = 128;
+
+static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const std::vector<int32_t> &bcol)
+{
+    SceneDev &H = s.h;
+    const size_t rs = real_size(s);
+    auto chunks = [&](int nt) {
+        return std::max(nblocks(H.nb_rows, nt / (2 * kRowsPerBlock)), nblocks(H.pcg_nvp, nt / kBlock));
+    };
+    const int narrow = team_narrow(rs);
+    H.team_nt = chunks(narrow) > (rs == sizeof(float) ? kTeamWide : kTeamMax) || chunks(2 * narrow) == 1 ? 2 * narrow : narrow;
+    H.team_T = chunks(H.team_nt);
+    H.team_A = std::max(s.mas_max_aggs, 1);
+    H.team_spin = s.tune.team_spin;
+    H.team_fit = 0;
+    int device = 0, cus = 0;
+    IPC_HIP(hipGetDevice(&device));
+    IPC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    if (H.team_T > std::min(kTeamMax, cus)) return;
+    if ((uint64_t)H.n_slots * kSlice * 9 * rs >= 0xffffffffu) return;  // the matrix is reached by 32-bit byte offsets
+    const int rows = H.team_nt / 2, n = H.n;
+    std::vector<int32_t> hptr(H.team_T + 1, 0), hlist, at(n, -1);
+    std::vector<uint16_t> lcol((size_t)H.n_slots * kSlice, 0);
+    for (int w = 0; w < H.team_T; ++w) {
+        const size_t first = hlist.size();
+        const int r0 = std::min(w * rows, n), r1 = std::min(r0 + rows, n);
+        const int sl1 = (r1 + kSlice - 1) / kSlice;
+        for (int sl = r0 / kSlice; r0 < r1 && sl < sl1; ++sl)  // chunks hold whole slices
+            for (size_t e = (size_t)slice_ptr[sl] * kSlice; e < (size_t)slice_ptr[sl + 1] * kSlice; ++e)
+                if (bcol[e] >= 0 && at[bcol[e]] != w) {
+                    at[bcol[e]] = w;
+                    hlist.push_back(bcol[e]);
+                }
+        std::sort(hlist.begin() + first, hlist.end());
+        hptr[w + 1] = (int32_t)hlist.size();
+        H.team_H = std::max(H.team_H, (int)(hlist.size() - first));
+    }
+    if (H.team_H > 0xffff || team_lds_bytes(H.team_nt, H.team_H, H.team_A, rs) > kTeamLds - 1024) return;
+    std::vector<int32_t> pos(n, 0);
+    for (int w = 0; w < H.team_T; ++w) {
+        for (int k = hptr[w]; k < hptr[w + 1]; ++k) pos[hlist[k]] = k - hptr[w];
+        const int r0 = std::min(w * rows, n), r1 = std::min(r0 + rows, n);
+        for (int sl = r0 / kSlice; r0 < r1 && sl < (r1 + kSlice - 1) / kSlice; ++sl)
+            for (size_t e = (size_t)slice_ptr[sl] * kSlice; e < (size_t)slice_ptr[sl + 1] * kSlice; ++e) {
+                // padding entries hold zeros: they read their row's own column
+                const int row = std::min(sl * kSlice + (int)(e % kSlice), n - 1);
+                lcol[e] = (uint16_t)pos[bcol[e] >= 0 ? bcol[e] : row];
+            }
+    }
+    H.team_hptr = upload(s, hptr);
+    H.team_hlist = upload(s, hlist);
+    H.team_lcol = upload(s, lcol);
+    H.team_z = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.team_q = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.team_ll = dalloc<unsigned long long>(s, 4 * (size_t)H.team_T);
+    IPC_HIP(hipStreamSynchronize(s.stream));  // host vectors above are locals
+    team_prepare_device();
+    H.team_fit = 1;
 }
 
 static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
@@ -906,12 +974,13 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
     for (void **p : {&H.r, &H.z, &H.dA, &H.dB, &H.q, &H.sol}) *p = dalloc_bytes(s, n3 * rs);
     IPC_HIP(hipMemsetAsync(H.sol, 0, n3 * rs, s.stream));
     H.pcg_nvp = H.mas_levels > 0 ? H.mas_ng + nblocks(H.mas_nother) : H.nb_vert;
-    H.pcg_part = dalloc<double>(s, (size_t)H.nb_rows + 2 * ((size_t)H.pcg_nvp + n + 1) + 8);
-    H.hflag = dalloc<int32_t>(s, n + 1);
-    H.heavy_idx = dalloc<int32_t>(s, n + 1);
-    H.heavy_rows = dalloc<int32_t>(s, n + 1);
-    H.hdiag = dalloc<double>(s, 9 * ((size_t)n + 1));
-    IPC_HIP(hipMemsetAsync(H.hflag, 0, sizeof(int32_t) * (n + 1), s.stream));
+    H.pcg_part = dalloc<double>(s, (size_t)H.nb_rows + 2 * (size_t)H.pcg_nvp + 8);
+    build_team(s, slice_ptr, bcol);
+    H.pcg_cpart = dalloc<double>(s, H.team_T);
+    H.c_n = dalloc<int32_t>(s, n);
+    H.c_q = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.c_grad = dalloc<double>(s, 3 * (size_t)n);
+    H.c_diag = dalloc<double>(s, 9 * (size_t)n);
     if (H.mas_levels > 0) {
         int total = H.mas_off[H.mas_levels];
         H.mas_mem = upload(s, mas.mem);
@@ -2053,11 +2122,11 @@ int64_t ipc_scene_footprint_bytes(const ipc_scene_desc *d)
     if (!check_desc(d)) return -1;
     int64_t n = (int64_t)d->n_verts + d->n_ind_verts, m = d->n_tets;
     int64_t rs = d->precision == IPC_MIXED ? 4 : 8;
-    int64_t per_vertex = 8 * (3 * 9 + 1) + rs * (3 * 8 + 9) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers) and one scalar; the PCG vectors in R
+    int64_t per_vertex = 8 * (3 * 9 + 1 + 12) + rs * (3 * 8 + 9) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers) and one scalar; the PCG vectors in R
     int64_t per_tet = 4 * 4 + 8 * 10 + rs * (12 + 90) + 4 * 16 + 4 * 4;
     int64_t bell = n * 16 * (9 * rs + 4 + 4);
     int64_t surf = 4 * (int64_t)std::pow((double)d->n_verts, 2.0 / 3.0) + d->n_ind_verts + 2 * d->n_ind_tris;
-    int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * 156 + 4 * 9);
+    int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * (156 + 108) + 4 * 33);
     return n * per_vertex + m * per_tet + bell + contact + (8 << 20);
 }
 
@@ -2672,7 +2741,7 @@ int32_t ipcx_assemble_elastic(ipc_scene *s, const double *x, double *g, const do
         s->dev_dirty = true;
         b.upload_views();
         SceneOut &o = b.h_out[0];
-        o.n_cand = o.n_act = o.n_pair = o.n_heavy = 0;
+        o.n_cand = o.n_act = o.n_pair = o.n_crow = o.n_cblk = 0;
         IPC_HIP(hipMemcpyAsync(b.d_out, &o, sizeof(SceneOut), hipMemcpyHostToDevice, b.stream));
         launch_contact_incidence(b);
         launch_elastic_elements(b);
@@ -2719,7 +2788,7 @@ int32_t ipcx_barrier(ipc_scene *s, const double *x, int64_t cap, int32_t *kind, 
                 if (g12)
                     for (int e = 0; e < 12; ++e) g12[12 * k + e] = gg[(size_t)e * pc + k];
                 if (H144)
-                    for (int e = 0; e < 144; ++e) H144[144 * k + e] = hh[(size_t)e * pc + k];
+                    for (int e = 0; e < 144; ++e) H144[144 * k + e] = hh[144 * (size_t)k + e];
             }
         }
         return IPC_OK;
