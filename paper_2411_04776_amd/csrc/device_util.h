@@ -41,7 +41,7 @@ __device__ __forceinline__ void lane_pair(uint32_t x, uint32_t &a, uint32_t &b)
         b = r[1];
     } else {
         a = x;
-        b = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + O, 0xf, 0xf, false);
+        b = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x120 + O, 0xf, 0xf, true);
     }
 }
 template <int O>
@@ -55,13 +55,14 @@ __device__ __forceinline__ double lane_add(double v)
            __longlong_as_double((long long)((uint64_t)b1 << 32 | b0));
 }
 
-// the value of another lane of the quad (CTRL 0xb1: lane ^ 1, 0x4e: lane ^ 2)
+// the value of another lane of the quad (CTRL 0xb1: lane ^ 1, 0x4e: lane ^ 2) or
+// row of 16 lanes (0x141: 7 - lane of each eight, 0x140: 15 - lane)
 template <int CTRL>
 __device__ __forceinline__ double quad_other(double v)
 {
     const uint64_t x = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, false);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)x, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 

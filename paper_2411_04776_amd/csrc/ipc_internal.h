@@ -61,7 +61,7 @@ constexpr int kMasTarget = 256;   // groups are packed with top-level aggregates
 constexpr int kTeamMax = 256;     // workgroups of a resident PCG team (one per CU)
 constexpr int kTeamSlots = 8;     // matrix slots of a row half kept in registers (two threads per row)
 constexpr int kTeamHalo = 4;      // column ids a thread keeps in registers
-constexpr int kTeamLds = 160 * 1024;  // LDS of a CU
+constexpr int kTeamDyn = 158 * 1024;  // dynamic LDS of a team's workgroup (160 KB a CU, less its static arrays)
 constexpr int kChunkRows = 512;    // contact rows a resident team's member takes (more: the launched form)
 
 // kernels timed by the optional profiler
@@ -200,16 +200,18 @@ struct SceneDev {
     int32_t *mas_other;              // their ids, ascending
     int32_t *mas_vpos;               // member position of each vertex, -1 outside
     int pcg_nvp;                     // PCG update blocks (and their r.z partials)
-    // PCG sums and the resident team (k_pcg_team.hip): a chunk is team_nt / 2
-    // matrix rows, team_nt / 256 update units; both forms of the solver add each chunk's partials first, then the chunks
+    // PCG sums and the resident team (k_pcg_team.hip): both forms of the solver
+    // add each chunk's partials first, then the chunks
     int team_T;                      // chunks (the team's workgroups)
-    int team_nt;                     // threads of a workgroup
+    int team_rows, team_units;       // matrix rows and update units of a chunk
+    int team_variant;                // layout of the resident form
     int team_fit;                    // 1: the solve can run in one resident launch
     int team_H, team_A;              // largest column list of a chunk, aggregates of a group (LDS sizes)
     int team_spin;                   // polls a member waits for its team to form
     int32_t *team_hptr, *team_hlist; // columns of each chunk's rows (ascending vertex ids)
     uint16_t *team_lcol;             // BELL column as an index into its chunk's list
-    void *team_z, *team_q;           // z and q of the resident form, 4 values per vertex
+    void *team_z, *team_q;           // z and q of the resident form, 4 values' space per vertex
+    void *team_dA, *team_dB;         // and the contact rows' directions, of odd and even iterations
     unsigned long long *team_ll;     // tagged partials: d.q of every chunk, then r.z (two words each)
     // PCG
     void *r, *z, *dA, *dB, *q, *sol;
@@ -529,8 +531,11 @@ void launch_energy_body(Batch &b, bool trial);
 void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap);
 // resident solves of the scenes with on[i] (host)
 void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on);
-int team_narrow(size_t real);  // threads of a team's narrow workgroups (wide: twice that)
-size_t team_lds_bytes(int nt, int H, int A, size_t real);
+// layouts of a team's workgroups: 0 narrow, 1 wide (twice the rows and units),
+// 2 and 3 teams of one (twice the units, twice both)
+int team_rows(int variant, size_t real);
+int team_units(int variant, size_t real);
+size_t team_lds_bytes(int variant, int H, int A, size_t real);
 void team_prepare_device();  // dynamic-LDS limit of the team kernels on the current device
 void run_pinf(Batch &b);
 void launch_hess_apply(Batch &b);  // y (S.q) = H v (S.dB)

@@ -233,9 +233,27 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
     if (lb >= S.nb_rows) {  // the chunk's contact rows
         constexpr int NT = kRowsPerBlock * LPR;
         const int c = lb - S.nb_rows;
-        auto dir = [&](int v, R (&d)[3]) {
-            for (int k = 0; k < 3; ++k) d[k] = bon ? z[3 * v + k] + rb * dold[3 * v + k] : z[3 * v + k];
-        };
+        struct Dir {  // d = z + beta d_prev
+            const R *z, *dold;
+            R rb;
+            bool bon;
+            struct Raw {
+                R z[3], d[3];
+            };
+            __device__ __forceinline__ Raw start(int v) const
+            {
+                Raw x;
+                for (int k = 0; k < 3; ++k) {
+                    x.z[k] = glob(z)[3 * (int64_t)v + k];
+                    x.d[k] = bon ? glob(dold)[3 * (int64_t)v + k] : R(0);
+                }
+                return x;
+            }
+            __device__ __forceinline__ void end(int, const Raw &x, R (&d)[3]) const
+            {
+                for (int k = 0; k < 3; ++k) d[k] = bon ? x.z[k] + rb * x.d[k] : x.z[k];
+            }
+        } dir{z, dold, rb, bon};
         auto put = [&](int v, const R (&y)[3]) {
             for (int k = 0; k < 3; ++k) as<R>(S.c_q)[4 * (int64_t)v + k] = y[k];
         };
@@ -243,7 +261,7 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
         for (int skip = 0;; skip += kPassRows) {
             const int n = chunk_contact_rows<NT, kPassRows>(S, c, skip, clist, ccnt), m = min(n, kPassRows);
             const auto cc = glob((const int32_t *)S.c_col);
-            contact_rows<NT, R>(glob((const R *)as<R>(S.c_val)), cc, clist, m, t, contact_first(cc, clist, m, t), dir, put,
+            contact_rows<NT, R>(glob((const R *)as<R>(S.c_val)), cc, clist, 0, m, t, dir, put,
                                 cdot);
             __syncthreads();
             contact_dots(cdot, m, t_dq);
@@ -612,22 +630,21 @@ __device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, 
         }
     }
     __syncthreads();
-    auto range = [&](int l, int a) {
+    const int na0 = sh.lv[0][1], na1 = nl > 1 ? sh.lv[1][1] : 0, na2 = nl > 2 ? sh.lv[2][1] : 0;
+    auto range = [&](int l, int a, bool) {
+        const auto mb = glob(S.mas_mb), me = glob(S.mas_me);
         const int64_t g = (int64_t)S.mas_off[l] + sh.first[l] + a;
-        const int off = l == 0 ? -k0 : sh.lv[l - 1][0] - sh.first[l - 1];
-        return (uint32_t)(glob(S.mas_mb)[g] + off) | (uint32_t)(glob(S.mas_me)[g] + off) << 16;
-    };
-    mas_restrict(sh.lv[0][0], sh.lv[0][1], sh.rm, sh.ra, tid, kBlock, [&](int, int a) { return range(0, a); });
-    __syncthreads();
-    if (tid < kWave)
-        for (int l = 1; l < nl; ++l) {
-            mas_restrict(sh.lv[l][0], sh.lv[l][1], sh.ra, sh.ra, tid, kWave, [&](int, int a) { return range(l, a); });
-            wave_lds_fence();
+        int b = mb[g], e = me[g], off = l == 0 ? k0 : sh.first[0];
+        if (l == 2) {  // children of level 1: the first one's first child and the last one's end
+            b = mb[S.mas_off[1] + b];
+            e = me[S.mas_off[1] + e - 1];
         }
+        return (uint32_t)(b - off) | (uint32_t)(e - off) << 16;
+    };
+    mas_restrict<R>(na0, sh.rm, sh.ra, tid, range);
     __syncthreads();
-    rz += mas_correct<R>(sh.lv[nl - 1][0] + sh.lv[nl - 1][1], sh.rm, sh.ra, tid, [&](int q, int k) {
-        int l = 0;
-        while (l + 1 < nl && q >= sh.lv[l + 1][0]) ++l;
+    rz += mas_coarse<R>(nl, na0, na1, na2, sh.rm, sh.ra, tid, range, [&](int q, int k) {
+        const int l = q >= na0 + na1 ? 2 : (q >= na0 ? 1 : 0);
         return glob(Di)[9 * ((int64_t)S.mas_off[l] + sh.first[l] + q - sh.lv[l][0]) + k];
     });
     __syncthreads();

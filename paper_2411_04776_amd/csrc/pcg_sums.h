@@ -2,8 +2,8 @@
 // shared by the resident form (k_pcg_team.hip) and the launched form
 // (k_solver.hip), so a solve gives the same bits in either.
 //
-// A scene is cut into team_T chunks: chunk c holds team_nt / 2 consecutive
-// matrix rows, team_nt / 256 consecutive update units, and the contact rows
+// A scene is cut into team_T chunks: chunk c holds team_rows consecutive
+// matrix rows, team_units consecutive update units, and the contact rows
 // whose first incidence entry lies in its 1/T of the entries (contact rows
 // cluster in a few slices of the matrix; by entries they spread evenly). A
 // chunk's partials are added in order, then one wavefront adds the chunks (lane l takes l, l + 64, ...) and its fixed tree
@@ -42,7 +42,7 @@ __device__ __forceinline__ double half_wave_sum(double v)
 
 __device__ __forceinline__ double chunk_rz(const SceneDev &S, const double *slot, int c)
 {
-    const int U = S.team_nt / kBlock;
+    const int U = S.team_units;
     double t = 0.0;
     for (int u = c * U; u < min((c + 1) * U, S.pcg_nvp); ++u) t += glob(slot)[u];
     return t;
@@ -50,7 +50,7 @@ __device__ __forceinline__ double chunk_rz(const SceneDev &S, const double *slot
 
 __device__ __forceinline__ double chunk_dq(const SceneDev &S, bool contact, int c)
 {
-    const int RB = S.team_nt / (2 * kRowsPerBlock);
+    const int RB = S.team_rows / kRowsPerBlock;
     double a = 0.0;
     for (int k = c * RB; k < min((c + 1) * RB, S.nb_rows); ++k) a += glob(S.pcg_part)[k];
     return contact ? a + glob(S.pcg_cpart)[c] : a;
@@ -88,54 +88,76 @@ __device__ __forceinline__ int chunk_contact_rows(const SceneDev &S, int c, int 
 }
 
 // Contact part of q for the listed rows, sum over a row's blocks j of
-// C_j d(col_j), by a block of NT threads: a team of W lanes a row (kRowTeam,
-// or a wavefront for rows of more than kRowLong blocks: a coarse indenter's
-// vertex has hundreds), lane u adding blocks u, u + W, ... in order, then an
-// xor tree. cv, cc: the blocks' values and columns; dir(v, d): the direction
-// at a vertex; put(row, sums) on one lane of each row, the row's d . sums in
-// dot[]. A lane's next column is read ahead of the current one's direction;
-// col0: the first one of the first row it shares (contact_first), which a
-// solve that keeps its rows reads once.
-__device__ __forceinline__ int contact_first(gptr<const int32_t> cc, const CRow *list, int n, int tid)
+// C_j d(col_j): kRowTeam blocks at a time (an item) summed by the xor tree of
+// kRowTeam lanes, then the row's items in order.
+//
+// contact_rows: rows h0, h0 + 1, ... by a block of NT threads, a team of
+// kRowTeam lanes each, or a wavefront (four items at a time) for rows of more
+// than kRowLong blocks: a coarse indenter's vertex has hundreds. cv, cc: the
+// blocks' values and columns; dir.start(v) reads what dir.end(v, raw, d) turns into the direction
+// at a vertex; put(row,
+// sums) on one lane of each row, the row's d . sums in dot[].
+template <class R>
+__device__ __forceinline__ void contact_item(bool has, const R (&A)[9], const R (&d)[3], double (&t)[3])
 {
-    const int h = tid / kRowTeam, u = tid % kRowTeam;
-    return h < n && u < list[h].n ? cc[list[h].base + u] : 0;
+    R y0 = R(0), y1 = R(0), y2 = R(0);
+    block_fma(A, d[0], d[1], d[2], y0, y1, y2);
+    t[0] = has ? (double)y0 : 0.0;
+    t[1] = has ? (double)y1 : 0.0;
+    t[2] = has ? (double)y2 : 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) t[c] = lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(t[c]))));
+}
+template <class R>
+__device__ __forceinline__ double contact_dot(const R (&own)[3], const R (&q)[3])
+{
+    return (double)own[0] * (double)q[0] + (double)own[1] * (double)q[1] + (double)own[2] * (double)q[2];
 }
 template <int NT, class R, class D, class P>
-__device__ __forceinline__ void contact_rows(gptr<const R> cv, gptr<const int32_t> cc, const CRow *list, int n, int tid,
-                                             int col0, D dir, P put, double *dot)
+__device__ __forceinline__ void contact_rows(gptr<const R> cv, gptr<const int32_t> cc, const CRow *list, int h0, int n,
+                                             int tid, D &dir, P put, double *dot)
 {
+    static_assert(kRowTeam == 16, "the items' tree");
     auto pass = [&](auto team, bool longer) {  // a team of lanes per row
         constexpr int W = decltype(team)::value;
         const int u = tid % W;
-        for (int h = tid / W; h < n; h += NT / W) {
+        for (int h = h0 + tid / W; h < n; h += NT / W) {
             const CRow cr = list[h];
             if ((cr.n > kRowLong) != longer) continue;
-            int col = !longer && h == tid / W ? col0 : (u < cr.n ? cc[cr.base + u] : 0);
+            int col = u < cr.n ? cc[cr.base + u] : cr.row;
+            auto ro = dir.start(cr.row);
             R own[3];
-            dir(cr.row, own);
             double acc[3] = {0.0, 0.0, 0.0};
-            for (int j = u; j < cr.n; j += W) {
-                const auto from = cv + 9 * ((int64_t)cr.base + j);
-                R A[9], d[3], y0 = R(0), y1 = R(0), y2 = R(0);
+            for (int j = u; j - u < cr.n; j += W) {
+                const bool has = j < cr.n;
+                const auto at = cv + 9 * ((int64_t)cr.base + (has ? j : 0));
+                R A[9], d[3];
+                double t[3];
 #pragma unroll
-                for (int e = 0; e < 9; ++e) A[e] = from[e];
-                dir(col, d);
+                for (int e = 0; e < 9; ++e) A[e] = at[e];
+                auto rc = dir.start(col);
+                const int c0 = col;
                 if (j + W < cr.n) col = cc[cr.base + j + W];
-                block_fma(A, d[0], d[1], d[2], y0, y1, y2);
-                acc[0] += (double)y0;
-                acc[1] += (double)y1;
-                acc[2] += (double)y2;
-            }
+                dir.end(c0, rc, d);
+                contact_item<R>(has, A, d, t);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if constexpr (W == kWave) acc[c] = lane_add<16>(lane_add<32>(acc[c]));
-                acc[c] = lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(acc[c]))));
+                for (int c = 0; c < 3; ++c) {
+                    if constexpr (W == kWave) {  // the items that exist, in order
+#pragma unroll
+                        for (int i = 0; i < W / kRowTeam; ++i) {
+                            const double v = __shfl(t[c], kRowTeam * i, kWave);
+                            acc[c] = j - u + kRowTeam * i < cr.n ? acc[c] + v : acc[c];
+                        }
+                    } else {
+                        acc[c] += t[c];
+                    }
+                }
             }
             if (u == 0) {
                 const R q[3] = {(R)acc[0], (R)acc[1], (R)acc[2]};
+                dir.end(cr.row, ro, own);
                 put(cr.row, q);
-                dot[h] = (double)own[0] * (double)q[0] + (double)own[1] * (double)q[1] + (double)own[2] * (double)q[2];
+                dot[h] = contact_dot(own, q);
             }
         }
     };
@@ -149,57 +171,111 @@ __device__ __forceinline__ void contact_dots(const double *dot, int n, double &t
     for (int h = (int)(threadIdx.x & (kWave - 1)); h < n; h += kWave) t += dot[h];
 }
 
-// Coarse part of the multilevel preconditioner for one group, by the kBlock
-// threads of its unit (t: thread of the unit). Between block barriers:
-//   1. mas_restrict(level 0), all threads: each aggregate's sum of its
-//      members' residuals rm, four lanes per aggregate and component (lane k
-//      takes members k, k + 4, ... in order);
-//   2. mas_restrict(coarser levels), one wavefront: the children's sums;
-//   3. mas_correct, all threads: e = E^-1 r_agg per aggregate replaces rm;
-//      returns the thread's sum of r_agg . e.
-// base, na: the level's first aggregate in ra and their number; range(i, a):
-// first and end of aggregate a's members (rows of rm) or children (of ra),
-// packed in 16 bits each, for item i (the t / 4-th and on); inv(q, k): entry k of
-// aggregate q's inverse.
-template <class V, class RANGE>
-__device__ __forceinline__ void mas_restrict(int base, int na, const V (*from)[3], double (*ra)[3], int t, int nt,
-                                             RANGE range)
-{
-    const int sub = t % 4;
-    for (int i = t / 4; i < 3 * na; i += nt / 4) {
-        const int a = i / 3, c = i - 3 * a;
-        const uint32_t rg = range(i, a);
-        const int j0 = (int)(rg & 0xffffu) + sub, j1 = (int)(rg >> 16);
-        double acc = 0.0;
-        for (int j = j0; j < j1; j += 16) {  // four reads in flight
-            V v[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = from[min(j + 4 * k, j1 - 1)][c];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc += j + 4 * k < j1 ? (double)v[k] : 0.0;
-        }
-        acc += quad_other<0xb1>(acc);  // lane ^ 1
-        acc += quad_other<0x4e>(acc);  // lane ^ 2
-        if (sub == 0) ra[base + a][c] = acc;
-    }
-}
-template <class R, class INV>
-__device__ __forceinline__ double mas_correct(int total, R (*rm)[3], const double (*ra)[3], int t, INV inv)
-{
-    double rz = 0.0;
-    for (int i = t; i < 3 * total; i += kBlock) {
-        const int q = i / 3, c = i - 3 * q;
-        const R e = inv(q, 3 * c) * (R)ra[q][0] + inv(q, 3 * c + 1) * (R)ra[q][1] + inv(q, 3 * c + 2) * (R)ra[q][2];
-        rm[q][c] = e;
-        rz += ra[q][c] * (double)e;
-    }
-    return rz;
-}
 // orders a wavefront's LDS writes before its other lanes' reads
 __device__ __forceinline__ void wave_lds_fence()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+}
+
+// Coarse part of the multilevel preconditioner for one group, by the kBlock
+// threads of its unit (t: thread of the unit), between block barriers:
+//   1. mas_restrict, all threads: each level-0 aggregate's sum of its members'
+//      residuals rm, four lanes per aggregate and component;
+//   2. mas_coarse: the first wavefront sums the level-1 aggregates and the
+//      second the level-2 ones, both from level 0, and each forms e = E^-1
+//      r_agg of its level; the other two form level 0's. e replaces rm;
+//      returns the thread's sum of r_agg . e.
+// A chain of LDS round trips bounds it, so the levels run beside each other:
+// level by level over all threads it took 3,600 cycles of an iteration's
+// 19,000 (1,442 vertices, FP64).
+// na: aggregates per level, one level after the other in ra; range(l, a, first):
+// first and end of level l's aggregate a, packed in 16 bits each (level 0: rows
+// of rm, else level-0 aggregates; first: of the lane's first item); inv(q, k): entry k of aggregate q's inverse.
+// The code is straight for the usual sizes (a group has 10 to 40 level-0
+// aggregates of 8 to 27 members): a taken branch costs about as much as an LDS
+// read, so later rounds stand behind conditions that are uniform.
+//
+// Lanes that share a sum, as a shift: of level 0, 1 and 2.
+constexpr int kMasShare[kMasLevels] = {2, 2, 3};
+template <int L, class V, class RANGE>
+__device__ __forceinline__ void mas_sums(int na, const V (*from)[3], double (*to)[3], int t, int nt, RANGE range)
+{
+    constexpr int SH = kMasShare[L], W = 1 << SH;
+    const int sub = t & (W - 1), step = nt >> SH;
+    int i = t >> SH, base = 0;
+#pragma clang loop unroll(disable)
+    do {
+        if (i < 3 * na) {
+            const int a = i / 3, c = i - 3 * a;
+            const uint32_t rg = range(L, a, base == 0);
+            int j = (int)(rg & 0xffffu) + sub;
+            const int j1 = (int)(rg >> 16);
+            double acc = 0.0;
+            auto four = [&]() {  // four reads in flight
+                V v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = from[min(j + W * k, j1 - 1)][c];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc += j + W * k < j1 ? (double)v[k] : 0.0;
+            };
+            four();
+            if (__any(j + 4 * W < j1)) {
+#pragma clang loop unroll(disable)
+                for (j += 4 * W; __any(j < j1); j += 4 * W) four();
+            }
+            acc += quad_other<0xb1>(acc);                         // lane ^ 1
+            acc += quad_other<0x4e>(acc);                         // lane ^ 2
+            if constexpr (SH > 2) acc += quad_other<0x141>(acc);  // the half row mirrored: the other quad of eight lanes
+            if (sub == 0) to[a][c] = acc;
+        }
+        i += step;
+        base += step;
+    } while (base < 3 * na);
+}
+template <class R, class RANGE>
+__device__ __forceinline__ void mas_restrict(int na0, const R (*rm)[3], double (*ra)[3], int t, RANGE range)
+{
+    mas_sums<0>(na0, rm, ra, t, kBlock, range);
+}
+template <class R, class RANGE, class INV>
+__device__ __forceinline__ double mas_coarse(int nl, int na0, int na1, int na2, R (*rm)[3], double (*ra)[3], int t,
+                                             RANGE range, INV inv)
+{
+    const int lane = t % kWave, wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    double rz = 0.0;
+    auto solve = [&](int q0, int na, int first, int step) {
+        int i = first, base = 0;
+#pragma clang loop unroll(disable)
+        do {
+            if (i < 3 * na) {
+                const int a = i / 3, c = i - 3 * a, q = q0 + a;
+                const R i0 = inv(q, 3 * c), i1 = inv(q, 3 * c + 1), i2 = inv(q, 3 * c + 2);
+                const double r0 = ra[q][0], r1 = ra[q][1], r2 = ra[q][2];
+                const R e = i0 * (R)r0 + i1 * (R)r1 + i2 * (R)r2;
+                rm[q][c] = e;
+                rz += (c == 0 ? r0 : c == 1 ? r1 : r2) * (double)e;
+            }
+            i += step;
+            base += step;
+        } while (base < 3 * na);
+    };
+    if (wave == 0) {
+        if (nl > 1) {
+            mas_sums<1>(na1, ra, ra + na0, lane, kWave, range);
+            wave_lds_fence();
+            solve(na0, na1, lane, kWave);
+        }
+    } else if (wave == 1) {
+        if (nl > 2) {
+            mas_sums<2>(na2, ra, ra + na0 + na1, lane, kWave, range);
+            wave_lds_fence();
+            solve(na0 + na1, na2, lane, kWave);
+        }
+    } else {
+        solve(0, na0, t - 2 * kWave, 2 * kWave);
+    }
+    return rz;
 }
 
 // the sums over all chunks, by one wavefront (every lane gets them)

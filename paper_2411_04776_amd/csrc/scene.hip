@@ -638,12 +638,14 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
 {
     SceneDev &H = s.h;
     const size_t rs = real_size(s);
-    auto chunks = [&](int nt) {
-        return std::max(nblocks(H.nb_rows, nt / (2 * kRowsPerBlock)), nblocks(H.pcg_nvp, nt / kBlock));
+    auto chunks = [&](int v) {
+        return std::max(nblocks(H.nb_rows, team_rows(v, rs) / kRowsPerBlock), nblocks(H.pcg_nvp, team_units(v, rs)));
     };
-    const int narrow = team_narrow(rs);
-    H.team_nt = chunks(narrow) > (rs == sizeof(float) ? kTeamWide : kTeamMax) || chunks(2 * narrow) == 1 ? 2 * narrow : narrow;
-    H.team_T = chunks(H.team_nt);
+    const int v = chunks(2) == 1 ? 2 : chunks(3) == 1 ? 3 : chunks(0) > (rs == sizeof(float) ? kTeamWide : kTeamMax) ? 1 : 0;
+    H.team_variant = v;
+    H.team_rows = team_rows(v, rs);
+    H.team_units = team_units(v, rs);
+    H.team_T = chunks(v);
     H.team_A = std::max(s.mas_max_aggs, 1);
     H.team_spin = s.tune.team_spin;
     H.team_fit = 0;
@@ -652,7 +654,7 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
     IPC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
     if (H.team_T > std::min(kTeamMax, cus)) return;
     if ((uint64_t)H.n_slots * kSlice * 9 * rs >= 0xffffffffu) return;  // the matrix is reached by 32-bit byte offsets
-    const int rows = H.team_nt / 2, n = H.n;
+    const int rows = H.team_rows, n = H.n;
     std::vector<int32_t> hptr(H.team_T + 1, 0), hlist, at(n, -1);
     std::vector<uint16_t> lcol((size_t)H.n_slots * kSlice, 0);
     for (int w = 0; w < H.team_T; ++w) {
@@ -669,7 +671,7 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
         hptr[w + 1] = (int32_t)hlist.size();
         H.team_H = std::max(H.team_H, (int)(hlist.size() - first));
     }
-    if (H.team_H > 0xffff || team_lds_bytes(H.team_nt, H.team_H, H.team_A, rs) > kTeamLds - 1024) return;
+    if (H.team_H > 0xffff || team_lds_bytes(v, H.team_H, H.team_A, rs) > kTeamDyn) return;
     std::vector<int32_t> pos(n, 0);
     for (int w = 0; w < H.team_T; ++w) {
         for (int k = hptr[w]; k < hptr[w + 1]; ++k) pos[hlist[k]] = k - hptr[w];
@@ -686,6 +688,8 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
     H.team_lcol = upload(s, lcol);
     H.team_z = dalloc_bytes(s, 4 * (size_t)n * rs);
     H.team_q = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.team_dA = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.team_dB = dalloc_bytes(s, 4 * (size_t)n * rs);
     H.team_ll = dalloc<unsigned long long>(s, 4 * (size_t)H.team_T);
     IPC_HIP(hipStreamSynchronize(s.stream));  // host vectors above are locals
     team_prepare_device();
@@ -2122,9 +2126,9 @@ int64_t ipc_scene_footprint_bytes(const ipc_scene_desc *d)
     if (!check_desc(d)) return -1;
     int64_t n = (int64_t)d->n_verts + d->n_ind_verts, m = d->n_tets;
     int64_t rs = d->precision == IPC_MIXED ? 4 : 8;
-    int64_t per_vertex = 8 * (3 * 9 + 1 + 12) + rs * (3 * 8 + 9) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers) and one scalar; the PCG vectors in R
+    int64_t per_vertex = 8 * (3 * 9 + 1 + 12) + rs * (3 * 8 + 9 + 4 * 5) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers), one scalar, the contact gradient and diagonal block; the PCG vectors in R, five of them padded
     int64_t per_tet = 4 * 4 + 8 * 10 + rs * (12 + 90) + 4 * 16 + 4 * 4;
-    int64_t bell = n * 16 * (9 * rs + 4 + 4);
+    int64_t bell = n * 16 * (9 * rs + 4 + 4 + 2);
     int64_t surf = 4 * (int64_t)std::pow((double)d->n_verts, 2.0 / 3.0) + d->n_ind_verts + 2 * d->n_ind_tris;
     int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * (156 + 108) + 4 * 33);
     return n * per_vertex + m * per_tet + bell + contact + (8 << 20);
