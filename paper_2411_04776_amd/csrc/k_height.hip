@@ -7,8 +7,11 @@
 // an upward-facing gel surface triangle), 0 where it meets none: the
 // indentation depth below the reference height. Upward-facing: positive
 // signed xy area, the surface triangles being oriented outward. Triangles are
-// rasterised one per thread over their xy bounding box (widened by one
-// pixel); a pixel is inside when its three edge functions are >= 0, z is the
+// rasterised one per wavefront over their xy bounding box (widened by one
+// pixel), 16 x 4 pixels at a time: a triangle of an ordinary image has a box of
+// about 100 pixels, and one thread per triangle left a chain of as many edge
+// tests, divisions and atomics (53.1 us for 320 x 400 pixels of a 40x50x8 gel,
+// 6.5 us so); a pixel is inside when its three edge functions are >= 0, z is the
 // barycentric interpolation. The maximum is taken with
 // 64-bit atomics on an order-preserving integer image of the FP64 height, so
 // the map does not depend on the order of the threads.
@@ -36,10 +39,12 @@ __global__ void k_height_clear(unsigned long long *key, int64_t np)
     if (p < np) key[p] = 0ull;
 }
 
-__global__ void k_height_raster(const double *__restrict__ x, const int32_t *__restrict__ trv, int n_tris,
+constexpr int kPixX = 16, kPixY = kWave / kPixX;
+__global__ void __launch_bounds__(kBlock) k_height_raster(const double *__restrict__ x, const int32_t *__restrict__ trv, int n_tris,
                                 int n_gel_tris, HeightSpec hs, unsigned long long *key)
 {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave));
+    const int li = (int)threadIdx.x % kPixX, lj = (int)threadIdx.x % kWave / kPixX;
     if (t >= n_gel_tris) return;
     const double *a = x + 3 * (int64_t)trv[t], *b = x + 3 * (int64_t)trv[n_tris + t],
                  *c = x + 3 * (int64_t)trv[2 * (int64_t)n_tris + t];
@@ -52,9 +57,9 @@ __global__ void k_height_raster(const double *__restrict__ x, const int32_t *__r
     if (!(fi1 >= 0.0) || !(fj1 >= 0.0) || !(fi0 < (double)hs.nx) || !(fj0 < (double)hs.ny)) return;
     int i0 = (int)fmax(fi0, 0.0), i1 = (int)fmin(fi1, (double)(hs.nx - 1));
     int j0 = (int)fmax(fj0, 0.0), j1 = (int)fmin(fj1, (double)(hs.ny - 1));
-    for (int j = j0; j <= j1; ++j) {
+    for (int j = j0 + lj; j <= j1; j += kPixY) {
         double py = hs.y0 + j * hs.dy;
-        for (int i = i0; i <= i1; ++i) {
+        for (int i = i0 + li; i <= i1; i += kPixX) {
             double px = hs.x0 + i * hs.dx;
             double w0 = (c[0] - b[0]) * (py - b[1]) - (c[1] - b[1]) * (px - b[0]);
             double w1 = (a[0] - c[0]) * (py - c[1]) - (a[1] - c[1]) * (px - c[0]);
@@ -80,7 +85,7 @@ void launch_height_map(Scene &s, const HeightSpec &hs, unsigned long long *key, 
     int nb = (int)((np + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_height_clear, dim3(nb), dim3(kBlock), 0, strm, key, np);
     if (s.n_gel_tris > 0)
-        hipLaunchKernelGGL(k_height_raster, dim3(nblocks(s.n_gel_tris)), dim3(kBlock), 0, strm, s.h.x, s.h.trv,
+        hipLaunchKernelGGL(k_height_raster, dim3(nblocks(s.n_gel_tris, kBlock / kWave)), dim3(kBlock), 0, strm, s.h.x, s.h.trv,
                            s.h.n_tris, s.n_gel_tris, hs, key);
     hipLaunchKernelGGL(k_height_out, dim3(nb), dim3(kBlock), 0, strm, key, np, hs.z_ref, out);
 }
