@@ -134,9 +134,10 @@ struct SceneDev {
     int32_t *tv;
     double *Bm, *vol;
     void *eg, *eH;
-    int32_t *vt_ptr, *vt_src;
+    int32_t *vt_ptr, *vt_src;  // tets of each vertex, (place, corner): lists padded per kSlice vertices
     // elastic matrix
-    int32_t *slice_ptr, *bcol, *g_ptr, *g_src;
+    int32_t *slice_ptr, *slot_slice, *bcol;
+    int32_t *g_ptr, *g_src;    // element blocks of each stored block, (place, corners): padded per slot
     void *bval, *Minv, *grad;
     // surface primitives and broad phase
     int32_t *pts, *ev, *trv, *surf_verts;

@@ -291,10 +291,24 @@ __global__ void __launch_bounds__(kBlock) k_elastic_elements(Launch L)
 template <class R>
 __device__ __forceinline__ void vertex_gradient(const SceneDev &S, int i, double g[3])
 {
-    const R *eg = as<R>(S.eg);
-    for (int k = S.vt_ptr[i]; k < S.vt_ptr[i + 1]; ++k) {
-        int src = S.vt_src[k], e = src >> 2, a = src & 3;
-        for (int c = 0; c < 3; ++c) g[c] += (double)eg[(int64_t)(a * 3 + c) * S.m + e];
+    const auto eg = glob(as<R>(S.eg));
+    const auto src = glob(S.vt_src) + i % kSlice;
+    const int64_t m = S.m;
+    const int k1 = S.vt_ptr[i / kSlice + 1];
+    constexpr int kU = 8;  // tets whose reads are in flight
+    for (int k = S.vt_ptr[i / kSlice]; k < k1; k += kU) {
+        int t[kU];
+        R v[kU][3];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) t[u] = src[(int64_t)min(k + u, k1 - 1) * kSlice];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[u][c] = eg[((max(t[u], 0) & 3) * 3 + c) * m + (max(t[u], 0) >> 2)];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) g[c] = k + u < k1 && t[u] >= 0 ? g[c] + (double)v[u][c] : g[c];
     }
     if (i < S.n_gel) {
         double kk = S.mass[i] * S.inv_h2;
@@ -333,45 +347,54 @@ __global__ void __launch_bounds__(kBlock) k_assemble_gradient(Launch L)
     for (int c = 0; c < 3; ++c) grad[3 * i + c] = (R)g[c];
 }
 
-// Matrix gather: one thread per stored BELL block. Sums the element blocks
-// listed for this (row, col) in tet order; the diagonal block also takes the
+// Matrix gather: one thread per stored BELL block, a wavefront per slot. Sums
+// the element blocks listed for this (row, col) in tet order; the diagonal block also takes the
 // inertia / target term and the contact diagonal block, and writes the
 // inverse used by the block-Jacobi preconditioner. Fixed rows/cols become
-// identity / zero.
+// identity / zero. Bound by the element blocks' reads (405 MB through L2 at
+// 704,000 tets, FP32); with tets stored by pattern, lists padded per slot and
+// two blocks in flight 228 -> 120 us there, 64 -> 37 us at 80,000 tets FP64.
 template <class R>
 __global__ void __launch_bounds__(kBlock) k_assemble_bell(Launch L)
 {
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
-    int64_t slot_lane = (int64_t)lb * blockDim.x + threadIdx.x;
-    int64_t total = (int64_t)S.n_slots * kSlice;
-    if (slot_lane >= total) return;
-    int64_t slot = slot_lane / kSlice;
-    int lane = (int)(slot_lane % kSlice);
-    int lo = 0, hi = S.n_slices;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (S.slice_ptr[mid] <= slot) lo = mid; else hi = mid;
-    }
-    int row = lo * kSlice + lane;
-    int k = (int)(slot - S.slice_ptr[lo]);
-    int col = S.bcol[slot_lane];
-    const R *eH = as<R>(S.eH);
+    const int slot = __builtin_amdgcn_readfirstlane(lb * (kBlock / kSlice) + (int)threadIdx.x / kSlice);
+    if (slot >= S.n_slots) return;
+    const int lane = (int)threadIdx.x % kSlice, sl = S.slot_slice[slot];
+    const int row = sl * kSlice + lane, k = slot - S.slice_ptr[sl];
+    const int col = S.bcol[(int64_t)slot * kSlice + lane];
+    const auto eH = glob(as<R>(S.eH));
+    const auto src = glob(S.g_src) + lane;
+    const int64_t m = S.m;
     double A[9];
     for (int c = 0; c < 9; ++c) A[c] = 0.0;
-    if (col >= 0) {
-        for (int t = S.g_ptr[slot_lane]; t < S.g_ptr[slot_lane + 1]; ++t) {
-            int src = S.g_src[t];
-            int e = src >> 4, a = (src >> 2) & 3, b = src & 3;
-            if (a <= b) {
-                int blk = elem_block(a, b);
-                for (int c = 0; c < 9; ++c) A[c] += (double)eH[(int64_t)(blk * 9 + c) * S.m + e];
-            } else {
-                int blk = elem_block(b, a);
-                for (int i = 0; i < 3; ++i)
-                    for (int j = 0; j < 3; ++j) A[i * 3 + j] += (double)eH[(int64_t)(blk * 9 + j * 3 + i) * S.m + e];
-            }
+    const int t1 = S.g_ptr[slot + 1];
+    for (int t = S.g_ptr[slot]; t < t1; t += 2) {  // two blocks' reads in flight
+        int g[2];
+        R v[2][9];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) g[u] = t + u < t1 ? src[(int64_t)(t + u) * kSlice] : -1;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int a = (g[u] >> 2) & 3, b = g[u] & 3;
+            const int64_t from = g[u] >= 0 ? elem_block(min(a, b), max(a, b)) * 9 * m + (g[u] >> 4) : 0;
+#pragma unroll
+            for (int c = 0; c < 9; ++c) v[u][c] = eH[from + c * m];
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const bool upper = ((g[u] >> 2) & 3) <= (g[u] & 3);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const double x = (double)(upper ? v[u][i * 3 + j] : v[u][j * 3 + i]);
+                    A[i * 3 + j] = g[u] >= 0 ? A[i * 3 + j] + x : A[i * 3 + j];
+                }
+        }
+    }
+    if (col >= 0) {
         if (k == 0) {
             double dk = row < S.n_gel ? S.mass[row] * S.inv_h2 : S.k_target;
             if (row < S.n_gel && S.attached && S.attached[row]) dk += S.k_target;
@@ -387,7 +410,7 @@ __global__ void __launch_bounds__(kBlock) k_assemble_bell(Launch L)
         }
     }
     R *bval = as<R>(S.bval);
-    for (int c = 0; c < 9; ++c) bval[(slot * 9 + c) * kSlice + lane] = (R)A[c];
+    for (int c = 0; c < 9; ++c) bval[((int64_t)slot * 9 + c) * kSlice + lane] = (R)A[c];
     if (k == 0 && row < S.n) {
         double Inv[9];
         inverse3(A, Inv);
@@ -423,7 +446,10 @@ __global__ void k_rest_mass(Launch L)
     int i = lb * blockDim.x + threadIdx.x;
     if (i >= S.n) return;
     double acc = 0.0;
-    for (int k = S.vt_ptr[i]; k < S.vt_ptr[i + 1]; ++k) acc += S.rho * S.vol[S.vt_src[k] >> 2] / 4.0;
+    for (int k = S.vt_ptr[i / kSlice]; k < S.vt_ptr[i / kSlice + 1]; ++k) {
+        const int src = S.vt_src[(int64_t)k * kSlice + i % kSlice];
+        if (src >= 0) acc += S.rho * S.vol[src >> 2] / 4.0;
+    }
     S.mass[i] = acc;
 }
 

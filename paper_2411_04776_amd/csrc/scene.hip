@@ -696,6 +696,52 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
     H.team_fit = 1;
 }
 
+// Storage order of the tets. In a regular mesh neighbouring vertices' tets
+// differ by a shift of their ids only; tets of one such pattern, in the order
+// of their first vertex, are stored side by side, so the values that 64
+// consecutive vertices or matrix rows gather from them are consecutive too
+// (cell by cell, a wavefront's reads of one value touched six times the lines).
+// Patterns are grouped within 4,096 vertices, which keeps a neighbourhood in
+// an L2. A mesh whose patterns repeat less than 32 times keeps its order.
+static std::vector<int32_t> tet_places(const int32_t *T, int m)
+{
+    struct Rec {
+        int32_t key[5], e;  // vertex group, three shifts, first vertex
+        bool operator<(const Rec &o) const { return std::lexicographical_compare(key, key + 5, o.key, o.key + 5); }
+    };
+    std::vector<Rec> r(m);
+    for (int e = 0; e < m; ++e) {
+        const int32_t *t = T + 4 * (size_t)e;
+        r[e] = {{t[0] / 4096, t[1] - t[0], t[2] - t[0], t[3] - t[0], t[0]}, e};
+    }
+    std::sort(r.begin(), r.end());
+    int runs = 0;
+    for (int e = 0; e < m; ++e) runs += e == 0 || !std::equal(r[e].key, r[e].key + 4, r[e - 1].key);
+    std::vector<int32_t> place(m);
+    for (int e = 0; e < m; ++e) place[(int64_t)runs * 32 <= m ? r[e].e : e] = e;
+    return place;
+}
+
+// Lists of n rows, padded to the longest of each kSlice consecutive ones: entry
+// j of row i at (ptr[i / kSlice] + j) * kSlice + i % kSlice, -1 past its end;
+// a row's values keep their order.
+static void sliced_lists(size_t n, const std::vector<int32_t> &row, const std::vector<int32_t> &val,
+                         std::vector<int32_t> &ptr, std::vector<int32_t> &out)
+{
+    const size_t ns = (n + kSlice - 1) / kSlice;
+    std::vector<int32_t> cnt(ns * kSlice, 0);
+    for (int32_t i : row) cnt[i]++;
+    ptr.assign(ns + 1, 0);
+    for (size_t k = 0; k < ns; ++k)
+        ptr[k + 1] = ptr[k] + *std::max_element(cnt.begin() + k * kSlice, cnt.begin() + (k + 1) * kSlice);
+    out.assign((size_t)ptr[ns] * kSlice, -1);
+    std::fill(cnt.begin(), cnt.end(), 0);
+    for (size_t k = 0; k < row.size(); ++k) {
+        const size_t i = row[k];
+        out[((size_t)ptr[i / kSlice] + cnt[i]++) * kSlice + i % kSlice] = val[k];
+    }
+}
+
 static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
 {
     int n_gel_tris = 0, n_gel_edges = 0;
@@ -792,14 +838,17 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
         }
     s.h.n_pts = (int)s.h_pts.size();
 
-    // ---- vertex -> tet incidence (tet order)
-    std::vector<int32_t> vt_ptr(n + 1, 0), vt_src(4 * (size_t)m);
-    for (int64_t k = 0; k < 4 * (int64_t)m; ++k) vt_ptr[d.T[k] + 1]++;
-    for (int i = 0; i < n; ++i) vt_ptr[i + 1] += vt_ptr[i];
+    // ---- places of the tets in storage, and vertex -> tet incidence (tet order)
+    const std::vector<int32_t> place = tet_places(d.T, m);
+    std::vector<int32_t> vt_ptr, vt_src;
     {
-        std::vector<int32_t> cur(vt_ptr.begin(), vt_ptr.end() - 1);
+        std::vector<int32_t> row(4 * (size_t)m), val(4 * (size_t)m);
         for (int e = 0; e < m; ++e)
-            for (int a = 0; a < 4; ++a) vt_src[cur[d.T[4 * e + a]]++] = e * 4 + a;
+            for (int a = 0; a < 4; ++a) {
+                row[4 * (size_t)e + a] = d.T[4 * e + a];
+                val[4 * (size_t)e + a] = place[e] * 4 + a;
+            }
+        sliced_lists((size_t)n, row, val, vt_ptr, vt_src);
     }
     // ---- BELL pattern: row = diagonal first, then sorted neighbours
     std::vector<std::vector<int32_t>> nbr(n);
@@ -822,6 +871,9 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
         slice_ptr[sl + 1] = slice_ptr[sl] + w;
     }
     s.h.n_slots = slice_ptr[s.h.n_slices];
+    std::vector<int32_t> slot_slice(s.h.n_slots);
+    for (int sl = 0; sl < s.h.n_slices; ++sl)
+        std::fill(slot_slice.begin() + slice_ptr[sl], slot_slice.begin() + slice_ptr[sl + 1], sl);
     s.nnzb = 0;
     for (int row = 0; row < n; ++row) s.nnzb += 1 + (int64_t)nbr[row].size();
     size_t nent = (size_t)s.h.n_slots * kSlice;
@@ -840,19 +892,19 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
         }
         return (size_t)(slice_ptr[sl] + k) * kSlice + l;
     };
-    std::vector<int32_t> g_ptr(nent + 1, 0), g_src(16 * (size_t)m);
-    for (int e = 0; e < m; ++e)
-        for (int a = 0; a < 4; ++a)
-            for (int b = 0; b < 4; ++b) g_ptr[entry_of(d.T[4 * e + a], d.T[4 * e + b]) + 1]++;
-    for (size_t i = 0; i < nent; ++i) g_ptr[i + 1] += g_ptr[i];
+    std::vector<int32_t> g_ptr, g_src;
     {
-        std::vector<int32_t> cur(g_ptr.begin(), g_ptr.end() - 1);
+        std::vector<int32_t> row(16 * (size_t)m), val(16 * (size_t)m);
         for (int e = 0; e < m; ++e)
             for (int a = 0; a < 4; ++a)
-                for (int b = 0; b < 4; ++b)
-                    g_src[cur[entry_of(d.T[4 * e + a], d.T[4 * e + b])]++] = e * 16 + a * 4 + b;
+                for (int b = 0; b < 4; ++b) {
+                    const size_t k = 16 * (size_t)e + 4 * a + b;
+                    row[k] = (int32_t)entry_of(d.T[4 * e + a], d.T[4 * e + b]);
+                    val[k] = place[e] * 16 + a * 4 + b;
+                }
+        sliced_lists(nent, row, val, g_ptr, g_src);
     }
-    s.n_gather = (int64_t)g_src.size();
+    s.n_gather = 16 * (int64_t)m;
 
     // ---- multilevel aggregates of the free gel vertices (preconditioner)
     MasHost mas;
@@ -870,7 +922,7 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
     // ---- SoA tets, surface arrays
     std::vector<int32_t> tv(4 * (size_t)m);
     for (int e = 0; e < m; ++e)
-        for (int a = 0; a < 4; ++a) tv[(size_t)a * m + e] = d.T[4 * e + a];
+        for (int a = 0; a < 4; ++a) tv[(size_t)a * m + place[e]] = d.T[4 * e + a];
     std::vector<int32_t> ev(2 * (size_t)s.h.n_edges), trv(3 * (size_t)s.h.n_tris);
     for (int k = 0; k < s.h.n_edges; ++k) {
         ev[k] = s.h_edges[2 * k];
@@ -951,6 +1003,7 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
     H.vt_ptr = upload(s, vt_ptr);
     H.vt_src = upload(s, vt_src);
     H.slice_ptr = upload(s, slice_ptr);
+    H.slot_slice = upload(s, slot_slice);
     H.bcol = upload(s, bcol);
     H.bval = dalloc_bytes(s, nent * 9 * rs);
     H.g_ptr = upload(s, g_ptr);
@@ -2127,8 +2180,8 @@ int64_t ipc_scene_footprint_bytes(const ipc_scene_desc *d)
     int64_t n = (int64_t)d->n_verts + d->n_ind_verts, m = d->n_tets;
     int64_t rs = d->precision == IPC_MIXED ? 4 : 8;
     int64_t per_vertex = 8 * (3 * 9 + 1 + 12) + rs * (3 * 8 + 9 + 4 * 5) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers), one scalar, the contact gradient and diagonal block; the PCG vectors in R, five of them padded
-    int64_t per_tet = 4 * 4 + 8 * 10 + rs * (12 + 90) + 4 * 16 + 4 * 4;
-    int64_t bell = n * 16 * (9 * rs + 4 + 4 + 2);
+    int64_t per_tet = 4 * 4 + 8 * 10 + rs * (12 + 90) + (4 * 16 + 4 * 4) * 4 / 3;  // the lists padded
+    int64_t bell = n * 16 * (9 * rs + 4 + 2);
     int64_t surf = 4 * (int64_t)std::pow((double)d->n_verts, 2.0 / 3.0) + d->n_ind_verts + 2 * d->n_ind_tris;
     int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * (156 + 108) + 4 * 33);
     return n * per_vertex + m * per_tet + bell + contact + (8 << 20);
