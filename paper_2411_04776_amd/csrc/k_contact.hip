@@ -228,8 +228,8 @@ __device__ void boxes_body(const SceneDev &S, int lb, int kind, int swept)
         }
     }
     for (int c = 0; c < 3; ++c) {
-        box[c * N + i] = lo[c] - r;
-        box[(3 + c) * N + i] = hi[c] + r;
+        box[6 * (int64_t)i + c] = lo[c] - r;
+        box[6 * (int64_t)i + 3 + c] = hi[c] + r;
     }
 }
 
@@ -253,7 +253,7 @@ __global__ void k_boxes_all(Launch L, int swept, int extent)
     int i = kb * blockDim.x + threadIdx.x;
     double e = 0.0;
     if (i < N)
-        for (int c = 0; c < 3; ++c) e = fmax(e, box[(3 + c) * N + i] - box[c * N + i]);
+        for (int c = 0; c < 3; ++c) e = fmax(e, box[6 * (int64_t)i + 3 + c] - box[6 * (int64_t)i + c]);
     e = block_sum_all(e);
     if (threadIdx.x == 0) S.red[(kind == 1 ? 0 : ne) + kb] = e;
 }
@@ -333,7 +333,7 @@ __device__ void hash_insert_body(const Launch &L, int s, const SceneDev &S, int 
     double h = *S.cell_h;
     int lo[3], hi[3];
     for (int c = 0; c < 3; ++c) {
-        double a = box[c * N + i], b = box[(3 + c) * N + i];
+        double a = box[6 * (int64_t)i + c], b = box[6 * (int64_t)i + 3 + c];
         if (!(a <= b) || !((b - a) / h < (double)kMaxSpan)) {
             if (!FILL) atomicOr(&L.out[s].bad, 1);
             return;
@@ -382,41 +382,48 @@ __device__ __forceinline__ bool ee_admissible(const SceneDev &S, int a0, int a1,
     return true;
 }
 
-// kLanesQ lanes per query primitive (PT: surface point index, EE: edge
-// index) split the hash entries of the cells its box spans. COUNT: each lane's number of
+// kLanesQ lanes per query primitive (PT: surface point index, EE: edge index).
+// The (body, cell) pairs that its box spans are looked up a lane each, and the
+// lanes then split the buckets' entries between them, two in flight each: cell
+// by cell, every lane computed every hash and a query waited for two dependent
+// loads per cell. Boxes are six doubles in a row, one line a gather. Bound by
+// those gathers' latency: count pass 158 -> 128 us and fill pass 92 -> 49 us
+// (26,000 points and 77,000 edges), 554 -> 418 and 161 -> 119 us (a list of 128
+// gels). Looking the next cells up ahead gained nothing. COUNT: each lane's number of
 // accepted pairs, and the query's total. Else each lane writes its pairs at
-// q_off plus the counts of the lanes before it, and lane 0 sorts the query's
-// segment by b (each pair is found in exactly one cell, so the sorted segment
+// q_off plus the counts of the lanes before it, and the query's segment is
+// sorted by b (each pair is found in exactly one cell, so the sorted segment
 // does not depend on the split). swept selects the output list.
+static_assert(kLanesQ == 8, "eight lanes' sums");
 template <int KIND, bool COUNT>
 __device__ void query_body(const Launch &L, int s, const SceneDev &S, int lb, int swept)
 {
     int NA = KIND == 0 ? S.n_pts : S.n_edges;
-    int NB = KIND == 0 ? S.n_tris : S.n_edges;
     int64_t gt = (int64_t)lb * blockDim.x + threadIdx.x;
     int qa = (int)(gt / kLanesQ), lane = (int)(gt % kLanesQ);
     const bool live = qa < NA;  // whole lane groups
-    const double *abox = KIND == 0 ? S.pbox : S.ebox;
-    const double *bbox = KIND == 0 ? S.tbox : S.ebox;
+    const auto abox = glob(KIND == 0 ? S.pbox : S.ebox);
+    const auto bbox = glob(KIND == 0 ? S.tbox : S.ebox);
     const int table = KIND == 0 ? 0 : 1;
     uint32_t mask = (1u << S.ht_bits[table]) - 1;
-    const int32_t *start = S.ht_start[table];
-    const int4 *entries = S.ht_entries[table];
+    const auto start = glob(S.ht_start[table]);
+    typedef int Int4 __attribute__((ext_vector_type(4)));
+    const auto entries = glob((const Int4 *)S.ht_entries[table]);
     int cap = S.ht_cap[table];
     int qidx = (KIND == 0 ? 0 : S.n_pts) + qa;
     double h = *S.cell_h;
     double alo[3], ahi[3];
-    int clo[3], chi[3];
+    int clo[3], nc[3];
     bool ok = live;
     for (int c = 0; c < 3 && ok; ++c) {
-        alo[c] = abox[c * NA + qa];
-        ahi[c] = abox[(3 + c) * NA + qa];
+        alo[c] = abox[6 * (int64_t)qa + c];
+        ahi[c] = abox[6 * (int64_t)qa + 3 + c];
         if (!(alo[c] <= ahi[c]) || !((ahi[c] - alo[c]) / h < (double)kMaxSpan)) {
             ok = false;
             break;
         }
         clo[c] = cell_of(alo[c], h);
-        chi[c] = cell_of(ahi[c], h);
+        nc[c] = cell_of(ahi[c], h) - clo[c] + 1;
     }
     int va0 = -1, va1 = -1, a_id = -1;
     if (ok) {
@@ -429,22 +436,27 @@ __device__ void query_body(const Launch &L, int s, const SceneDev &S, int lb, in
             a_id = qa;
         }
     }
-    int32_t *out = swept ? S.cand_sw : S.cand;
+    const auto out = glob(swept ? S.cand_sw : S.cand);
     int64_t ocap = swept ? S.sw_cap : S.cand_cap;
     int64_t o0 = 0, o = 0;
     // the count pass keeps a lane's first kQueryKeep pairs; the fill pass
     // copies them when that was all of them and walks the buckets again only
-    // for lanes that found more
-    int32_t *keep = S.q_keep + ((int64_t)kLanesQ * qidx + lane) * kQueryKeep;
-    bool walk = ok;
+    // where a lane of the query found more
+    const auto keep = glob(S.q_keep) + ((int64_t)kLanesQ * qidx + lane) * kQueryKeep;
+    bool walk = ok, kept = false;
     int count = 0;
     if (!COUNT && ok) {
         o0 = S.q_off[qidx];
-        o = o0;
-        for (int j = 0; j < lane; ++j) o += S.q_lane[(int64_t)kLanesQ * qidx + j];
         const int mine = S.q_lane[(int64_t)kLanesQ * qidx + lane];
-        if (mine <= kQueryKeep) {
-            walk = false;
+        int upto = mine;
+#pragma unroll
+        for (int d = 1; d < kLanesQ; d <<= 1) {
+            const int up = __shfl_up(upto, d, kLanesQ);
+            if (lane >= d) upto += up;
+        }
+        o = o0 + upto - mine;
+        kept = mine <= kQueryKeep;
+        if (kept) {
             for (int j = 0; j < mine; ++j)
                 if (o + j < ocap) {
                     out[o + j] = KIND;
@@ -453,62 +465,119 @@ __device__ void query_body(const Launch &L, int s, const SceneDev &S, int lb, in
                 }
             count = mine;
         }
+        int all = kept;
+#pragma unroll
+        for (int d = 1; d < kLanesQ; d <<= 1) all &= __shfl_xor(all, d, kLanesQ);
+        walk = !all;
     }
     // bodies whose entries this query scans: a gel point or edge looks at
     // the indenter's, and at the gel's under self-contact; an indenter point
     // at the gel's; an indenter edge at none (its pairs with gel edges have
-    // the gel edge first). Lanes split the (body, cell) pairs; the sort below
-    // puts the query's pairs in b order whatever the split.
+    // the gel edge first).
     const int b_gel = KIND == 0 ? S.n_gel_tris : S.n_gel_edges;
-    bool scan0 = false, scan1 = false;
-    if (ok) {
+    int64_t cells = 0, total = 0;  // (body, cell) pairs: the gel's cells, then the indenter's
+    if (walk) {
         const bool a_gel = KIND == 0 ? va0 < S.n_gel : qa < S.n_gel_edges;
-        scan0 = a_gel ? S.self_contact != 0 : KIND == 0;
-        scan1 = a_gel;
+        const bool scan0 = a_gel ? S.self_contact != 0 : KIND == 0, scan1 = a_gel;
+        const int64_t n = (int64_t)nc[0] * nc[1] * nc[2];
+        cells = scan0 ? n : 0;
+        total = cells + (scan1 ? n : 0);
     }
-    // the (body, cell) pairs in a fixed order, taken by all the query's
-    // lanes together; a bucket's entries are split over them (entry k to
-    // lane k mod kLanesQ): a query spans one to a few cells, and a bucket
-    // beside the indenter holds tens of entries
-    for (int body = 0; body < 2 && walk; ++body) {
-        if (!(body == 0 ? scan0 : scan1)) continue;
-        for (int iz = clo[2]; iz <= chi[2]; ++iz)
-            for (int iy = clo[1]; iy <= chi[1]; ++iy)
-                for (int ix = clo[0]; ix <= chi[0]; ++ix) {
-                    uint32_t bkt = cell_hash(ix, iy, iz, body, mask);
-                    int kend = min(start[bkt + 1], cap);
-                    for (int k = start[bkt] + lane; k < kend; k += kLanesQ) {
-                        int4 en = entries[k];
-                        if (en.x != ix || en.y != iy || en.z != iz) continue;
-                        int b = en.w;
-                        if ((b >= b_gel) != (body == 1)) continue;  // another body's entry in this bucket
-                        if (KIND == 1 && b <= qa) continue;
-                        // box test first: most bucket entries fail it, and it
-                        // needs no index loads
-                        bool ov = true;
-                        double corner[3];
-                        for (int c = 0; c < 3; ++c) {
-                            double blo = bbox[c * NB + b], bhi = bbox[(3 + c) * NB + b];
-                            ov = ov && (alo[c] <= bhi) && (blo <= ahi[c]);
-                            corner[c] = fmax(alo[c], blo);
-                        }
-                        if (!ov) continue;
-                        if (cell_of(corner[0], h) != ix || cell_of(corner[1], h) != iy || cell_of(corner[2], h) != iz)
-                            continue;
-                        if (KIND == 0) {
-                            if (!pt_admissible(S, va0, S.trv[b], S.trv[S.n_tris + b], S.trv[2 * S.n_tris + b])) continue;
-                        } else {
-                            if (!ee_admissible(S, va0, va1, S.ev[b], S.ev[S.n_edges + b])) continue;
-                        }
-                        if (COUNT && count < kQueryKeep) keep[count] = b;
-                        if (!COUNT && o + count < ocap) {
-                            out[o + count] = KIND;
-                            out[ocap + o + count] = a_id;
-                            out[2 * ocap + o + count] = b;
-                        }
-                        ++count;
+    for (int64_t base = 0; base < total; base += kLanesQ) {
+        // this lane's pair: its bucket's entries
+        int ix = 0, iy = 0, iz = 0, body = 0, first = 0, len = 0;
+        if (base + lane < total) {
+            int64_t q = base + lane;
+            body = q >= cells ? 1 : 0;
+            if (body) q -= cells;
+            if (total <= 0x7fffffff) {
+                const uint32_t u = (uint32_t)q, nx = (uint32_t)nc[0], ny = (uint32_t)nc[1], r = u / nx;
+                ix = (int)(u - r * nx);
+                iz = (int)(r / ny);
+                iy = (int)(r - (uint32_t)iz * ny);
+            } else {
+                ix = (int)(q % nc[0]);
+                iy = (int)(q / nc[0] % nc[1]);
+                iz = (int)(q / nc[0] / nc[1]);
+            }
+            ix += clo[0];
+            iy += clo[1];
+            iz += clo[2];
+            const uint32_t bkt = cell_hash(ix, iy, iz, body, mask);
+            first = start[bkt];
+            len = max(min(start[bkt + 1], cap) - first, 0);
+        }
+        int upto = len;  // entries of this lane's bucket and those before it
+#pragma unroll
+        for (int d = 1; d < kLanesQ; d <<= 1) {
+            const int up = __shfl_up(upto, d, kLanesQ);
+            if (lane >= d) upto += up;
+        }
+        int ends[kLanesQ];
+#pragma unroll
+        for (int j = 0; j < kLanesQ; ++j) ends[j] = __shfl(upto, j, kLanesQ);
+        first -= upto - len;  // entry f of the batch is at first + f in its bucket's lane
+        for (int f0 = 0; f0 < ends[kLanesQ - 1]; f0 += 2 * kLanesQ) {
+            Int4 en[2];
+            int cx[2], cy[2], cz[2], cb[2];
+            bool in[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int f = f0 + u * kLanesQ + lane;
+                in[u] = f < ends[kLanesQ - 1];
+                int j = 0;
+#pragma unroll
+                for (int t = 0; t < kLanesQ - 1; ++t) j += f >= ends[t] ? 1 : 0;
+                const int at = __shfl(first, j, kLanesQ) + f;
+                cx[u] = __shfl(ix, j, kLanesQ);
+                cy[u] = __shfl(iy, j, kLanesQ);
+                cz[u] = __shfl(iz, j, kLanesQ);
+                cb[u] = __shfl(body, j, kLanesQ);
+                en[u] = in[u] ? entries[at] : Int4{0, 0, 0, -1};
+            }
+            double blo[2][3], bhi[2][3];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int b = en[u].w;
+                in[u] = in[u] && en[u].x == cx[u] && en[u].y == cy[u] && en[u].z == cz[u] &&
+                        (b >= b_gel) == (cb[u] == 1) &&  // not another body's entry in this bucket
+                        !(KIND == 1 && b <= qa);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    blo[u][c] = in[u] ? bbox[6 * (int64_t)b + c] : 0.0;
+                    bhi[u][c] = in[u] ? bbox[6 * (int64_t)b + 3 + c] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // box test first: most entries fail it, and it needs no index loads
+                const int b = en[u].w;
+                bool ov = in[u];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) ov = ov && alo[c] <= bhi[u][c] && blo[u][c] <= ahi[c];
+                if (!ov) continue;
+                // found in the cell of the boxes' common lower corner alone: where
+                // that is not the query's first cell, the entry's first cell decides
+                if ((cx[u] != clo[0] && cell_of(blo[u][0], h) != cx[u]) ||
+                    (cy[u] != clo[1] && cell_of(blo[u][1], h) != cy[u]) ||
+                    (cz[u] != clo[2] && cell_of(blo[u][2], h) != cz[u]))
+                    continue;
+                if (KIND == 0) {
+                    if (!pt_admissible(S, va0, S.trv[b], S.trv[S.n_tris + b], S.trv[2 * S.n_tris + b])) continue;
+                } else {
+                    if (!ee_admissible(S, va0, va1, S.ev[b], S.ev[S.n_edges + b])) continue;
+                }
+                if (COUNT && count < kQueryKeep) keep[count] = b;
+                if (!COUNT && !kept) {
+                    if (o + count < ocap) {
+                        out[o + count] = KIND;
+                        out[ocap + o + count] = a_id;
+                        out[2 * ocap + o + count] = b;
                     }
                 }
+                if (COUNT || !kept) ++count;
+            }
+        }
     }
     // the query's total over its lanes (every lane of the wavefront takes part)
     int tot = count;
@@ -519,18 +588,43 @@ __device__ void query_body(const Launch &L, int s, const SceneDev &S, int lb, in
             if (lane == 0) S.q_count[qidx] = tot;
         }
     } else {
-        __syncthreads();  // the lanes' writes are visible to lane 0
-        if (ok && lane == 0) {
-            int32_t *ob = out + 2 * ocap + o0;
-            int len = (int)min((int64_t)tot, ocap - o0);  // equal to tot once the list has grown
-            for (int i = 1; i < len; ++i) {
-                int key = ob[i];
-                int j = i - 1;
-                while (j >= 0 && ob[j] > key) {
-                    ob[j + 1] = ob[j];
-                    --j;
+        __syncthreads();  // the lanes' writes are visible to the query's other lanes
+        if (ok) {
+            const auto ob = out + 2 * ocap + o0;
+            const int len = (int)min((int64_t)tot, ocap - o0);  // equal to tot once the list has grown
+            constexpr int kRank = 8;  // pairs a lane places (a query has a few tens at most)
+            if (len <= kRank * kLanesQ) {
+                // every pair's place is the number of smaller ones
+                int key[kRank], place[kRank];
+#pragma unroll
+                for (int u = 0; u < kRank; ++u) {
+                    key[u] = u * kLanesQ + lane < len ? ob[u * kLanesQ + lane] : 0x7fffffff;
+                    place[u] = 0;
                 }
-                ob[j + 1] = key;
+                for (int u0 = 0; u0 * kLanesQ < len; ++u0) {
+                    int mine = 0x7fffffff;
+#pragma unroll
+                    for (int u = 0; u < kRank; ++u) mine = u == u0 ? key[u] : mine;
+#pragma unroll
+                    for (int j = 0; j < kLanesQ; ++j) {
+                        const int other = __shfl(mine, j, kLanesQ);
+#pragma unroll
+                        for (int u = 0; u < kRank; ++u) place[u] += other < key[u] ? 1 : 0;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kRank; ++u)
+                    if (u * kLanesQ + lane < len) ob[place[u]] = key[u];
+            } else if (lane == 0) {
+                for (int i = 1; i < len; ++i) {
+                    int key = ob[i];
+                    int j = i - 1;
+                    while (j >= 0 && ob[j] > key) {
+                        ob[j + 1] = ob[j];
+                        --j;
+                    }
+                    ob[j + 1] = key;
+                }
             }
         }
     }
@@ -569,25 +663,12 @@ __global__ void k_sw_filter(Launch L)
         }
         return;
     }
-    const double *abox, *bbox;
-    int ia, NA, NB;
-    if (type == 0) {
-        abox = S.pbox;
-        NA = S.n_pts;
-        ia = S.pt_idx[a];
-        bbox = S.tbox;
-        NB = S.n_tris;
-    } else {
-        abox = S.ebox;
-        NA = S.n_edges;
-        ia = a;
-        bbox = S.ebox;
-        NB = S.n_edges;
-    }
+    const double *abox = type == 0 ? S.pbox : S.ebox, *bbox = type == 0 ? S.tbox : S.ebox;
+    const int ia = type == 0 ? S.pt_idx[a] : a;
     bool ov = true;
     for (int c = 0; c < 3; ++c) {
-        double alo = abox[c * NA + ia], ahi = abox[(3 + c) * NA + ia];
-        double blo = bbox[c * NB + b], bhi = bbox[(3 + c) * NB + b];
+        double alo = abox[6 * (int64_t)ia + c], ahi = abox[6 * (int64_t)ia + 3 + c];
+        double blo = bbox[6 * (int64_t)b + c], bhi = bbox[6 * (int64_t)b + 3 + c];
         ov = ov && (alo <= bhi) && (blo <= ahi);
     }
     S.sw_flag[i] = ov ? 1 : 0;
