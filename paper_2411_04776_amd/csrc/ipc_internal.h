@@ -51,6 +51,7 @@ constexpr int kRowLong = 64;      // contact rows of more blocks take a wavefron
 constexpr int kRowSeg = 680;      // incidence entries of a contact row merged at a time (three columns each, sorted in LDS)
 constexpr int64_t kSpmvOneLaneRows = 65536;  // lists with at least this many rows: one thread per row
 constexpr int kScanTile = 1024;   // elements per scan tile
+constexpr int kScanOne = 32768;   // elements that one block scans in one launch
 constexpr int kQueryKeep = 4;     // pairs a query lane keeps from the count pass for the fill pass
 constexpr int kLanesQ = 8;        // broad-phase lanes per query primitive (they split its buckets' entries)
 constexpr int kMasLevels = 3;     // aggregate levels of the multilevel preconditioner
@@ -420,6 +421,9 @@ enum PhaseKind {
     kPhTeam0, kPhTeam1, kPhTeam2, kPhTeam3,  // resident PCG teams: narrow, wide, narrow of one workgroup, wide of one
     kPhOne,       // one block per scene
     kPhTilesT, kPhTilesE, kPhTilesQ, kPhTilesC, kPhTilesA,  // scan tiles
+    kPhZeroC,     // contact counts to clear, kBlock threads
+    kPhScan0,     // scans of one block, by ScanWhich (the tables' two in the first)
+    kPhScanLast = kPhScan0 + 5,
     kPhKinds
 };
 
@@ -543,7 +547,8 @@ void launch_hess_apply(Batch &b);  // y (S.q) = H v (S.dB)
 
 enum ScanWhich { kScanTri = 0, kScanEdge = 1, kScanQuery = 2, kScanContact = 3, kScanActive = 4, kScanSwFilter = 5 };
 // len[s] < 0: scene s sits out; query_sw selects the swept-candidate total
-void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, const std::vector<int64_t> &len, int query_sw = 0);
+void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, std::vector<int64_t> len, int query_sw = 0);
+void segmented_scan_tables(Batch &b, std::vector<int64_t> lt, std::vector<int64_t> le);
 
 void mark_dirty(Scene &s);
 // per-scene growth of the dynamic buffers (host; sets s.dev_dirty)

@@ -1594,15 +1594,13 @@ void run_broad_phase(Batch &b, int which)
             le[i] = int64_t(1) << S.ht_bits[1];
             lq[i] = (int64_t)S.n_pts + S.n_edges;
         }
-        // zero the buckets, count, scan, zero again, fill; then count queries
+        // zero the buckets, count, scan (which zeroes again), fill; then count queries
         std::vector<int32_t> zt = tiles_of(0), ze = tiles_of(1);
         for (size_t i = 0; i < ns; ++i) zt[i] += ze[i];
         b.set_phase(kPhTilesTE, zt);
         IPC_LAUNCH(b, k_zero_tables, kPhTilesTE, kBlock);
         IPC_LAUNCH(b, k_hash_insert_all<false>, kPhTE, kBlock);
-        segmented_scan(b, kScanTri, kPhTilesT, lt);
-        segmented_scan(b, kScanEdge, kPhTilesE, le);
-        IPC_LAUNCH(b, k_zero_tables, kPhTilesTE, kBlock);
+        segmented_scan_tables(b, lt, le);
         IPC_LAUNCH(b, k_hash_insert_all<true>, kPhTE, kBlock);
         IPC_LAUNCH(b, k_query_all<true>, kPhQAll, kBlock, which);
         segmented_scan(b, kScanQuery, kPhTilesQ, lq, which);
@@ -1760,12 +1758,10 @@ void launch_contact_incidence(Batch &b)
     }
     b.set_phase(kPhActT, na);
     b.set_phase(kPhEnt, ne);
-    b.set_phase(kPhTilesC, nz);
-    IPC_LAUNCH(b, k_zero, kPhTilesC, kBlock, 2);
+    b.set_phase(kPhZeroC, nz);
+    IPC_LAUNCH(b, k_zero, kPhZeroC, kBlock, 2);
     IPC_LAUNCH(b, k_incidence<false>, kPhActT, kBlock);
     segmented_scan(b, kScanContact, kPhTilesC, len);
-    b.set_phase(kPhTilesC, nz);
-    IPC_LAUNCH(b, k_zero, kPhTilesC, kBlock, 2);
     IPC_LAUNCH(b, k_incidence<true>, kPhActT, kBlock);
     IPC_LAUNCH(b, k_incidence_rank, kPhEnt, kBlock);
     std::vector<int32_t> nr(ns);

@@ -884,10 +884,14 @@ __global__ void k_gather_surface(int ns, const int32_t *__restrict__ ids, const 
 }
 
 // ---- segmented exclusive scan of per-scene int32 arrays ------------------------
-// Each scene's array is cut into tiles of kScanTile values (its own block
-// range); per-tile sums are scanned by one block per scene; then each tile
-// writes its exclusive prefix. out[len] and the scene's read-back slot get
-// the total.
+// An array of up to kScanOne values takes one block and one launch (k_scan_one:
+// 32 consecutive values a thread). A longer one is cut into tiles of kScanTile
+// values (its own block range); per-tile sums are scanned by one block per
+// scene; then each tile writes its exclusive prefix. out[len] and the scene's
+// read-back slot get the total. Counts that a second pass counts again (hash
+// buckets, contact entries) are cleared once they are read. A Newton iteration
+// of a small gel made 18 launches of 2 to 3 us for its scans and 2 to clear,
+// now 5.
 
 struct ScanSel {
     const int32_t *in;
@@ -907,9 +911,10 @@ __device__ __forceinline__ ScanSel scan_sel(const SceneDev &S, const SceneOut &O
     }
 }
 
+template <int NT = kBlock>
 __device__ int block_exclusive_scan(int v, int *total)
 {
-    __shared__ int sh[kBlock / 64];
+    __shared__ int sh[NT / 64];
     int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int incl = v;
     for (int o = 1; o < 64; o <<= 1) {
@@ -919,7 +924,7 @@ __device__ int block_exclusive_scan(int v, int *total)
     if (lane == 63) sh[w] = incl;
     __syncthreads();
     int woff = 0, tot = 0;
-    for (int k = 0; k < kBlock / 64; ++k) {
+    for (int k = 0; k < NT / 64; ++k) {
         if (k < w) woff += sh[k];
         tot += sh[k];
     }
@@ -944,6 +949,80 @@ __global__ void __launch_bounds__(kBlock) k_scan_tiles(Launch L, int which)
     if (threadIdx.x == 0) S.scan_tmp[lb] = tot;
 }
 
+__device__ __forceinline__ void scan_total(const SceneDev &S, SceneOut &O, int which, int query_sw, int total)
+{
+    const ScanSel sel = scan_sel(S, O, which);
+    sel.out[sel.len] = total;
+    if (which == kScanTri) O.ent_tri = total;
+    if (which == kScanEdge) O.ent_edge = total;
+    if (which == kScanQuery) {
+        if (query_sw)
+            O.n_sw = total;
+        else
+            O.n_cand = total;
+    }
+    if (which == kScanActive) O.n_act = total;
+    if (which == kScanSwFilter) O.n_cand = total;
+}
+
+// counts that the next pass counts again
+__device__ __forceinline__ bool scan_clears(int which)
+{
+    return which == kScanTri || which == kScanEdge || which == kScanContact;
+}
+
+constexpr int kScanWide = 1024;  // threads of k_scan_one
+constexpr int kScanRun = kScanOne / kScanWide / 4;  // its four-value reads a thread
+// Block lb of a scene scans array which + lb.
+__global__ void __launch_bounds__(kScanWide) k_scan_one(Launch L, int which, int query_sw)
+{
+    int lb, s = scene_of_block(L, lb);
+    const SceneDev &S = *L.sc[s];
+    which += lb;
+    const ScanSel sel = scan_sel(S, L.out[s], which);
+    const int len = (int)min(sel.len, (int64_t)kScanOne);
+    typedef int Int4 __attribute__((ext_vector_type(4)));
+    const int run = (len + 4 * kScanWide - 1) / (4 * kScanWide), first = 4 * run * (int)threadIdx.x;
+    const auto in = glob(const_cast<int32_t *>(sel.in));
+    const auto out = glob(sel.out);
+    Int4 v[kScanRun];
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < kScanRun; ++k) {
+        const int i = first + 4 * k;
+        v[k] = Int4{0, 0, 0, 0};
+        if (k < run && i + 4 <= len)
+            v[k] = *(gptr<const Int4>)(in + i);
+        else if (k < run)
+            for (int c = 0; c < 4; ++c)
+                if (i + c < len) v[k][c] = in[i + c];
+        sum += v[k][0] + v[k][1] + v[k][2] + v[k][3];
+    }
+    int tot;
+    int ex = block_exclusive_scan<kScanWide>(sum, &tot);
+    const bool clear = scan_clears(which);
+#pragma unroll
+    for (int k = 0; k < kScanRun; ++k) {
+        const int i = first + 4 * k;
+        Int4 o;
+        for (int c = 0; c < 4; ++c) {
+            o[c] = ex;
+            ex += v[k][c];
+        }
+        if (k < run && i + 4 <= len) {
+            *(gptr<Int4>)(out + i) = o;
+            if (clear) *(gptr<Int4>)(in + i) = Int4{0, 0, 0, 0};
+        } else if (k < run) {
+            for (int c = 0; c < 4; ++c)
+                if (i + c < len) {
+                    out[i + c] = o[c];
+                    if (clear) in[i + c] = 0;
+                }
+        }
+    }
+    if (threadIdx.x == 0) scan_total(S, L.out[s], which, query_sw, tot);
+}
+
 __global__ void __launch_bounds__(kBlock) k_scan_top(Launch one, Launch tiles, int which, int query_sw)
 {
     int lb, s = scene_of_block(one, lb);
@@ -958,21 +1037,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_top(Launch one, Launch tiles, i
         if (i < nt) S.scan_tmp[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) {
-        SceneOut &O = one.out[s];
-        ScanSel sel = scan_sel(S, O, which);
-        sel.out[sel.len] = carry;
-        if (which == kScanTri) O.ent_tri = carry;
-        if (which == kScanEdge) O.ent_edge = carry;
-        if (which == kScanQuery) {
-            if (query_sw)
-                O.n_sw = carry;
-            else
-                O.n_cand = carry;
-        }
-        if (which == kScanActive) O.n_act = carry;
-        if (which == kScanSwFilter) O.n_cand = carry;
-    }
+    if (threadIdx.x == 0) scan_total(S, one.out[s], which, query_sw, carry);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_apply(Launch L, int which)
@@ -990,7 +1055,10 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(Launch L, int which)
     int tot;
     int ex = block_exclusive_scan(sum, &tot) + S.scan_tmp[lb];
     for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < sel.len) sel.out[base + k] = ex;
+        if (base + k < sel.len) {
+            sel.out[base + k] = ex;
+            if (scan_clears(which)) const_cast<int32_t *>(sel.in)[base + k] = 0;
+        }
         ex += vals[k];
     }
 }
@@ -999,7 +1067,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(Launch L, int which)
 
 static bool mixed(const Batch &b) { return b.sc[0]->prm.precision == IPC_MIXED; }
 
-void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, const std::vector<int64_t> &len, int query_sw)
+static void long_scan(Batch &b, ScanWhich which, PhaseKind tiles, const std::vector<int64_t> &len, int query_sw)
 {
     size_t ns = b.sc.size();
     std::vector<int32_t> nt(ns), one(ns);
@@ -1012,6 +1080,39 @@ void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, const std::vecto
     IPC_LAUNCH(b, k_scan_tiles, tiles, kBlock, (int)which);
     IPC_LAUNCH(b, k_scan_top, kPhOne, kBlock, b.launch(tiles), (int)which, query_sw);
     IPC_LAUNCH(b, k_scan_apply, tiles, kBlock, (int)which);
+}
+
+void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, std::vector<int64_t> len, int query_sw)
+{
+    const PhaseKind ph = (PhaseKind)(kPhScan0 + which);
+    std::vector<int32_t> small(len.size(), 0);
+    bool rest = false;
+    for (size_t i = 0; i < len.size(); ++i) {
+        small[i] = len[i] >= 0 && len[i] <= kScanOne;
+        if (small[i]) len[i] = -1;
+        rest |= len[i] >= 0;
+    }
+    b.set_phase(ph, small);
+    IPC_LAUNCH(b, k_scan_one, ph, kScanWide, (int)which, query_sw);
+    if (rest) long_scan(b, which, tiles, len, query_sw);
+}
+
+// both hash tables' bucket counts
+void segmented_scan_tables(Batch &b, std::vector<int64_t> lt, std::vector<int64_t> le)
+{
+    std::vector<int32_t> small(lt.size(), 0);
+    bool rest = false;
+    for (size_t i = 0; i < lt.size(); ++i) {
+        small[i] = lt[i] >= 0 && std::max(lt[i], le[i]) <= kScanOne ? 2 : 0;
+        if (small[i]) lt[i] = le[i] = -1;
+        rest |= lt[i] >= 0;
+    }
+    static_assert(kScanEdge == kScanTri + 1, "block 1 of a scene scans the edges' counts");
+    b.set_phase(kPhScan0, small);
+    IPC_LAUNCH(b, k_scan_one, kPhScan0, kScanWide, (int)kScanTri, 0);
+    if (!rest) return;
+    long_scan(b, kScanTri, kPhTilesT, lt, 0);
+    long_scan(b, kScanEdge, kPhTilesE, le, 0);
 }
 
 void launch_begin_step(Batch &b) { IPC_LAUNCH(b, k_begin_step, kPhVert, kBlock); }
