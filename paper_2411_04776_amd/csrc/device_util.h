@@ -75,6 +75,13 @@ __device__ __forceinline__ double wave_first(double v)
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
+// orders a wavefront's LDS writes before its other lanes' reads
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Sum over the wavefront, the same value in every lane: the tree of
 // distances 32, 16, ..., 1.
 __device__ __forceinline__ double wave_sum(double v)

@@ -126,9 +126,12 @@ __device__ double dist_residual(const DistSpec &sp, const double *x, double r[3]
     double r0[3];
     for (int i = 0; i < 3; ++i)
         r0[i] = sp.c0[0] * x[i] + sp.c0[1] * x[3 + i] + sp.c0[2] * x[6 + i] + sp.c0[3] * x[9 + i];
-    for (int m = 0; m < sp.np; ++m)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
         for (int i = 0; i < 3; ++i)
-            u[m][i] = sp.D[m][0] * x[i] + sp.D[m][1] * x[3 + i] + sp.D[m][2] * x[6 + i] + sp.D[m][3] * x[9 + i];
+            u[m][i] = m < sp.np ? sp.D[m][0] * x[i] + sp.D[m][1] * x[3 + i] + sp.D[m][2] * x[6 + i] + sp.D[m][3] * x[9 + i]
+                                : 0.0;
     double beta[2] = {0.0, 0.0};
     if (sp.np == 1) {
         G[0] = d3(u[0], u[0]);
@@ -718,8 +721,11 @@ __device__ void dist_deriv_setup(const DistSpec &sp, const double *x, DistDeriv 
     double u[2][3], G[3];
     dd.np = sp.np;
     dd.s = dist_residual(sp, x, dd.r, dd.c, u, G);
+#pragma unroll
     for (int k = 0; k < 4; ++k)
+#pragma unroll
         for (int i = 0; i < 3; ++i)
+#pragma unroll
             for (int m = 0; m < 2; ++m)
                 dd.W[3 * k + i][m] = m < sp.np ? 2.0 * (sp.D[m][k] * dd.r[i] + dd.c[k] * u[m][i]) : 0.0;
     dd.S00 = dd.S01 = dd.S11 = 0.0;
@@ -734,15 +740,22 @@ __device__ void dist_deriv_setup(const DistSpec &sp, const double *x, DistDeriv 
     }
 }
 
+// The parts that lanes index by entry, in LDS (indexed in a thread's own arrays
+// they were scratch memory).
+struct PairLds {
+    double r[3], c[4], W[12][2], ea[3], eb[3];
+    int v[4], fixed[4];
+};
+
 // d2s/dx_p dx_q at fixed type
-__device__ __forceinline__ double dist_hess_entry(const DistDeriv &dd, int p, int q)
+__device__ __forceinline__ double dist_hess_entry(const DistDeriv &dd, const PairLds &pl, int p, int q)
 {
     int k = p / 3, i = p % 3, l = q / 3, j = q % 3;
-    double v = (i == j) ? 2.0 * dd.c[k] * dd.c[l] : 0.0;
+    double v = (i == j) ? 2.0 * pl.c[k] * pl.c[l] : 0.0;
     if (dd.np > 0) {
-        double acc = dd.W[p][0] * dd.S00 * dd.W[q][0];
+        double acc = pl.W[p][0] * dd.S00 * pl.W[q][0];
         if (dd.np == 2)
-            acc += dd.W[p][0] * dd.S01 * dd.W[q][1] + dd.W[p][1] * dd.S01 * dd.W[q][0] + dd.W[p][1] * dd.S11 * dd.W[q][1];
+            acc += pl.W[p][0] * dd.S01 * pl.W[q][1] + pl.W[p][1] * dd.S01 * pl.W[q][0] + pl.W[p][1] * dd.S11 * pl.W[q][1];
         v -= acc;
     }
     return v;
@@ -789,32 +802,39 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
             for (int b = a + 1; b < 5; ++b) off += U[ut5(a, b)] * U[ut5(a, b)];
         if (off <= 0.5e-36 * fro || off == 0.0) break;
 #pragma unroll
-        for (int p = 0; p < 5; ++p)
+        for (int r = 0; r < 5; ++r) {  // a round's two pairs are disjoint: their angles form beside each other
+            const int p[2] = {(r + 1) % 5, (r + 2) % 5}, q[2] = {(r + 4) % 5, (r + 3) % 5};
+            double c[2], sn[2];
 #pragma unroll
-            for (int q = p + 1; q < 5; ++q) {
-                const double apq = U[ut5(p, q)];
-                if (apq == 0.0) continue;
-                double theta = (U[ut5(q, q)] - U[ut5(p, p)]) / (2.0 * apq);
+            for (int k = 0; k < 2; ++k) {
+                const double apq = U[ut5(p[k], q[k])];
+                const double theta = (U[ut5(q[k], q[k])] - U[ut5(p[k], p[k])]) / (2.0 * apq);
                 double t = fabs(theta) > 1e150 ? 0.5 / theta
                                                 : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                double c = 1.0 / sqrt(t * t + 1.0), sn = t * c;
-                U[ut5(p, p)] -= t * apq;
-                U[ut5(q, q)] += t * apq;
-                U[ut5(p, q)] = 0.0;
+                t = apq == 0.0 ? 0.0 : t;
+                c[k] = 1.0 / sqrt(t * t + 1.0);
+                sn[k] = t * c[k];
+                U[ut5(p[k], p[k])] -= t * apq;
+                U[ut5(q[k], q[k])] += t * apq;
+                U[ut5(p[k], q[k])] = 0.0;
+            }
 #pragma unroll
-                for (int r = 0; r < 5; ++r) {
-                    if (r == p || r == q) continue;
-                    double arp = U[ut5(r, p)], arq = U[ut5(r, q)];
-                    U[ut5(r, p)] = c * arp - sn * arq;
-                    U[ut5(r, q)] = sn * arp + c * arq;
+            for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                for (int m = 0; m < 5; ++m) {
+                    if (m == p[k] || m == q[k]) continue;
+                    const double amp = U[ut5(m, p[k])], amq = U[ut5(m, q[k])];
+                    U[ut5(m, p[k])] = c[k] * amp - sn[k] * amq;
+                    U[ut5(m, q[k])] = sn[k] * amp + c[k] * amq;
                 }
 #pragma unroll
-                for (int r = 0; r < 5; ++r) {
-                    double vrp = V[r][p], vrq = V[r][q];
-                    V[r][p] = c * vrp - sn * vrq;
-                    V[r][q] = sn * vrp + c * vrq;
+                for (int m = 0; m < 5; ++m) {
+                    const double vmp = V[m][p[k]], vmq = V[m][q[k]];
+                    V[m][p[k]] = c[k] * vmp - sn[k] * vmq;
+                    V[m][q[k]] = sn[k] * vmp + c[k] * vmq;
                 }
             }
+        }
     }
 }
 
@@ -824,12 +844,15 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
 // 12x12 in LDS and negative eigenvalues are clamped to zero; matrices that are
 // already PSD are kept as assembled. Gauss-Newton form (S.barrier_gn): the
 // entries kappa w b''(d) gd_p gd_q, PSD and rank one as they are.
+// Bound by the chain of one pair: what lanes index by entry is in LDS, the
+// basis is orthogonalised with a component per lane, the 5x5 rotations run two
+// at a time and a 12x12 round is one pass over its 2 x 2 blocks: 241 -> 184 us
+// (130,600 vertices, mollified pairs among them), 40.7 -> 32.8 us (4,500).
 template <class R>
 __global__ void __launch_bounds__(64) k_barrier(Launch L)
 {
     __shared__ double A[144], V[144], A0[144];
-    __shared__ double rc[6], rs[6];
-    __shared__ int rp[6], rq[6];
+    __shared__ PairLds pl;
     int lbk, s = scene_of_block(L, lbk);
     const SceneDev &S = *L.sc[s];
     int64_t k = lbk;
@@ -858,7 +881,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
     // EE mollifier
     double w = 1.0, m1 = 0.0, m2 = 0.0;
     bool moll = false;
-    double ea[3], eb[3], aa = 0.0, bq = 0.0, ab = 0.0;
+    double ea[3] = {0.0, 0.0, 0.0}, eb[3] = {0.0, 0.0, 0.0}, aa = 0.0, bq = 0.0, ab = 0.0;
     if (type == 1) {
         double eps_x = kMollifier * edge_rest_sq[a] * edge_rest_sq[b];
         for (int i = 0; i < 3; ++i) {
@@ -877,26 +900,47 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
             ab = d3(ea, eb);
         }
     }
-    const double sa[4] = {-1, 1, 0, 0}, sb[4] = {0, 0, -1, 1};
-    auto gs_of = [&](int p) { return 2.0 * dd.c[p / 3] * dd.r[p % 3]; };
+    if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            pl.r[i] = dd.r[i];
+            pl.ea[i] = ea[i];
+            pl.eb[i] = eb[i];
+        }
+#pragma unroll
+        for (int k4 = 0; k4 < 4; ++k4) {
+            pl.c[k4] = dd.c[k4];
+            pl.v[k4] = v[k4];
+            pl.fixed[k4] = fixed[v[k4]];
+        }
+#pragma unroll
+        for (int p = 0; p < 12; ++p) {
+            pl.W[p][0] = dd.W[p][0];
+            pl.W[p][1] = dd.W[p][1];
+        }
+    }
+    __syncthreads();
+    auto sa = [](int k4) { return k4 == 0 ? -1.0 : k4 == 1 ? 1.0 : 0.0; };
+    auto sb = [](int k4) { return k4 == 2 ? -1.0 : k4 == 3 ? 1.0 : 0.0; };
+    auto gs_of = [&](int p) { return 2.0 * pl.c[p / 3] * pl.r[p % 3]; };
     auto gc_of = [&](int p) {
         int kk = p / 3, i = p % 3;
-        double ga = 2.0 * bq * ea[i] - 2.0 * ab * eb[i];
-        double gb = 2.0 * aa * eb[i] - 2.0 * ab * ea[i];
-        return sa[kk] * ga + sb[kk] * gb;
+        double ga = 2.0 * bq * pl.ea[i] - 2.0 * ab * pl.eb[i];
+        double gb = 2.0 * aa * pl.eb[i] - 2.0 * ab * pl.ea[i];
+        return sa(kk) * ga + sb(kk) * gb;
     };
     if (S.barrier_gn) {
         double wb2 = kappa * w * bb[2];
         if (lane < 12) {
             double gv = w * bb[1] * gs_of(lane) * inv2d;
             if (moll) gv += bb[0] * m1 * gc_of(lane);
-            act_g[(int64_t)lane * act_cap + k] = fixed[v[lane / 3]] ? R(0) : (R)(kappa * gv);
+            act_g[(int64_t)lane * act_cap + k] = pl.fixed[lane / 3] ? R(0) : (R)(kappa * gv);
         }
-        if (lane < 4) act_v[(int64_t)lane * act_cap + k] = v[lane];
+        if (lane < 4) act_v[(int64_t)lane * act_cap + k] = pl.v[lane];
         for (int e = lane; e < 144; e += 64) {
             int p = e / 12, q = e % 12;
             double val = wb2 * (gs_of(p) * inv2d) * (gs_of(q) * inv2d);
-            if (fixed[v[p / 3]] || fixed[v[q / 3]]) val = 0.0;
+            if (pl.fixed[p / 3] || pl.fixed[q / 3]) val = 0.0;
             act_H[144 * k + e] = (R)val;
         }
         return;
@@ -906,16 +950,16 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         int p = e / 12, q = e % 12;
         double gsp = gs_of(p), gsq = gs_of(q);
         double gdp = gsp * inv2d, gdq = gsq * inv2d;
-        double hd = dist_hess_entry(dd, p, q) * inv2d - gsp * gsq * inv4d3;
+        double hd = dist_hess_entry(dd, pl, p, q) * inv2d - gsp * gsq * inv4d3;
         double hv = w * (bb[2] * gdp * gdq + bb[1] * hd);
         if (moll) {
             int kp = p / 3, i = p % 3, kq = q / 3, j = q % 3;
             double dij = i == j ? 1.0 : 0.0;
-            double haa = 2.0 * bq * dij - 2.0 * eb[i] * eb[j];
-            double hbb = 2.0 * aa * dij - 2.0 * ea[i] * ea[j];
-            double hab = 4.0 * ea[i] * eb[j] - 2.0 * ab * dij - 2.0 * eb[i] * ea[j];
-            double hba = 4.0 * ea[j] * eb[i] - 2.0 * ab * dij - 2.0 * eb[j] * ea[i];
-            double hc = sa[kp] * sa[kq] * haa + sb[kp] * sb[kq] * hbb + sa[kp] * sb[kq] * hab + sb[kp] * sa[kq] * hba;
+            double haa = 2.0 * bq * dij - 2.0 * pl.eb[i] * pl.eb[j];
+            double hbb = 2.0 * aa * dij - 2.0 * pl.ea[i] * pl.ea[j];
+            double hab = 4.0 * pl.ea[i] * pl.eb[j] - 2.0 * ab * dij - 2.0 * pl.eb[i] * pl.ea[j];
+            double hba = 4.0 * pl.ea[j] * pl.eb[i] - 2.0 * ab * dij - 2.0 * pl.eb[j] * pl.ea[i];
+            double hc = sa(kp) * sa(kq) * haa + sb(kp) * sb(kq) * hbb + sa(kp) * sb(kq) * hab + sb(kp) * sa(kq) * hba;
             double gcp = gc_of(p), gcq = gc_of(q);
             hv += bb[0] * (m2 * gcp * gcq + m1 * hc);
             hv += bb[1] * m1 * (gcp * gdq + gdp * gcq);
@@ -929,7 +973,7 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         if (moll) gv += bb[0] * m1 * gc_of(lane);
         act_g[(int64_t)lane * act_cap + k] = (R)(kappa * gv);
     }
-    if (lane < 4) act_v[(int64_t)lane * act_cap + k] = v[lane];
+    if (lane < 4) act_v[(int64_t)lane * act_cap + k] = pl.v[lane];
     __syncthreads();
 
     if (!moll) {
@@ -940,36 +984,35 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         // restriction to an orthonormal basis Q of the span (k <= 5): a k x k
         // Jacobi instead of the 12 x 12 one.
         __shared__ double Q[5][12], AQ[12][5], M[5][5], MV[5][5];
-        __shared__ int kq;
-        if (lane == 0) {
-            double cn = sqrt(dd.c[0] * dd.c[0] + dd.c[1] * dd.c[1] + dd.c[2] * dd.c[2] + dd.c[3] * dd.c[3]);
-            for (int i = 0; i < 3; ++i)
-                for (int pp = 0; pp < 12; ++pp) Q[i][pp] = pp % 3 == i ? dd.c[pp / 3] / cn : 0.0;
-            int kk = 3;
-            for (int m = 0; m < dd.np; ++m) {
-                double w[12], n0 = 0.0;
-                for (int pp = 0; pp < 12; ++pp) {
-                    w[pp] = dd.W[pp][m];
-                    n0 += w[pp] * w[pp];
-                }
-                for (int pass = 0; pass < 2; ++pass)  // Gram-Schmidt, repeated once
-                    for (int aa2 = 0; aa2 < kk; ++aa2) {
-                        double dt = 0.0;
-                        for (int pp = 0; pp < 12; ++pp) dt += Q[aa2][pp] * w[pp];
-                        for (int pp = 0; pp < 12; ++pp) w[pp] -= dt * Q[aa2][pp];
-                    }
-                double n = 0.0;
-                for (int pp = 0; pp < 12; ++pp) n += w[pp] * w[pp];
-                if (n > 1e-24 * n0) {  // a direction already in the span adds none
-                    n = sqrt(n);
-                    for (int pp = 0; pp < 12; ++pp) Q[kk][pp] = w[pp] / n;
-                    ++kk;
-                }
+        // Gram-Schmidt with a component per lane (each row of 16 lanes holds a copy)
+        const int pp = lane & 15;
+        auto dot = [](double a, double c) { return lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(a * c)))); };
+        const double cn = sqrt(dd.c[0] * dd.c[0] + dd.c[1] * dd.c[1] + dd.c[2] * dd.c[2] + dd.c[3] * dd.c[3]);
+        const double qc = pp < 12 ? pl.c[pp / 3] / cn : 0.0;
+        double q[4] = {pp % 3 == 0 ? qc : 0.0, pp % 3 == 1 ? qc : 0.0, pp % 3 == 2 ? qc : 0.0, 0.0};
+        if (lane < 12)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) Q[i][pp] = q[i];
+        int kk = 3;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            if (m >= dd.np) break;
+            double wv = pp < 12 ? pl.W[pp][m] : 0.0;
+            const double n0 = dot(wv, wv);
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass)  // repeated once
+#pragma unroll
+                for (int a2 = 0; a2 < 3 + m; ++a2) wv -= dot(q[a2], wv) * q[a2];
+            const double n = dot(wv, wv);
+            if (n > 1e-24 * n0) {  // a direction already in the span adds none
+                const double qv = wv / sqrt(n);
+                if (lane < 12) Q[kk][pp] = qv;
+                if (m == 0) q[3] = qv;
+                ++kk;
             }
-            kq = kk;
         }
         __syncthreads();
-        const int kd = kq;
+        const int kd = kk;
         for (int t = lane; t < 12 * kd; t += 64) {  // A Q^T
             int i = t / kd, bq2 = t % kd;
             double acc = 0.0;
@@ -1025,10 +1068,10 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         for (int e = lane; e < 144; e += 64) {
             int i = e / 12, j = e % 12;
             double val = negr ? A[e] : A0[e];
-            if (fixed[v[i / 3]] || fixed[v[j / 3]]) val = 0.0;
+            if (pl.fixed[i / 3] || pl.fixed[j / 3]) val = 0.0;
             act_H[144 * k + e] = (R)val;
         }
-        if (lane < 12 && fixed[v[lane / 3]]) act_g[(int64_t)lane * act_cap + k] = R(0);
+        if (lane < 12 && pl.fixed[lane / 3]) act_g[(int64_t)lane * act_cap + k] = R(0);
         return;
     }
 
@@ -1047,52 +1090,54 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         off = __shfl(off, 0, 64);
         if (off <= 1e-36 * fro || off == 0.0) break;
         for (int round = 0; round < 11; ++round) {
-            if (lane < 6) {
-                int p, q;
-                rr_pair(round, lane, p, q);
-                double apq = A[p * 12 + q];
-                double c = 1.0, sn = 0.0;
-                if (apq != 0.0) {
-                    double theta = (A[q * 12 + q] - A[p * 12 + p]) / (2.0 * apq);
-                    double t = fabs(theta) > 1e150 ? 0.5 / theta
-                                                   : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                    c = 1.0 / sqrt(t * t + 1.0);
-                    sn = t * c;
+            // a lane takes the 2 x 2 block of two pairs (lanes 0 to 35), rows
+            // first, and two columns' entries of V; its column pair's angle
+            // beside the reads, its row pair's from that pair's lane
+            const int bi = lane / 6 % 6, bj = lane % 6;
+            int p, q, pr, qr;
+            rr_pair(round, bj, p, q);
+            rr_pair(round, bi, pr, qr);
+            const double a00 = A[pr * 12 + p], a01 = A[pr * 12 + q], a10 = A[qr * 12 + p], a11 = A[qr * 12 + q];
+            const double apq = A[p * 12 + q], app = A[p * 12 + p], aqq = A[q * 12 + q];
+            int vp[2], vq[2];
+            double vkp[2], vkq[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int task = min(lane + 64 * u, 71), col = task % 12;
+                rr_pair(round, task / 12, vp[u], vq[u]);
+                vp[u] += col * 12;
+                vq[u] += col * 12;
+                vkp[u] = V[vp[u]];
+                vkq[u] = V[vq[u]];
+            }
+            double c = 1.0, sn = 0.0;
+            if (apq != 0.0) {
+                double theta = (aqq - app) / (2.0 * apq);
+                double t = fabs(theta) > 1e150 ? 0.5 / theta
+                                               : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+                c = 1.0 / sqrt(t * t + 1.0);
+                sn = t * c;
+            }
+            const double cr = __shfl(c, bi, 64), sr = __shfl(sn, bi, 64);
+            const double cv[2] = {__shfl(c, lane / 12, 64), __shfl(c, 5, 64)};
+            const double sv[2] = {__shfl(sn, lane / 12, 64), __shfl(sn, 5, 64)};
+            wave_lds_fence();
+            if (lane < 36) {
+                const double b00 = cr * a00 - sr * a10, b01 = cr * a01 - sr * a11;
+                const double b10 = sr * a00 + cr * a10, b11 = sr * a01 + cr * a11;
+                const bool zero = bi == bj && sn != 0.0;
+                A[pr * 12 + p] = c * b00 - sn * b01;
+                A[pr * 12 + q] = zero ? 0.0 : sn * b00 + c * b01;
+                A[qr * 12 + p] = zero ? 0.0 : c * b10 - sn * b11;
+                A[qr * 12 + q] = sn * b10 + c * b11;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (lane + 64 * u < 72) {
+                    V[vp[u]] = cv[u] * vkp[u] - sv[u] * vkq[u];
+                    V[vq[u]] = sv[u] * vkp[u] + cv[u] * vkq[u];
                 }
-                rc[lane] = c;
-                rs[lane] = sn;
-                rp[lane] = p;
-                rq[lane] = q;
-            }
-            __syncthreads();
-            // rows p, q of A and columns p, q of V
-            for (int task = lane; task < 72; task += 64) {
-                int rr = task / 12, col = task % 12;
-                int p = rp[rr], q = rq[rr];
-                double c = rc[rr], sn = rs[rr];
-                double apk = A[p * 12 + col], aqk = A[q * 12 + col];
-                A[p * 12 + col] = c * apk - sn * aqk;
-                A[q * 12 + col] = sn * apk + c * aqk;
-                double vkp = V[col * 12 + p], vkq = V[col * 12 + q];
-                V[col * 12 + p] = c * vkp - sn * vkq;
-                V[col * 12 + q] = sn * vkp + c * vkq;
-            }
-            __syncthreads();
-            // columns p, q of A
-            for (int task = lane; task < 72; task += 64) {
-                int rr = task / 12, row = task % 12;
-                int p = rp[rr], q = rq[rr];
-                double c = rc[rr], sn = rs[rr];
-                double akp = A[row * 12 + p], akq = A[row * 12 + q];
-                A[row * 12 + p] = c * akp - sn * akq;
-                A[row * 12 + q] = sn * akp + c * akq;
-            }
-            __syncthreads();
-            if (lane < 6 && rs[lane] != 0.0) {
-                A[rp[lane] * 12 + rq[lane]] = 0.0;
-                A[rq[lane] * 12 + rp[lane]] = 0.0;
-            }
-            __syncthreads();
+            wave_lds_fence();
         }
     }
     bool neg = false;
@@ -1108,10 +1153,10 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
             }
         }
         // Dirichlet vertices drop out (their identity rows live in the elastic matrix)
-        if (fixed[v[i / 3]] || fixed[v[j / 3]]) val = 0.0;
+        if (pl.fixed[i / 3] || pl.fixed[j / 3]) val = 0.0;
         act_H[144 * k + e] = (R)val;
     }
-    if (lane < 12 && fixed[v[lane / 3]]) act_g[(int64_t)lane * act_cap + k] = R(0);
+    if (lane < 12 && pl.fixed[lane / 3]) act_g[(int64_t)lane * act_cap + k] = R(0);
 }
 
 

@@ -171,13 +171,6 @@ __device__ __forceinline__ void contact_dots(const double *dot, int n, double &t
     for (int h = (int)(threadIdx.x & (kWave - 1)); h < n; h += kWave) t += dot[h];
 }
 
-// orders a wavefront's LDS writes before its other lanes' reads
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Coarse part of the multilevel preconditioner for one group, by the kBlock
 // threads of its unit (t: thread of the unit), between block barriers:
 //   1. mas_restrict, all threads: each level-0 aggregate's sum of its members'
