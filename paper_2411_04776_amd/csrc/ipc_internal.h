@@ -61,9 +61,10 @@ constexpr int kMasTarget = 256;   // groups are packed with top-level aggregates
 
 constexpr int kTeamMax = 256;     // workgroups of a resident PCG team (one per CU)
 constexpr int kTeamSlots = 8;     // matrix slots of a row half kept in registers (two threads per row)
-constexpr int kTeamHalo = 4;      // column ids a thread keeps in registers
+constexpr int kTeamCompact = 4;   // layout of a resident team's workgroups that share CUs (the others: 0 to 3)
 constexpr int kTeamDyn = 158 * 1024;  // dynamic LDS of a team's workgroup (160 KB a CU, less its static arrays)
 constexpr int kChunkRows = 512;    // contact rows a resident team's member takes (more: the launched form)
+constexpr int kCompactRows = 256;  // and in the compact layout
 
 // kernels timed by the optional profiler
 enum ProfKernel {
@@ -418,7 +419,7 @@ enum PhaseKind {
     kPhMas,       // preconditioner diagonal: a wavefront per level-0 aggregate, a block per coarser one
     kPhMasG,      // preconditioner groups (a block each)
     kPhPcgB,      // PCG update: groups, then vertex blocks
-    kPhTeam0, kPhTeam1, kPhTeam2, kPhTeam3,  // resident PCG teams: narrow, wide, narrow of one workgroup, wide of one
+    kPhTeam0, kPhTeam1, kPhTeam2, kPhTeam3, kPhTeam4,  // resident PCG teams: narrow, wide, teams of one (two), compact
     kPhOne,       // one block per scene
     kPhTilesT, kPhTilesE, kPhTilesQ, kPhTilesC, kPhTilesA,  // scan tiles
     kPhZeroC,     // contact counts to clear, kBlock threads
@@ -537,7 +538,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap);
 // resident solves of the scenes with on[i] (host)
 void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on);
 // layouts of a team's workgroups: 0 narrow, 1 wide (twice the rows and units),
-// 2 and 3 teams of one (twice the units, twice both)
+// 2 and 3 teams of one (twice the units, twice both), kTeamCompact the narrow one's chunks in half the threads
 int team_rows(int variant, size_t real);
 int team_units(int variant, size_t real);
 size_t team_lds_bytes(int variant, int H, int A, size_t real);
@@ -558,5 +559,10 @@ void grow_active(Scene &s, int64_t need);
 void grow_friction(Scene &s, int64_t need);
 // barrier + friction pairs of a scene from its last read-back active-pair count
 inline int64_t pair_count(const Scene &s, const SceneOut &o) { return (int64_t)o.n_act + s.h.n_fric; }
+// contact rows of a chunk at most
+inline int64_t chunk_rows_bound(const Scene &s, const SceneOut &o)
+{
+    return std::min<int64_t>(4 * pair_count(s, o) / std::max(s.h.team_T, 1) + 1, s.h.n);
+}
 
 }  // namespace ipcg

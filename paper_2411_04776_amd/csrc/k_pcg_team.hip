@@ -20,11 +20,11 @@
 // and the chunk's contact rows, 16 lanes for 16 blocks, held in registers too
 // as far as the lanes go. Wide workgroups (one thread a row, two units a
 // thread) of 1,024 threads with half a row each had half the registers and
-// spilled: 36.7 us an iteration at 130,600 vertices, not 27.0.
+// spilled: 36.7 us an iteration at 130,600 vertices, not 25.3.
 //
 // Measured (us per iteration, launched form before -> this): 90 vertices FP64
 // 21 -> 5.4; 1,442 FP64 24 -> 8.7; 16,800 FP64 26 -> 11.1; 10,100 mixed 29 ->
-// 12.9; 130,600 mixed 59 -> 27.0.
+// 12.9; 130,600 mixed 59 -> 25.3.
 //
 // Exchange. Values that cross workgroups are written and read with
 // agent-scope accesses (they pass the non-coherent caches), so no cache is
@@ -186,12 +186,17 @@ __device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt
 // registers a thread): threads per matrix row (RT) and update units per 256
 // threads (V). Two threads a row hold eight blocks each (144 of 512 registers
 // in FP64, 72 of 256 in FP32), one thread a row eleven (198 and 99) and four
-// in LDS; a longer row's other blocks are read again in each iteration.
-constexpr int kTeamRT[4] = {2, 1, 2, 1}, kTeamV[4] = {1, 2, 2, 2};
-constexpr int team_lds_slots(int variant) { return kTeamRT[variant] == 1 ? 4 : 0; }
-constexpr int team_threads(size_t real) { return real == 8 ? 256 : 512; }
-int team_rows(int variant, size_t real) { return team_threads(real) / kTeamRT[variant]; }
-int team_units(int variant, size_t real) { return team_threads(real) / kBlock * kTeamV[variant]; }
+// in LDS, with its vertices' solution in memory; a longer row's other blocks are read again in each iteration. The
+// compact layout (FP32, 256 threads) has the narrow one's chunks, a thread a
+// row: two of its workgroups share a CU, for launches with more workgroups
+// than CUs, where the waits of one are the time of the other.
+constexpr int kTeamRT[5] = {2, 1, 2, 1, 1}, kTeamV[5] = {1, 2, 2, 2, 2};
+constexpr int team_lds_slots(int variant) { return kTeamRT[variant] == 2 ? 0 : variant == kTeamCompact ? 5 : 4; }
+int team_contact_rows(int variant) { return variant == kTeamCompact ? kCompactRows : kChunkRows; }
+constexpr int team_threads(int variant, size_t real) { return real == 8 ? 256 : variant == kTeamCompact ? 256 : 512; }
+constexpr int team_columns(int variant) { return variant == kTeamCompact ? 5 : 4; }  // column ids a thread keeps in registers
+int team_rows(int variant, size_t real) { return team_threads(variant, real) / kTeamRT[variant]; }
+int team_units(int variant, size_t real) { return team_threads(variant, real) / kBlock * kTeamV[variant]; }
 
 // A value the optimiser cannot trace back: addresses made from it are formed
 // where they are used. Hoisted out of the iteration loop they would take the
@@ -214,10 +219,10 @@ __host__ __device__ inline size_t team_unit_bytes(int A, size_t real)
 }
 size_t team_lds_bytes(int variant, int H, int A, size_t real)
 {
-    const size_t own = variant >= 2 ? 9 * (size_t)team_rows(variant, real) * real : 0;  // z, q and contact q of a team of one
+    const size_t own = variant == 2 || variant == 3 ? 9 * (size_t)team_rows(variant, real) * real : 0;  // z, q and contact q of a team of one
     return up8(3 * (size_t)H * real) + (size_t)team_units(variant, real) * team_unit_bytes(A, real) + own +
-           (size_t)team_lds_slots(variant) * 9 * team_threads(real) * real +
-           (8 + sizeof(CRow)) * (size_t)kChunkRows;
+           (size_t)team_lds_slots(variant) * 9 * team_threads(variant, real) * real +
+           (8 + sizeof(CRow)) * (size_t)team_contact_rows(variant);
 }
 
 // The chunks' partials of one sum, 16 bytes each: two 8-byte words that each
@@ -283,11 +288,13 @@ __device__ __forceinline__ bool team_join(PcgState *P, int T, int spin)
 }
 
 template <class R, int VARIANT>
-__global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
+__global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == kTeamCompact ? 2 : 1) k_pcg_team(Launch L)
 {
-    constexpr int NT = team_threads(sizeof(R)), NW = NT / kWave, G = NT / kBlock;  // G: threads' groups of 256
+    constexpr int NT = team_threads(VARIANT, sizeof(R)), NW = NT / kWave, G = NT / kBlock;  // G: threads' groups of 256
     constexpr int RT = kTeamRT[VARIANT], V = kTeamV[VARIANT], U = V * G, RPW = NT / RT;
-    constexpr bool SOLO = VARIANT >= 2;
+    constexpr bool SOLO = VARIANT == 2 || VARIANT == 3;
+    constexpr int HALO = team_columns(VARIANT), ROWS = VARIANT == kTeamCompact ? kCompactRows : kChunkRows;
+    constexpr bool PMEM = RT == 1 && !SOLO;  // p in memory: registers are short
     constexpr bool HOLD = RT == 2 || SOLO;  // contact blocks in registers
     constexpr int NS = RT == 2 ? kTeamSlots : 2 * kTeamSlots - 1;  // blocks on the chip,
     constexpr int RS = NS - team_lds_slots(VARIANT);               // the first RS of them in registers
@@ -316,7 +323,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
     // store the compiler would read it by vector loads, a memory round trip each
     const Partials P_dq(S.team_ll, T), P_rz(S.team_ll + 2 * (size_t)T, T);
     const XVec<R> Z(S.team_z, S.n), Q(S.team_q, S.n), C(S.c_q, S.n), DA(S.team_dA, S.n), DB(S.team_dB, S.n);
-    R *const Mi = as<R>(S.Minv), *const Bv = as<R>(S.bval);
+    R *const Mi = as<R>(S.Minv), *const Bv = as<R>(S.bval), *const Sol = as<R>(S.sol);
     uint16_t *const Lc = S.team_lcol;
     int32_t *const Hl = S.team_hlist;
     const auto Cv = glob((const R *)as<R>(S.c_val));
@@ -347,11 +354,11 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
         return x;
     };
     double *const cdot = reinterpret_cast<double *>(base_u + (size_t)U * ub);  // contact rows: their d.q
-    CRow *const clist = reinterpret_cast<CRow *>(cdot + kChunkRows);           // and places
-    R *const zl = reinterpret_cast<R *>(clist + kChunkRows);  // a team of one: z, q, contact q, [c * n + v] each
+    CRow *const clist = reinterpret_cast<CRow *>(cdot + ROWS);           // and places
+    R *const zl = reinterpret_cast<R *>(clist + ROWS);  // a team of one: z, q, contact q, [c * n + v] each
     R *const ql = zl + 3 * n, *const cl = ql + 3 * n;
     R *const ml = SOLO ? zl + 9 * (size_t)RPW : zl;  // matrix blocks: ml[(k * 9 + e) * NT + tid]
-    static_assert(sizeof(CRow) * kChunkRows % 8 == 0, "the arrays after the list are 8-byte aligned");
+    static_assert(sizeof(CRow) * ROWS % 8 == 0, "the arrays after the list are 8-byte aligned");
 
     // ---- this thread's matrix row or half row (slot k of the thread: part + RT * k of the row)
     const int part = RT == 2 ? tid & 1 : 0, row = w * RPW + tid / RT;
@@ -386,10 +393,10 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
     }
     // ---- this thread's columns of the chunk's list (a team of one: all vertices, in order)
     const int h0 = SOLO ? 0 : glob(S.team_hptr)[w], nh = SOLO ? n : glob(S.team_hptr)[w + 1] - h0;
-    int hv[kTeamHalo];
+    int hv[HALO];
     if constexpr (!SOLO)
 #pragma unroll
-        for (int j = 0; j < kTeamHalo; ++j) hv[j] = tid + j * NT < nh ? glob(Hl)[h0 + tid + j * NT] : 0;
+        for (int j = 0; j < HALO; ++j) hv[j] = tid + j * NT < nh ? glob(Hl)[h0 + tid + j * NT] : 0;
     for (int i = tid; i < 3 * H; i += NT) hd[i] = R(0);
 
     // ---- this thread's vertices, one of each of its update units
@@ -464,7 +471,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
         touched = live && part == 0 && glob(S.c_ptr)[row + 1] > glob(S.c_ptr)[row];
 #pragma unroll
         for (int v = 0; v < V; ++v) vtouched[v] = vid[v] >= 0 && glob(S.c_ptr)[vid[v] + 1] > glob(S.c_ptr)[vid[v]];
-        ncrow = chunk_contact_rows<NT, kChunkRows>(S, w, 0, clist, s_cnt);
+        ncrow = chunk_contact_rows<NT, ROWS>(S, w, 0, clist, s_cnt);
         if constexpr (HOLD) {
             const int item = tid / kRowTeam, u = tid % kRowTeam;
             int at = 0, h = 0;
@@ -579,7 +586,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
                 if (grp[v]) {
                     const Unit x = unit_at(v * G + ug);
                     mas_restrict<R>(na0[v], x.rm, x.ra, tu,
-                                    [q = rg0[v], rng = x.rng](int, int a, bool first) { return first ? q : rng[a]; });
+                                    [q = rg0[v], rng = x.rng](int, int a, bool first) { return !PMEM && first ? q : rng[a]; });
                 }
             __syncthreads();
 #pragma unroll
@@ -589,7 +596,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
                     rz[v] += mas_coarse<R>(
                         nl, na0[v], na1[v], na2[v], x.rm, x.ra, tu,
                         [q = rgc[v], rng = x.rng + na0[v], n1 = na1[v]](int l, int a, bool first) {
-                            return first ? q : rng[(l == 2 ? n1 : 0) + a];
+                            return !PMEM && first ? q : rng[(l == 2 ? n1 : 0) + a];
                         },
                         [&](int q, int k) { return x.Dl[9 * q + k]; });
                 }
@@ -657,7 +664,10 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
     for (int v = 0; v < V; ++v)
         if (vid[v] >= 0)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) r[v][c] = -g[3 * (int64_t)vid[v] + c];
+            for (int c = 0; c < 3; ++c) {
+                r[v][c] = -g[3 * (int64_t)vid[v] + c];
+                if constexpr (PMEM) at(Sol, 3u * (uint32_t)vid[v])[c] = R(0);
+            }
     load_inverse();
     precondition(1u);
 
@@ -668,7 +678,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
         for (int k = 0; k < (NS + 1) / 2; ++k) lc[k] = here(lc[k]);
         if constexpr (!SOLO)
 #pragma unroll
-            for (int j = 0; j < kTeamHalo; ++j) hv[j] = here(hv[j]);
+            for (int j = 0; j < HALO; ++j) hv[j] = here(hv[j]);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             vid[v] = here(vid[v]);
@@ -681,11 +691,11 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
         lane = here(lane);
         const uint32_t tag = (uint32_t)it & 0xffffu;
         // z at the chunk's columns (and at the held contact block's)
-        typename XVec<R>::Raw zr[kTeamHalo], zc, zo;
+        typename XVec<R>::Raw zr[HALO], zc, zo;
         auto columns = [&]() {
             if constexpr (!SOLO) {
 #pragma unroll
-                for (int j = 0; j < kTeamHalo; ++j)
+                for (int j = 0; j < HALO; ++j)
                     if (j * NT < nh) Z.load(hv[j], zr[j]);  // uniform; ids past the list read vertex 0
                 if (HOLD && cteam) {
                     Z.load(ccol, zc);
@@ -694,7 +704,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
                 for (int k = 0;; ++k) {  // each until it is this iteration's
                     bool ok = true;
 #pragma unroll
-                    for (int j = 0; j < kTeamHalo; ++j)
+                    for (int j = 0; j < HALO; ++j)
                         if (j * NT < nh && !XVec<R>::is(zr[j], tag)) {
                             Z.load(hv[j], zr[j]);
                             ok = false;
@@ -752,13 +762,13 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < kTeamHalo; ++j)
+            for (int j = 0; j < HALO; ++j)
                 if (tid + j * NT < nh) {
                     R zv[3];
                     XVec<R>::get(zr[j], zv);
                     advance(tid + j * NT, zv);
                 }
-            for (int i = tid + kTeamHalo * NT; i < nh; i += NT) {
+            for (int i = tid + HALO * NT; i < nh; i += NT) {
                 R zv[3];
                 ok &= Z.wait(glob(Hl)[h0 + i], tag, zv);
                 advance(i, zv);
@@ -1007,7 +1017,12 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
                 }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    p[v][c] = p[v][c] + alpha * d[v][c];
+                    if constexpr (PMEM) {
+                        const auto to = at(Sol, 3u * (uint32_t)vid[v]) + c;
+                        *to = *to + alpha * d[v][c];
+                    } else {
+                        p[v][c] = p[v][c] + alpha * d[v][c];
+                    }
                     r[v][c] = r[v][c] - alpha * qv[c];
                 }
             }
@@ -1023,7 +1038,12 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
     for (int v = 0; v < V; ++v)
         if (vid[v] >= 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) as<R>(S.sol)[3 * (int64_t)vid[v] + c] = p[v][c];
+            for (int c = 0; c < 3; ++c) {
+                if constexpr (PMEM)
+                    p[v][c] = at(Sol, 3u * (uint32_t)vid[v])[c];
+                else
+                    at(Sol, 3u * (uint32_t)vid[v])[c] = p[v][c];
+            }
             if (!S.fixed[vid[v]])
                 pm = fmax(pm, fmax(fabs((double)p[v][0]), fmax(fabs((double)p[v][1]), fabs((double)p[v][2]))));
         }
@@ -1043,7 +1063,7 @@ __global__ void __launch_bounds__(team_threads(sizeof(R))) k_pcg_team(Launch L)
 template <class R>
 static void launch_variant(Batch &b, int variant, size_t lds)
 {
-    constexpr int N = team_threads(sizeof(R));
+    const int N = team_threads(variant, sizeof(R));
     const PhaseKind ph = (PhaseKind)(kPhTeam0 + variant);
     const int nb = b.blocks(ph);
     if (nb == 0) return;
@@ -1053,7 +1073,9 @@ static void launch_variant(Batch &b, int variant, size_t lds)
     case 0: hipLaunchKernelGGL((k_pcg_team<R, 0>), dim3(nb), dim3(N), lds, b.stream, l); break;
     case 1: hipLaunchKernelGGL((k_pcg_team<R, 1>), dim3(nb), dim3(N), lds, b.stream, l); break;
     case 2: hipLaunchKernelGGL((k_pcg_team<R, 2>), dim3(nb), dim3(N), lds, b.stream, l); break;
-    default: hipLaunchKernelGGL((k_pcg_team<R, 3>), dim3(nb), dim3(N), lds, b.stream, l); break;
+    case 3: hipLaunchKernelGGL((k_pcg_team<R, 3>), dim3(nb), dim3(N), lds, b.stream, l); break;
+    default:
+        if constexpr (sizeof(R) == 4) hipLaunchKernelGGL((k_pcg_team<R, kTeamCompact>), dim3(nb), dim3(N), lds, b.stream, l);
     }
     IPC_HIP(hipGetLastError());
 }
@@ -1063,12 +1085,24 @@ void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on)
     const size_t ns = b.sc.size();
     const bool mx = b.sc[0]->prm.precision == IPC_MIXED;
     const size_t rs = mx ? sizeof(float) : sizeof(double);
-    for (int v = 0; v < 4; ++v) {
+    // narrow teams that fill the CUs more than once: two workgroups a CU (a list
+    // of 128 gels 84.8 -> 77.0 ms: 5.2 -> 4.0 ms a launch of 2,000 workgroups)
+    int64_t narrow = 0;
+    for (size_t i = 0; i < ns; ++i)
+        if (on[i] && b.sc[i]->h.team_variant == 0) narrow += b.sc[i]->h.team_T;
+    auto variant = [&](size_t i) {
+        const SceneDev &h = b.sc[i]->h;
+        const bool compact = mx && h.team_variant == 0 && narrow > kTeamMax &&
+                             chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kCompactRows &&
+                             team_lds_bytes(kTeamCompact, h.team_H, h.team_A, rs) <= kTeamDyn / 2;
+        return compact ? kTeamCompact : h.team_variant;
+    };
+    for (int v = 0; v <= kTeamCompact; ++v) {
         std::vector<int32_t> nb(ns, 0);
         size_t lds = 0;
         for (size_t i = 0; i < ns; ++i) {
             const SceneDev &h = b.sc[i]->h;
-            if (!on[i] || h.team_variant != v) continue;
+            if (!on[i] || variant(i) != v) continue;
             nb[i] = h.team_T;
             lds = std::max(lds, team_lds_bytes(v, h.team_H, h.team_A, rs));
         }
@@ -1086,6 +1120,8 @@ static void raise_lds()
     for (const void *f : {(const void *)k_pcg_team<R, 0>, (const void *)k_pcg_team<R, 1>, (const void *)k_pcg_team<R, 2>,
                           (const void *)k_pcg_team<R, 3>})
         IPC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kTeamDyn));
+    if constexpr (sizeof(R) == 4)
+        IPC_HIP(hipFuncSetAttribute((const void *)k_pcg_team<R, kTeamCompact>, hipFuncAttributeMaxDynamicSharedMemorySize, kTeamDyn));
 }
 
 void team_prepare_device()

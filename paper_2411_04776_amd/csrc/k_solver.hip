@@ -1223,8 +1223,7 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
     for (size_t i = 0; i < ns; ++i) {
         if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
         const SceneDev &h = b.sc[i]->h;
-        const int64_t crows = std::min<int64_t>(4 * pair_count(*b.sc[i], b.h_out[i]) / std::max(h.team_T, 1) + 1, h.n);
-        const bool t = h.team_fit && b.sc[i]->tune.team && crows <= kChunkRows;
+        const bool t = h.team_fit && b.sc[i]->tune.team && chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kChunkRows;
         (t ? team : rest)[i] = 1;
         (t ? any_team : any_rest) = true;
     }
