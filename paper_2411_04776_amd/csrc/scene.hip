@@ -2218,14 +2218,17 @@ int32_t ipc_read_surface(const ipc_scene *cs, double *xyz, int64_t cap, int32_t 
     bool expect = false;
     if (!s->busy.compare_exchange_strong(expect, true)) return IPC_E_BUSY;
     int32_t rc = guarded([&]() -> int32_t {
+        // on the scene's own stream one wait at the end is enough (three took 10
+        // of the 57 us of a tactile image); another stream waits for the scene first
         hipStream_t strm = stream ? (hipStream_t)stream : s->stream;
-        IPC_HIP(hipStreamSynchronize(s->stream));
+        if (strm != s->stream) IPC_HIP(hipStreamSynchronize(s->stream));
         if (xyz) {
             double *dst = where == IPC_DEVICE ? xyz : s->ysurf;
             launch_gather_surface(*s, dst, strm);
-            if (where == IPC_HOST)
+            if (where == IPC_HOST) {
                 IPC_HIP(hipMemcpyAsync(xyz, s->ysurf, sizeof(double) * need, hipMemcpyDeviceToHost, strm));
-            IPC_HIP(hipStreamSynchronize(strm));
+                IPC_HIP(hipStreamSynchronize(strm));  // before anything that can fail: the caller's memory
+            }
         }
         if (obj_pos) {
             Batch &b = solo(*s);
@@ -2234,6 +2237,7 @@ int32_t ipc_read_surface(const ipc_scene *cs, double *xyz, int64_t cap, int32_t 
             b.read_out();
             for (int c = 0; c < 3; ++c) obj_pos[c] = b.h_out[0].obj[c];
         }
+        if (strm != s->stream || !obj_pos) IPC_HIP(hipStreamSynchronize(strm));
         return IPC_OK;
     });
     s->busy = false;
@@ -2260,7 +2264,7 @@ int32_t ipc_height_map(const ipc_scene *cs, const ipc_height_map_spec *spec, dou
     if (!s->busy.compare_exchange_strong(expect, true)) return IPC_E_BUSY;
     int32_t rc = guarded([&]() -> int32_t {
         hipStream_t strm = stream ? (hipStream_t)stream : s->stream;
-        IPC_HIP(hipStreamSynchronize(s->stream));
+        if (strm != s->stream) IPC_HIP(hipStreamSynchronize(s->stream));
         if (s->hm_cap < np) {
             Staged st(*s);
             auto *nk = st.get<unsigned long long>((size_t)np);
@@ -2340,7 +2344,7 @@ int32_t ipc_height_map_noalloc(const ipc_scene *cs, const ipc_height_map_spec *s
     int32_t rc = guarded([&]() -> int32_t {
         hipStream_t strm = stream ? (hipStream_t)stream : s->stream;
         unsigned long long *key = scratch_address();
-        IPC_HIP(hipStreamSynchronize(s->stream));
+        if (strm != s->stream) IPC_HIP(hipStreamSynchronize(s->stream));
         HeightSpec hs{spec->x0, spec->y0, spec->dx, spec->dy, spec->z_ref, spec->nx, spec->ny};
         // host output: heights overwrite their own keys (one thread per pixel
         // reads its key, then writes its height to the same 8 bytes)
