@@ -51,7 +51,8 @@ constexpr int kRowLong = 64;      // contact rows of more blocks take a wavefron
 constexpr int kRowSeg = 680;      // incidence entries of a contact row merged at a time (three columns each, sorted in LDS)
 constexpr int64_t kSpmvOneLaneRows = 65536;  // lists with at least this many rows: one thread per row
 constexpr int kScanTile = 1024;   // elements per scan tile
-constexpr int kScanOne = 32768;   // elements that one block scans in one launch
+constexpr int kScanOne = 32768;   // elements that one block scans at a time,
+constexpr int kScanMost = 131072; // and in one launch (four rounds of 4 us; three launches with their gaps take 20)
 constexpr int kQueryKeep = 4;     // pairs a query lane keeps from the count pass for the fill pass
 constexpr int kLanesQ = 8;        // broad-phase lanes per query primitive (they split its buckets' entries)
 constexpr int kMasLevels = 3;     // aggregate levels of the multilevel preconditioner
@@ -98,6 +99,7 @@ struct SceneOut {
     int32_t ent_tri, ent_edge;  // hash entries needed
     int32_t bad;          // non-finite positions seen by the broad phase
     int32_t infeasible;   // energy: a tet with J <= 0 or a pair with d <= 0
+    int32_t inf_seen;     // the same while the energy is formed; 0 between energies
     int32_t pcg_done, pcg_iters;
     int32_t n_crow;       // matrix rows with contact entries
     int32_t n_pair;       // pairs in the active arrays: n_act barrier pairs, then the friction pairs

@@ -293,17 +293,6 @@ __device__ __forceinline__ uint32_t cell_hash(int ix, int iy, int iz, int body, 
 // a non-finite or absurd position, which is flagged and skipped.
 constexpr int kMaxSpan = 4096;
 
-// zero a per-scene int array: 0/1 hash bucket counts, 2 contact counts
-__global__ void k_zero(Launch L, int which)
-{
-    int lb, s = scene_of_block(L, lb);
-    const SceneDev &S = *L.sc[s];
-    int32_t *a = which == 0 ? S.ht_count[0] : (which == 1 ? S.ht_count[1] : S.c_cnt);
-    int64_t len = which == 2 ? (int64_t)S.n + 1 : ((int64_t)1 << S.ht_bits[which]) + 1;
-    for (int64_t i = (int64_t)lb * blockDim.x + threadIdx.x; i < len; i += (int64_t)blocks_of(L, s) * blockDim.x)
-        a[i] = 0;
-}
-
 // zero both hash tables' bucket counts in one launch (table 0's blocks first)
 __global__ void k_zero_tables(Launch L)
 {
@@ -1160,6 +1149,20 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
 }
 
 
+// The pair and row counts of the incidence passes that follow, and their
+// entries' counts to zero.
+__global__ void __launch_bounds__(kBlock) k_contact_zero(Launch L)
+{
+    int lb, s = scene_of_block(L, lb);
+    const SceneDev &S = *L.sc[s];
+    const int i = lb * kBlock + (int)threadIdx.x;
+    if (i <= S.n) S.c_cnt[i] = 0;
+    if (i == 0) {
+        L.out[s].n_pair = L.out[s].n_act + S.n_fric;
+        L.out[s].n_crow = L.out[s].n_cblk = 0;
+    }
+}
+
 // Incidence lists of the active pairs' free vertices: a counting pass, a scan
 // into c_ptr, then a fill in arbitrary order (c_tmp) and a rank pass that
 // puts every row's entries in pair order and lists the rows.
@@ -1419,16 +1422,6 @@ __global__ void __launch_bounds__(kBlock) k_friction(Launch L)
                 }
 }
 
-__global__ void k_set_npair(Launch one)
-{
-    int lb, s = scene_of_block(one, lb);
-    const SceneDev &S = *one.sc[s];
-    if (threadIdx.x == 0) {
-        one.out[s].n_pair = one.out[s].n_act + S.n_fric;
-        one.out[s].n_crow = one.out[s].n_cblk = 0;  // counted by the incidence passes that follow
-    }
-}
-
 // friction energy partials, after the body and barrier partials
 __global__ void __launch_bounds__(kBlock) k_energy_fric(Launch L, Launch body, Launch cont, int trial)
 {
@@ -1542,7 +1535,7 @@ __global__ void __launch_bounds__(kBlock) k_energy_contact(Launch L, Launch body
         gather12(x, v, x12);
         double d = pair_distance(type, x12);
         if (!(d > 0.0)) {
-            atomicOr(&L.out[s].infeasible, 1);
+            atomicOr(&L.out[s].inf_seen, 1);
         } else if (d < S.dhat) {
             double bb[3];
             barrier3(d, S.dhat, bb);
@@ -1567,12 +1560,6 @@ __global__ void __launch_bounds__(kBlock) k_energy_contact(Launch L, Launch body
     }
 }
 
-__global__ void k_clear_infeasible(Launch one)
-{
-    int lb, s = scene_of_block(one, lb);
-    if (threadIdx.x == 0) one.out[s].infeasible = 0;
-}
-
 // final compensated sum over the body and contact partials of one scene
 __global__ void k_energy_final(Launch one, Launch body, Launch cont, Launch fric)
 {
@@ -1585,7 +1572,11 @@ __global__ void k_energy_final(Launch one, Launch body, Launch cont, Launch fric
         acc = csum_add(acc, t);
     }
     acc = block_csum(acc);
-    if (threadIdx.x == 0) one.out[s].energy = acc.s + acc.c;
+    if (threadIdx.x == 0) {
+        one.out[s].energy = acc.s + acc.c;
+        one.out[s].infeasible = one.out[s].inf_seen;
+        one.out[s].inf_seen = 0;  // for the next energy
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1804,7 +1795,7 @@ void launch_contact_incidence(Batch &b)
     b.set_phase(kPhActT, na);
     b.set_phase(kPhEnt, ne);
     b.set_phase(kPhZeroC, nz);
-    IPC_LAUNCH(b, k_zero, kPhZeroC, kBlock, 2);
+    IPC_LAUNCH(b, k_contact_zero, kPhZeroC, kBlock);
     IPC_LAUNCH(b, k_incidence<false>, kPhActT, kBlock);
     segmented_scan(b, kScanContact, kPhTilesC, len);
     IPC_LAUNCH(b, k_incidence<true>, kPhActT, kBlock);
@@ -1836,8 +1827,6 @@ void launch_friction(Batch &b)
         IPC_LAUNCH(b, k_friction<float>, kPhFric, kBlock);
     else
         IPC_LAUNCH(b, k_friction<double>, kPhFric, kBlock);
-    one_per_active(b, kPhVert);
-    IPC_LAUNCH(b, k_set_npair, kPhOne, 64);
 }
 
 void run_ccd(Batch &b)
@@ -1875,8 +1864,6 @@ void run_energy(Batch &b, bool trial)
     b.set_phase(kPhCandSw, nb);
     b.set_phase(kPhBody, per_scene(b, kPhVert, [](const Scene &s) { return nblocks((int64_t)s.h.m + s.h.n); }));
     b.set_phase(kPhFric, per_scene(b, kPhVert, [](const Scene &s) { return nblocks(s.h.n_fric); }));
-    one_per_active(b, kPhVert);
-    IPC_LAUNCH(b, k_clear_infeasible, kPhOne, 64);
     launch_energy_body(b, trial);
     IPC_LAUNCH(b, k_energy_contact, kPhCandSw, kBlock, b.launch(kPhBody), (int)trial);
     IPC_LAUNCH(b, k_energy_fric, kPhFric, kBlock, b.launch(kPhBody), b.launch(kPhCandSw), (int)trial);

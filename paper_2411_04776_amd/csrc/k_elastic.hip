@@ -455,7 +455,7 @@ __global__ void k_rest_mass(Launch L)
 
 // Elastic + inertia + target terms of the incremental potential (FP64), per
 // item, into compensated block partials S.red[2 lb], S.red[2 lb + 1]. Items:
-// tets, then vertices. out.infeasible is set if a tet has J <= 0.
+// tets, then vertices. out.inf_seen is set if a tet has J <= 0.
 __global__ void __launch_bounds__(kBlock) k_energy_body(Launch L, int trial)
 {
     int lb, s = scene_of_block(L, lb);
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(kBlock) k_energy_body(Launch L, int trial)
         tet_F<double>(S, x, e, F, q, Fd);
         double J = det3(Fd);
         if (!(J > 0.0)) {
-            atomicOr(&L.out[s].infeasible, 1);
+            atomicOr(&L.out[s].inf_seen, 1);
         } else {
             double tr = 0.0;
             for (int k = 0; k < 9; ++k) tr += Fd[k] * Fd[k];
