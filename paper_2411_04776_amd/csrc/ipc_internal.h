@@ -51,8 +51,7 @@ constexpr int kRowLong = 64;      // contact rows of more blocks take a wavefron
 constexpr int kRowSeg = 680;      // incidence entries of a contact row merged at a time (three columns each, sorted in LDS)
 constexpr int64_t kSpmvOneLaneRows = 65536;  // lists with at least this many rows: one thread per row
 constexpr int kScanTile = 1024;   // elements per scan tile
-constexpr int kScanOne = 32768;   // elements that one block scans at a time,
-constexpr int kScanMost = 131072; // and in one launch (four rounds of 4 us; three launches with their gaps take 20)
+constexpr int kScanOne = 32768;   // elements that one block scans in one launch (4 to 6 us; 131,072 in rounds took 40, three launches 14)
 constexpr int kQueryKeep = 4;     // pairs a query lane keeps from the count pass for the fill pass
 constexpr int kLanesQ = 8;        // broad-phase lanes per query primitive (they split its buckets' entries)
 constexpr int kMasLevels = 3;     // aggregate levels of the multilevel preconditioner

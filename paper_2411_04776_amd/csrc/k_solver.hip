@@ -884,8 +884,8 @@ __global__ void k_gather_surface(int ns, const int32_t *__restrict__ ids, const 
 }
 
 // ---- segmented exclusive scan of per-scene int32 arrays ------------------------
-// An array of up to kScanMost values takes one block and one launch (k_scan_one:
-// 32 consecutive values a thread, kScanOne values at a time). A longer one is cut into tiles of kScanTile
+// An array of up to kScanOne values takes one block and one launch (k_scan_one:
+// 32 consecutive values a thread). A longer one is cut into tiles of kScanTile
 // values (its own block range); per-tile sums are scanned by one block per
 // scene; then each tile writes its exclusive prefix. out[len] and the scene's
 // read-back slot get the total. Counts that a second pass counts again (hash
@@ -980,51 +980,47 @@ __global__ void __launch_bounds__(kScanWide) k_scan_one(Launch L, int which, int
     const SceneDev &S = *L.sc[s];
     which += lb;
     const ScanSel sel = scan_sel(S, L.out[s], which);
+    const int len = (int)min(sel.len, (int64_t)kScanOne);
     typedef int Int4 __attribute__((ext_vector_type(4)));
+    const int run = (len + 4 * kScanWide - 1) / (4 * kScanWide), first = 4 * run * (int)threadIdx.x;
     const auto in = glob(const_cast<int32_t *>(sel.in));
     const auto out = glob(sel.out);
+    Int4 v[kScanRun];
+    int sum = 0;
+#pragma unroll
+    for (int k = 0; k < kScanRun; ++k) {
+        const int i = first + 4 * k;
+        v[k] = Int4{0, 0, 0, 0};
+        if (k < run && i + 4 <= len)
+            v[k] = *(gptr<const Int4>)(in + i);
+        else if (k < run)
+            for (int c = 0; c < 4; ++c)
+                if (i + c < len) v[k][c] = in[i + c];
+        sum += v[k][0] + v[k][1] + v[k][2] + v[k][3];
+    }
+    int tot;
+    int ex = block_exclusive_scan<kScanWide>(sum, &tot);
     const bool clear = scan_clears(which);
-    int carry = 0;
-    for (int64_t base = 0; base == 0 || base < sel.len; base += kScanOne) {
-        const int len = (int)min(sel.len - base, (int64_t)kScanOne);
-        const int run = (len + 4 * kScanWide - 1) / (4 * kScanWide), first = 4 * run * (int)threadIdx.x;
-        Int4 v[kScanRun];
-        int sum = 0;
 #pragma unroll
-        for (int k = 0; k < kScanRun; ++k) {
-            const int i = first + 4 * k;
-            v[k] = Int4{0, 0, 0, 0};
-            if (k < run && i + 4 <= len)
-                v[k] = *(gptr<const Int4>)(in + base + i);
-            else if (k < run)
-                for (int c = 0; c < 4; ++c)
-                    if (i + c < len) v[k][c] = in[base + i + c];
-            sum += v[k][0] + v[k][1] + v[k][2] + v[k][3];
+    for (int k = 0; k < kScanRun; ++k) {
+        const int i = first + 4 * k;
+        Int4 o;
+        for (int c = 0; c < 4; ++c) {
+            o[c] = ex;
+            ex += v[k][c];
         }
-        int tot;
-        int ex = carry + block_exclusive_scan<kScanWide>(sum, &tot);
-        carry += tot;
-#pragma unroll
-        for (int k = 0; k < kScanRun; ++k) {
-            const int i = first + 4 * k;
-            Int4 o;
-            for (int c = 0; c < 4; ++c) {
-                o[c] = ex;
-                ex += v[k][c];
-            }
-            if (k < run && i + 4 <= len) {
-                *(gptr<Int4>)(out + base + i) = o;
-                if (clear) *(gptr<Int4>)(in + base + i) = Int4{0, 0, 0, 0};
-            } else if (k < run) {
-                for (int c = 0; c < 4; ++c)
-                    if (i + c < len) {
-                        out[base + i + c] = o[c];
-                        if (clear) in[base + i + c] = 0;
-                    }
-            }
+        if (k < run && i + 4 <= len) {
+            *(gptr<Int4>)(out + i) = o;
+            if (clear) *(gptr<Int4>)(in + i) = Int4{0, 0, 0, 0};
+        } else if (k < run) {
+            for (int c = 0; c < 4; ++c)
+                if (i + c < len) {
+                    out[i + c] = o[c];
+                    if (clear) in[i + c] = 0;
+                }
         }
     }
-    if (threadIdx.x == 0) scan_total(S, L.out[s], which, query_sw, carry);
+    if (threadIdx.x == 0) scan_total(S, L.out[s], which, query_sw, tot);
 }
 
 __global__ void __launch_bounds__(kBlock) k_scan_top(Launch one, Launch tiles, int which, int query_sw)
@@ -1092,7 +1088,7 @@ void segmented_scan(Batch &b, ScanWhich which, PhaseKind tiles, std::vector<int6
     std::vector<int32_t> small(len.size(), 0);
     bool rest = false;
     for (size_t i = 0; i < len.size(); ++i) {
-        small[i] = len[i] >= 0 && len[i] <= kScanMost;
+        small[i] = len[i] >= 0 && len[i] <= kScanOne;
         if (small[i]) len[i] = -1;
         rest |= len[i] >= 0;
     }
@@ -1107,7 +1103,7 @@ void segmented_scan_tables(Batch &b, std::vector<int64_t> lt, std::vector<int64_
     std::vector<int32_t> small(lt.size(), 0);
     bool rest = false;
     for (size_t i = 0; i < lt.size(); ++i) {
-        small[i] = lt[i] >= 0 && std::max(lt[i], le[i]) <= kScanMost ? 2 : 0;
+        small[i] = lt[i] >= 0 && std::max(lt[i], le[i]) <= kScanOne ? 2 : 0;
         if (small[i]) lt[i] = le[i] = -1;
         rest |= lt[i] >= 0;
     }
