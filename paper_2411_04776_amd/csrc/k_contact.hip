@@ -761,6 +761,20 @@ __device__ __forceinline__ void rr_pair(int round, int i, int &p, int &q)
     q = a < b ? b : a;
 }
 
+// The smaller rotation that zeroes a_pq: its tangent, cosine and sine, from
+// tan 2 phi = 2 a_pq / (a_qq - a_pp): a square root, a division and a
+// reciprocal root in a chain (by way of the cotangent it was three divisions
+// and two roots, most of a rotation's time).
+__device__ __forceinline__ double jacobi_angle(double app, double aqq, double apq, double &c, double &sn)
+{
+    const double h = aqq - app, g = 2.0 * apq, den = fabs(h) + sqrt(h * h + g * g);
+    double t = (h >= 0.0 ? g : -g) / den;
+    t = apq == 0.0 ? 0.0 : (den > 0.0 ? t : (apq > 0.0 ? 1.0 : -1.0));  // squares that vanish: 45 degrees
+    c = rsqrt(t * t + 1.0);
+    sn = t * c;
+    return t;
+}
+
 // Cyclic Jacobi on a symmetric 5 x 5 matrix held in registers as its upper
 // triangle (rows and columns past the restriction's dimension are zero and
 // stay zero): eigenvalues left on the diagonal, eigenvectors in V's columns.
@@ -797,12 +811,7 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const double apq = U[ut5(p[k], q[k])];
-                const double theta = (U[ut5(q[k], q[k])] - U[ut5(p[k], p[k])]) / (2.0 * apq);
-                double t = fabs(theta) > 1e150 ? 0.5 / theta
-                                                : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                t = apq == 0.0 ? 0.0 : t;
-                c[k] = 1.0 / sqrt(t * t + 1.0);
-                sn[k] = t * c[k];
+                const double t = jacobi_angle(U[ut5(p[k], p[k])], U[ut5(q[k], q[k])], apq, c[k], sn[k]);
                 U[ut5(p[k], p[k])] -= t * apq;
                 U[ut5(q[k], q[k])] += t * apq;
                 U[ut5(p[k], q[k])] = 0.0;
@@ -835,8 +844,8 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
 // entries kappa w b''(d) gd_p gd_q, PSD and rank one as they are.
 // Bound by the chain of one pair: what lanes index by entry is in LDS, the
 // basis is orthogonalised with a component per lane, the 5x5 rotations run two
-// at a time and a 12x12 round is one pass over its 2 x 2 blocks: 241 -> 184 us
-// (130,600 vertices, mollified pairs among them), 40.7 -> 32.8 us (4,500).
+// at a time and a 12x12 round is one pass over its 2 x 2 blocks: 241 -> 153 us
+// (130,600 vertices, mollified pairs among them), 40.7 -> 28.9 us (4,500).
 template <class R>
 __global__ void __launch_bounds__(64) k_barrier(Launch L)
 {
@@ -1099,14 +1108,8 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
                 vkp[u] = V[vp[u]];
                 vkq[u] = V[vq[u]];
             }
-            double c = 1.0, sn = 0.0;
-            if (apq != 0.0) {
-                double theta = (aqq - app) / (2.0 * apq);
-                double t = fabs(theta) > 1e150 ? 0.5 / theta
-                                               : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-                c = 1.0 / sqrt(t * t + 1.0);
-                sn = t * c;
-            }
+            double c, sn;
+            (void)jacobi_angle(app, aqq, apq, c, sn);
             const double cr = __shfl(c, bi, 64), sr = __shfl(sn, bi, 64);
             const double cv[2] = {__shfl(c, lane / 12, 64), __shfl(c, 5, 64)};
             const double sv[2] = {__shfl(sn, lane / 12, 64), __shfl(sn, 5, 64)};
