@@ -172,6 +172,8 @@ def pcg_roofline(prof, workload, note):
                       "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                       "traffic": tr, "traffic_over_algorithmic": ratio,
                       "traffic_source": TRAFFIC_PROFILES[workload][kname], "bytes_per_launch": int(bpl),
+                      "bytes_note": "algorithmic; a resident solve keeps its vectors on the chip, so its rate is "
+                                    "work done and not memory traffic",
                       "timed_launches": int(n), "avg_launch_us": round(avg_s * 1e6, 3), "event_ms": round(ms, 3),
                       "timing": "HIP events around each resident launch and one other launch in sixteen, on the launch "
                                 "stream, timed region",

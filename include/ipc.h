@@ -273,21 +273,20 @@ IPC_API int32_t ipc_batch_wait(ipc_batch *b, ipc_ticket t, ipc_step_stats *st);
 IPC_API int32_t ipc_batch_next(ipc_batch *b, double timeout_ms, ipc_ticket *t, int32_t *status,
                                ipc_step_stats *st);
 /* Kernel timing inside the engine: enable (1) or disable (0) resets the
- * totals; from the next Newton round on, each phase launch, each
- * launch of resident PCG solves and one other PCG launch in sixteen is bracketed by HIP events on the engine's stream (same classes as
- * ipcx_profile). profile_read returns the timed launches, their summed
- * milliseconds and, for classes 0 and 1 (the two PCG kernels;
- * a launch of resident solves counts in class 0, with both classes' bytes of
- * all its iterations), the summed
- * algorithmic bytes of those launches over every scene of the list whose
- * solve was still running: class 0 (SpMV) per stored 3x3 block its values and
- * column index, per vertex the z and d gathers, the d and q writes and the
- * row pointer, per merged contact block (per contact row one for each other
- * vertex that it shares a pair with) its values, column and gathers; class 1
- * (update) per vertex q, d, p, r and the 3x3 inverse read and p, r, z
- * written, per contact row its part of q, per preconditioner member 16 bytes
- * of ids, per SpMV block its d.q
- * partial (4- or 8-byte reals by the list's precision). */
+ * totals; from the next Newton round on, each phase launch, each launch of
+ * resident PCG solves and one other PCG launch in sixteen is bracketed by HIP
+ * events on the engine's stream (same classes as ipcx_profile). profile_read
+ * returns the timed launches, their summed milliseconds and, for classes 0 and
+ * 1 (the two PCG kernels; a launch of resident solves counts in class 0, with
+ * both classes' bytes of all its iterations), the summed algorithmic bytes of
+ * those launches over every scene of the list whose solve was still running:
+ * class 0 (SpMV) per stored 3x3 block its values and column index, per vertex
+ * the z and d gathers, the d and q writes and the row pointer, per merged
+ * contact block (per contact row one for each other vertex that it shares a
+ * pair with) its values and column; class 1 (update) per vertex q, d, p, r and
+ * the 3x3 inverse read and p, r, z written, per preconditioner member 16 bytes
+ * of ids, per SpMV block its d.q partial (4- or 8-byte reals by the list's
+ * precision). */
 IPC_API int32_t ipc_batch_profile(ipc_batch *b, int32_t enable);
 /* Every launch of PCG class 0 or 1 while profiling was on (not only the
  * timed ones) and their summed algorithmic bytes, counted as above: the

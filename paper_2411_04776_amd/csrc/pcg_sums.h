@@ -6,8 +6,8 @@
 // matrix rows, team_units consecutive update units, and the contact rows
 // whose first incidence entry lies in its 1/T of the entries (contact rows
 // cluster in a few slices of the matrix; by entries they spread evenly). A
-// chunk's partials are added in order, then one wavefront adds the chunks (lane l takes l, l + 64, ...) and its fixed tree
-// ends the sum.
+// chunk's partials are added in order, then one wavefront adds the chunks (lane
+// l takes l, l + 64, ...) and its fixed tree ends the sum.
 #pragma once
 #include <type_traits>
 
