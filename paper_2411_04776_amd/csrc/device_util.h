@@ -24,6 +24,16 @@ __device__ __forceinline__ gptr<T> glob(T *p)
     return (gptr<T>)p;
 }
 
+// A value the optimiser cannot trace back: addresses made from it are formed
+// where they are used. Hoisted out of a resident solve's iteration loop they
+// would take the registers of its matrix rows.
+template <class T>
+__device__ __forceinline__ T here(T v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // One 32-bit step of a 64-lane butterfly: lanes exchange over distance O
 // without the LDS crossbar (a __shfl of a double is two ds_bpermute of about
 // 130 cycles each; these are VALU moves). For O <= 8 the row rotation reads
@@ -72,6 +82,15 @@ __device__ __forceinline__ double wave_first(double v)
     const uint64_t x = (uint64_t)__double_as_longlong(v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// lane i's value (i the same in every lane)
+__device__ __forceinline__ double lane_value(double v, int i)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, i);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), i);
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 

@@ -48,6 +48,7 @@ constexpr int kSpmvStreams = 2;   // partial sums per SpMV row (slots k, k + 2, 
 constexpr int kRowsPerBlock = 64; // matrix rows per SpMV block (PCG A), a thread or two lanes each
 constexpr int kRowTeam = 16;      // lanes that share a contact row's blocks
 constexpr int kRowLong = 64;      // contact rows of more blocks take a wavefront
+constexpr int kHeavyRow = 24;     // contact rows of more incidence entries are summed by a whole block
 constexpr int kRowSeg = 680;      // incidence entries of a contact row merged at a time (three columns each, sorted in LDS)
 constexpr int64_t kSpmvOneLaneRows = 65536;  // lists with at least this many rows: one thread per row
 constexpr int kScanTile = 1024;   // elements per scan tile
@@ -61,6 +62,7 @@ constexpr int kMasTarget = 256;   // groups are packed with top-level aggregates
 
 constexpr int kTeamMax = 256;     // workgroups of a resident PCG team (one per CU)
 constexpr int kTeamSlots = 8;     // matrix slots of a row half kept in registers (two threads per row)
+constexpr int kTeamSoloPair = 2, kTeamSolo = 3;  // scenes that one workgroup holds (k_pcg_solo.hip): two threads a row, one
 constexpr int kTeamCompact = 4;   // layout of a resident team's workgroups that share CUs (the others: 0 to 3)
 constexpr int kTeamDyn = 158 * 1024;  // dynamic LDS of a team's workgroup (160 KB a CU, less its static arrays)
 constexpr int kChunkRows = 512;    // contact rows a resident team's member takes (more: the launched form)
@@ -420,7 +422,8 @@ enum PhaseKind {
     kPhMas,       // preconditioner diagonal: a wavefront per level-0 aggregate, a block per coarser one
     kPhMasG,      // preconditioner groups (a block each)
     kPhPcgB,      // PCG update: groups, then vertex blocks
-    kPhTeam0, kPhTeam1, kPhTeam2, kPhTeam3, kPhTeam4,  // resident PCG teams: narrow, wide, teams of one (two), compact
+    kPhTeam0, kPhTeam1, kPhTeam2,  // resident PCG teams: narrow, wide, compact
+    kPhSolo0, kPhSolo1,            // solves of one workgroup: two threads a row, one
     kPhOne,       // one block per scene
     kPhTilesT, kPhTilesE, kPhTilesQ, kPhTilesC, kPhTilesA,  // scan tiles
     kPhZeroC,     // contact counts to clear, kBlock threads
@@ -539,11 +542,16 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap);
 // resident solves of the scenes with on[i] (host)
 void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on);
 // layouts of a team's workgroups: 0 narrow, 1 wide (twice the rows and units),
-// 2 and 3 teams of one (twice the units, twice both), kTeamCompact the narrow one's chunks in half the threads
+// kTeamSoloPair and kTeamSolo a scene in one workgroup (twice the units, twice both), kTeamCompact the narrow one's
+// chunks in half the threads
 int team_rows(int variant, size_t real);
 int team_units(int variant, size_t real);
 size_t team_lds_bytes(int variant, int H, int A, size_t real);
 void team_prepare_device();  // dynamic-LDS limit of the team kernels on the current device
+// the same for the scenes with on[i] that one workgroup holds
+void launch_pcg_solo(Batch &b, const std::vector<uint8_t> &on);
+void solo_prepare_device();
+inline bool solo_layout(const SceneDev &h) { return h.team_variant == kTeamSoloPair || h.team_variant == kTeamSolo; }
 void run_pinf(Batch &b);
 void launch_hess_apply(Batch &b);  // y (S.q) = H v (S.dB)
 

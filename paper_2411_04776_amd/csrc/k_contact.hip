@@ -761,16 +761,15 @@ __device__ __forceinline__ void rr_pair(int round, int i, int &p, int &q)
     q = a < b ? b : a;
 }
 
-// The smaller rotation that zeroes a_pq: its tangent, cosine and sine, from
-// tan 2 phi = 2 a_pq / (a_qq - a_pp): a square root, a division and a
-// reciprocal root in a chain (by way of the cotangent it was three divisions
-// and two roots, most of a rotation's time).
+// The smaller rotation that zeroes a_pq != 0: its tangent, cosine and sine by
+// way of the cotangent 2 theta, which scales out of range for no entries that
+// the sweeps' sums of squares can hold.
 __device__ __forceinline__ double jacobi_angle(double app, double aqq, double apq, double &c, double &sn)
 {
-    const double h = aqq - app, g = 2.0 * apq, den = fabs(h) + sqrt(h * h + g * g);
-    double t = (h >= 0.0 ? g : -g) / den;
-    t = apq == 0.0 ? 0.0 : (den > 0.0 ? t : (apq > 0.0 ? 1.0 : -1.0));  // squares that vanish: 45 degrees
-    c = rsqrt(t * t + 1.0);
+    const double theta = (aqq - app) / (2.0 * apq);
+    const double t = fabs(theta) > 1e150 ? 0.5 / theta
+                                         : (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+    c = 1.0 / sqrt(t * t + 1.0);
     sn = t * c;
     return t;
 }
@@ -805,34 +804,30 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
             for (int b = a + 1; b < 5; ++b) off += U[ut5(a, b)] * U[ut5(a, b)];
         if (off <= 0.5e-36 * fro || off == 0.0) break;
 #pragma unroll
-        for (int r = 0; r < 5; ++r) {  // a round's two pairs are disjoint: their angles form beside each other
-            const int p[2] = {(r + 1) % 5, (r + 2) % 5}, q[2] = {(r + 4) % 5, (r + 3) % 5};
-            double c[2], sn[2];
+        for (int p = 0; p < 5; ++p)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const double apq = U[ut5(p[k], q[k])];
-                const double t = jacobi_angle(U[ut5(p[k], p[k])], U[ut5(q[k], q[k])], apq, c[k], sn[k]);
-                U[ut5(p[k], p[k])] -= t * apq;
-                U[ut5(q[k], q[k])] += t * apq;
-                U[ut5(p[k], q[k])] = 0.0;
-            }
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
+            for (int q = p + 1; q < 5; ++q) {
+                const double apq = U[ut5(p, q)];
+                if (apq == 0.0) continue;
+                double c, sn;
+                const double t = jacobi_angle(U[ut5(p, p)], U[ut5(q, q)], apq, c, sn);
+                U[ut5(p, p)] -= t * apq;
+                U[ut5(q, q)] += t * apq;
+                U[ut5(p, q)] = 0.0;
 #pragma unroll
                 for (int m = 0; m < 5; ++m) {
-                    if (m == p[k] || m == q[k]) continue;
-                    const double amp = U[ut5(m, p[k])], amq = U[ut5(m, q[k])];
-                    U[ut5(m, p[k])] = c[k] * amp - sn[k] * amq;
-                    U[ut5(m, q[k])] = sn[k] * amp + c[k] * amq;
+                    if (m == p || m == q) continue;
+                    const double amp = U[ut5(m, p)], amq = U[ut5(m, q)];
+                    U[ut5(m, p)] = c * amp - sn * amq;
+                    U[ut5(m, q)] = sn * amp + c * amq;
                 }
 #pragma unroll
                 for (int m = 0; m < 5; ++m) {
-                    const double vmp = V[m][p[k]], vmq = V[m][q[k]];
-                    V[m][p[k]] = c[k] * vmp - sn[k] * vmq;
-                    V[m][q[k]] = sn[k] * vmp + c[k] * vmq;
+                    const double vmp = V[m][p], vmq = V[m][q];
+                    V[m][p] = c * vmp - sn * vmq;
+                    V[m][q] = sn * vmp + c * vmq;
                 }
             }
-        }
     }
 }
 
@@ -982,9 +977,16 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
         // restriction to an orthonormal basis Q of the span (k <= 5): a k x k
         // Jacobi instead of the 12 x 12 one.
         __shared__ double Q[5][12], AQ[12][5], M[5][5], MV[5][5];
-        // Gram-Schmidt with a component per lane (each row of 16 lanes holds a copy)
+        // Gram-Schmidt with a component per lane (each row of 16 lanes holds a
+        // copy), the dot products' terms added in the components' order
         const int pp = lane & 15;
-        auto dot = [](double a, double c) { return lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(a * c)))); };
+        auto dot = [](double a, double b) {
+            const double x = a * b;
+            double acc = 0.0;
+#pragma unroll
+            for (int i = 0; i < 12; ++i) acc += lane_value(x, i);
+            return acc;
+        };
         const double cn = sqrt(dd.c[0] * dd.c[0] + dd.c[1] * dd.c[1] + dd.c[2] * dd.c[2] + dd.c[3] * dd.c[3]);
         const double qc = pp < 12 ? pl.c[pp / 3] / cn : 0.0;
         double q[4] = {pp % 3 == 0 ? qc : 0.0, pp % 3 == 1 ? qc : 0.0, pp % 3 == 2 ? qc : 0.0, 0.0};
@@ -1108,8 +1110,8 @@ __global__ void __launch_bounds__(64) k_barrier(Launch L)
                 vkp[u] = V[vp[u]];
                 vkq[u] = V[vq[u]];
             }
-            double c, sn;
-            (void)jacobi_angle(app, aqq, apq, c, sn);
+            double c = 1.0, sn = 0.0;
+            if (apq != 0.0) (void)jacobi_angle(app, aqq, apq, c, sn);
             const double cr = __shfl(c, bi, 64), sr = __shfl(sn, bi, 64);
             const double cv[2] = {__shfl(c, lane / 12, 64), __shfl(c, 5, 64)};
             const double sv[2] = {__shfl(sn, lane / 12, 64), __shfl(sn, 5, 64)};
@@ -1218,7 +1220,7 @@ __global__ void __launch_bounds__(kBlock) k_contact_rows(Launch L)
 {
     __shared__ unsigned long long key[kRowKeys];
     __shared__ int first[kRowKeys + 1];  // first key of each distinct column
-    __shared__ double part[kBlock / 12][12];
+    __shared__ double part[kHeavyRow][12];
     __shared__ int wsum[kBlock / kWave];
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
@@ -1230,28 +1232,41 @@ __global__ void __launch_bounds__(kBlock) k_contact_rows(Launch L)
     int blocks = 0;
     for (int i = lb; i < nrow; i += nblk) {
         const int row = S.c_rows[i], e0 = S.c_ptr[row], ne = S.c_ptr[row + 1] - e0;
-        // gradient (components 0..2) and diagonal block (3..11): entries split
-        // over the groups of 12 threads, the groups' sums added in order
-        constexpr int G = kBlock / 12;
-        if (tid < 12 * G) {
-            const int c = tid % 12, g = tid / 12;
-            double acc = 0.0;
-            for (int e = g; e < ne; e += G) {
-                const int src = S.c_list[e0 + e], a = src & 3;
-                const int64_t p = src >> 2;
-                acc += c < 3 ? (double)ag[(int64_t)(3 * a + c) * cap + p]
-                             : (double)aH[144 * p + (3 * a + (c - 3) / 3) * 12 + 3 * a + (c - 3) % 3];
-            }
-            part[g][c] = acc;
-        }
-        __syncthreads();
-        if (tid < 12) {
-            double t = 0.0;
-            for (int g = 0; g < G; ++g) t += part[g][tid];
-            if (tid < 3)
-                S.c_grad[3 * (int64_t)row + tid] = t;
+        // gradient (components 0..2) and diagonal block (3..11): up to kHeavyRow
+        // entries in pair order, read by all threads at once and added by one per
+        // component; more entries an entry per thread, the threads' sums by the
+        // wavefronts' trees, the wavefronts in order
+        auto value = [&](int e, int c) {
+            const int src = S.c_list[e0 + e], a = src & 3;
+            const int64_t p = src >> 2;
+            return c < 3 ? (double)ag[(int64_t)(3 * a + c) * cap + p]
+                         : (double)aH[144 * p + (3 * a + (c - 3) / 3) * 12 + 3 * a + (c - 3) % 3];
+        };
+        auto keep = [&](int c, double t) {
+            if (c < 3)
+                S.c_grad[3 * (int64_t)row + c] = t;
             else
-                S.c_diag[9 * (int64_t)row + tid - 3] = t;
+                S.c_diag[9 * (int64_t)row + c - 3] = t;
+        };
+        if (ne <= kHeavyRow) {
+            for (int x = tid; x < 12 * ne; x += kBlock) part[x / 12][x % 12] = value(x / 12, x % 12);
+            __syncthreads();
+            if (tid < 12) {
+                double t = 0.0;
+                for (int e = 0; e < ne; ++e) t += part[e][tid];
+                keep(tid, t);
+            }
+        } else {
+            double acc[12];
+#pragma unroll
+            for (int c = 0; c < 12; ++c) acc[c] = 0.0;
+            for (int e = tid; e < ne; e += kBlock)
+#pragma unroll
+                for (int c = 0; c < 12; ++c) acc[c] += value(e, c);
+            block_sum_vec<12>(acc);
+            if (tid == 0)
+#pragma unroll
+                for (int c = 0; c < 12; ++c) keep(c, acc[c]);
         }
         int out = 0;  // blocks of the row so far
         for (int seg = 0; seg < ne; seg += kRowSeg) {

@@ -22,9 +22,10 @@
 // thread) of 1,024 threads with half a row each had half the registers and
 // spilled: 36.7 us an iteration at 130,600 vertices, not 25.3.
 //
-// Measured (us per iteration, launched form before -> this): 90 vertices FP64
-// 21 -> 5.4; 1,442 FP64 24 -> 8.7; 16,800 FP64 26 -> 11.1; 10,100 mixed 29 ->
-// 12.9; 130,600 mixed 59 -> 25.3.
+// Measured (us per iteration, launched form before -> this): 1,442 vertices
+// FP64 24 -> 8.7; 16,800 FP64 26 -> 11.1; 10,100 mixed 29 -> 12.9; 130,600
+// mixed 59 -> 25.3. A scene that one workgroup holds has a kernel of its own
+// (k_pcg_solo.hip).
 //
 // Exchange. Values that cross workgroups are written and read with
 // agent-scope accesses (they pass the non-coherent caches), so no cache is
@@ -38,8 +39,7 @@
 // (12.9 us: the polls get in the way of the partials).
 //
 // A slot is overwritten only after every member has read it: its next value
-// depends on a sum that depends on all members' uses of the last one. A
-// team of one exchanges through its LDS.
+// depends on a sum that depends on all members' uses of the last one.
 //
 // Waiting. A workgroup first adds itself to the scene's join word; the team
 // runs only once all T have arrived, all of them resident from then on, so
@@ -198,17 +198,6 @@ constexpr int team_columns(int variant) { return variant == kTeamCompact ? 5 : 4
 int team_rows(int variant, size_t real) { return team_threads(variant, real) / kTeamRT[variant]; }
 int team_units(int variant, size_t real) { return team_threads(variant, real) / kBlock * kTeamV[variant]; }
 
-// A value the optimiser cannot trace back: addresses made from it are formed
-// where they are used. Hoisted out of the iteration loop they would take the
-// registers of the matrix rows (64 of them for the polled slots and the
-// re-read matrix values alone).
-template <class T>
-__device__ __forceinline__ T here(T v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // LDS of one update unit: rm[256][3] members' residuals, then corrections (R);
 // ra[A][3] aggregate sums (double); inverses A * 9 (R); member ranges A (two
 // 16-bit positions); per level the number of the group's aggregates
@@ -219,8 +208,7 @@ __host__ __device__ inline size_t team_unit_bytes(int A, size_t real)
 }
 size_t team_lds_bytes(int variant, int H, int A, size_t real)
 {
-    const size_t own = variant == 2 || variant == 3 ? 9 * (size_t)team_rows(variant, real) * real : 0;  // z, q and contact q of a team of one
-    return up8(3 * (size_t)H * real) + (size_t)team_units(variant, real) * team_unit_bytes(A, real) + own +
+    return up8(3 * (size_t)H * real) + (size_t)team_units(variant, real) * team_unit_bytes(A, real) +
            (size_t)team_lds_slots(variant) * 9 * team_threads(variant, real) * real +
            (8 + sizeof(CRow)) * (size_t)team_contact_rows(variant);
 }
@@ -292,10 +280,9 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
 {
     constexpr int NT = team_threads(VARIANT, sizeof(R)), NW = NT / kWave, G = NT / kBlock;  // G: threads' groups of 256
     constexpr int RT = kTeamRT[VARIANT], V = kTeamV[VARIANT], U = V * G, RPW = NT / RT;
-    constexpr bool SOLO = VARIANT == 2 || VARIANT == 3;
     constexpr int HALO = team_columns(VARIANT), ROWS = VARIANT == kTeamCompact ? kCompactRows : kChunkRows;
-    constexpr bool PMEM = RT == 1 && !SOLO;  // p in memory: registers are short
-    constexpr bool HOLD = RT == 2 || SOLO;  // contact blocks in registers
+    constexpr bool PMEM = RT == 1;  // p in memory: registers are short
+    constexpr bool HOLD = RT == 2;  // contact blocks in registers
     constexpr int NS = RT == 2 ? kTeamSlots : 2 * kTeamSlots - 1;  // blocks on the chip,
     constexpr int RS = NS - team_lds_slots(VARIANT);               // the first RS of them in registers
     extern __shared__ double team_lds[];
@@ -316,7 +303,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         w = (int)blockIdx.x - L.blk_off[lo];
     }
     const SceneDev &S = *L.sc[s];
-    const int T = SOLO ? 1 : S.team_T;
+    const int T = S.team_T;
     int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     // what the loop needs of the view, read here: after the kernel's first
@@ -355,9 +342,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
     };
     double *const cdot = reinterpret_cast<double *>(base_u + (size_t)U * ub);  // contact rows: their d.q
     CRow *const clist = reinterpret_cast<CRow *>(cdot + ROWS);           // and places
-    R *const zl = reinterpret_cast<R *>(clist + ROWS);  // a team of one: z, q, contact q, [c * n + v] each
-    R *const ql = zl + 3 * n, *const cl = ql + 3 * n;
-    R *const ml = SOLO ? zl + 9 * (size_t)RPW : zl;  // matrix blocks: ml[(k * 9 + e) * NT + tid]
+    R *const ml = reinterpret_cast<R *>(clist + ROWS);  // matrix blocks: ml[(k * 9 + e) * NT + tid]
     static_assert(sizeof(CRow) * ROWS % 8 == 0, "the arrays after the list are 8-byte aligned");
 
     // ---- this thread's matrix row or half row (slot k of the thread: part + RT * k of the row)
@@ -391,12 +376,11 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             }
         }
     }
-    // ---- this thread's columns of the chunk's list (a team of one: all vertices, in order)
-    const int h0 = SOLO ? 0 : glob(S.team_hptr)[w], nh = SOLO ? n : glob(S.team_hptr)[w + 1] - h0;
+    // ---- this thread's columns of the chunk's list
+    const int h0 = glob(S.team_hptr)[w], nh = glob(S.team_hptr)[w + 1] - h0;
     int hv[HALO];
-    if constexpr (!SOLO)
 #pragma unroll
-        for (int j = 0; j < HALO; ++j) hv[j] = tid + j * NT < nh ? glob(Hl)[h0 + tid + j * NT] : 0;
+    for (int j = 0; j < HALO; ++j) hv[j] = tid + j * NT < nh ? glob(Hl)[h0 + tid + j * NT] : 0;
     for (int i = tid; i < 3 * H; i += NT) hd[i] = R(0);
 
     // ---- this thread's vertices, one of each of its update units
@@ -496,34 +480,30 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         }
     }
     // the workgroup's part of the exchanged vectors: no tag of an earlier solve
-    if constexpr (!SOLO) {
-        for (int i = tid; i < RPW; i += NT)
-            if (w * RPW + i < n) {
-                const int v = w * RPW + i;
-                Z.clear(v);
-                Q.clear(v);
-                C.clear(v);
-                DA.clear(v);
-                DB.clear(v);
-            }
-        if (tid == 0) {
-            P_dq.put(w, 0.0, 0u);
-            P_rz.put(w, 0.0, 0u);
+    for (int i = tid; i < RPW; i += NT)
+        if (w * RPW + i < n) {
+            const int v = w * RPW + i;
+            Z.clear(v);
+            Q.clear(v);
+            C.clear(v);
+            DA.clear(v);
+            DB.clear(v);
         }
-        stores_arrived();
+    if (tid == 0) {
+        P_dq.put(w, 0.0, 0u);
+        P_rz.put(w, 0.0, 0u);
     }
+    stores_arrived();
     __syncthreads();
     // ---- the team forms
-    if constexpr (!SOLO) {
-        if (tid == 0) {
-            if (!team_join(S.pcg, T, S.team_spin)) {
-                s_ok = 0;
-                xstore(glob(&L.out[s].pcg_fail), (int32_t)1);
-            }
+    if (tid == 0) {
+        if (!team_join(S.pcg, T, S.team_spin)) {
+            s_ok = 0;
+            xstore(glob(&L.out[s].pcg_fail), (int32_t)1);
         }
-        __syncthreads();
-        if (!s_ok) return;  // the whole workgroup
     }
+    __syncthreads();
+    if (!s_ok) return;  // the whole workgroup
 
     // the units' aggregates per level, and the ranges of this thread's items
     static_assert(kMasLevels == 3, "three levels' ranges");
@@ -615,11 +595,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                     }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) z[v][c] = (R)zi[c];
-                if constexpr (SOLO)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) zl[c * n + vid[v]] = z[v][c];
-                else
-                    Z.store(vid[v], z[v], tag);
+                Z.store(vid[v], z[v], tag);
             }
             rz[v] = wave_sum(rz[v]);
             if (lane == 0) s_rz[v * NW + wave] = rz[v];
@@ -629,33 +605,28 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             double t = 0.0;
 #pragma unroll
             for (int u = 0; u < U; ++u) t += (s_rz[4 * u] + s_rz[4 * u + 2]) + (s_rz[4 * u + 1] + s_rz[4 * u + 3]);
-            if constexpr (SOLO)
-                s_tot = 0.0 + t;
-            else if (s_ok)
-                P_rz.put(w, t, tag);
+            if (s_ok) P_rz.put(w, t, tag);
         }
     };
     // the sum over all chunks, for every thread; false if a wait ran out
     auto total = [&](const Partials &P, uint32_t tag, double &t) {
-        if constexpr (!SOLO) {
-            if (wave == 0) {
-                bool ok;
-                double v;
-                switch ((T + kWave - 1) / kWave) {
-                case 1: ok = P.sum<1>(T, tag, v); break;
-                case 2: ok = P.sum<2>(T, tag, v); break;
-                case 3: ok = P.sum<3>(T, tag, v); break;
-                default: ok = P.sum<kTeamMax / kWave>(T, tag, v);
-                }
-                if (lane == 0) {
-                    s_tot = v;
-                    if (!ok) s_ok = 0;
-                }
+        if (wave == 0) {
+            bool ok;
+            double v;
+            switch ((T + kWave - 1) / kWave) {
+            case 1: ok = P.sum<1>(T, tag, v); break;
+            case 2: ok = P.sum<2>(T, tag, v); break;
+            case 3: ok = P.sum<3>(T, tag, v); break;
+            default: ok = P.sum<kTeamMax / kWave>(T, tag, v);
+            }
+            if (lane == 0) {
+                s_tot = v;
+                if (!ok) s_ok = 0;
             }
         }
         __syncthreads();
         t = wave_first(s_tot);
-        return SOLO || s_ok != 0;
+        return s_ok != 0;
     };
 
     // ---- start: p = 0, r = -g
@@ -676,9 +647,8 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
     for (int it = 1;; ++it) {
 #pragma unroll
         for (int k = 0; k < (NS + 1) / 2; ++k) lc[k] = here(lc[k]);
-        if constexpr (!SOLO)
 #pragma unroll
-            for (int j = 0; j < HALO; ++j) hv[j] = here(hv[j]);
+        for (int j = 0; j < HALO; ++j) hv[j] = here(hv[j]);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             vid[v] = here(vid[v]);
@@ -693,32 +663,29 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         // z at the chunk's columns (and at the held contact block's)
         typename XVec<R>::Raw zr[HALO], zc, zo;
         auto columns = [&]() {
-            if constexpr (!SOLO) {
+#pragma unroll
+            for (int j = 0; j < HALO; ++j)
+                if (j * NT < nh) Z.load(hv[j], zr[j]);  // uniform; ids past the list read vertex 0
+            if (HOLD && cteam) {
+                Z.load(ccol, zc);
+                Z.load(crow, zo);
+            }
+            for (int k = 0;; ++k) {  // each until it is this iteration's
+                bool ok = true;
 #pragma unroll
                 for (int j = 0; j < HALO; ++j)
-                    if (j * NT < nh) Z.load(hv[j], zr[j]);  // uniform; ids past the list read vertex 0
-                if (HOLD && cteam) {
-                    Z.load(ccol, zc);
-                    Z.load(crow, zo);
-                }
-                for (int k = 0;; ++k) {  // each until it is this iteration's
-                    bool ok = true;
-#pragma unroll
-                    for (int j = 0; j < HALO; ++j)
-                        if (j * NT < nh && !XVec<R>::is(zr[j], tag)) {
-                            Z.load(hv[j], zr[j]);
-                            ok = false;
-                        }
-                    if (HOLD && cteam && !(XVec<R>::is(zc, tag) && XVec<R>::is(zo, tag))) {
-                        Z.load(ccol, zc);
-                        Z.load(crow, zo);
+                    if (j * NT < nh && !XVec<R>::is(zr[j], tag)) {
+                        Z.load(hv[j], zr[j]);
                         ok = false;
                     }
-                    if (ok) return true;
-                    if (k == kTeamPoll) return false;
+                if (HOLD && cteam && !(XVec<R>::is(zc, tag) && XVec<R>::is(zo, tag))) {
+                    Z.load(ccol, zc);
+                    Z.load(crow, zo);
+                    ok = false;
                 }
+                if (ok) return true;
+                if (k == kTeamPoll) return false;
             }
-            return true;
         };
         double rz;
         if (!total(P_rz, (uint32_t)it, rz)) break;
@@ -755,50 +722,29 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int c = 0; c < 3; ++c) d[v][c] = z[v][c] + rb * d[v][c];
-        if constexpr (SOLO) {
-            for (int i = tid; i < n; i += NT) {
-                const R zv[3] = {zl[i], zl[n + i], zl[2 * n + i]};
-                advance(i, zv);
-            }
-        } else {
 #pragma unroll
-            for (int j = 0; j < HALO; ++j)
-                if (tid + j * NT < nh) {
-                    R zv[3];
-                    XVec<R>::get(zr[j], zv);
-                    advance(tid + j * NT, zv);
-                }
-            for (int i = tid + HALO * NT; i < nh; i += NT) {
+        for (int j = 0; j < HALO; ++j)
+            if (tid + j * NT < nh) {
                 R zv[3];
-                ok &= Z.wait(glob(Hl)[h0 + i], tag, zv);
-                advance(i, zv);
+                XVec<R>::get(zr[j], zv);
+                advance(tid + j * NT, zv);
             }
+        for (int i = tid + HALO * NT; i < nh; i += NT) {
+            R zv[3];
+            ok &= Z.wait(glob(Hl)[h0 + i], tag, zv);
+            advance(i, zv);
         }
         // contact rows: the held items, and the rows that are not held as the
-        // launched form does, with directions from memory (a team of one: LDS)
-        auto put_c = [&](int v, const R (&y)[3]) {
-            if constexpr (SOLO)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) cl[c * n + v] = y[c];
-            else
-                C.store(v, y, tag);
-        };
+        // launched form does, with directions from memory
+        auto put_c = [&](int v, const R (&y)[3]) { C.store(v, y, tag); };
         auto items = [&]() {
-            if constexpr (SOLO) {
+            R zv[3];
+            XVec<R>::get(zc, zv);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    cd[c] = hd[c * H + ccol];
-                    cown[c] = hd[c * H + crow];
-                }
-            } else {
-                R zv[3];
-                XVec<R>::get(zc, zv);
+            for (int c = 0; c < 3; ++c) cd[c] = zv[c] + rb * cd[c];
+            XVec<R>::get(zo, zv);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) cd[c] = zv[c] + rb * cd[c];
-                XVec<R>::get(zo, zv);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) cown[c] = zv[c] + rb * cown[c];
-            }
+            for (int c = 0; c < 3; ++c) cown[c] = zv[c] + rb * cown[c];
             double t[3];
             contact_item<R>(chas, cA, cd, t);
             const int i = tid / kRowTeam;
@@ -812,8 +758,6 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         auto others = [&]() {
             struct Dir {
                 XVec<R> Z, D;
-                const R *hd;
-                int H;
                 uint32_t tag;
                 R rb;
                 bool bon, ok;
@@ -823,32 +767,26 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                 __device__ __forceinline__ Raw start(int v) const
                 {
                     Raw x;
-                    if constexpr (!SOLO) {
-                        Z.load(v, x.z);
-                        D.load(v, x.d);
-                    }
+                    Z.load(v, x.z);
+                    D.load(v, x.d);
                     return x;
                 }
                 __device__ __forceinline__ void end(int v, Raw &x, R (&o)[3])
                 {
-                    if constexpr (SOLO) {
-                        for (int c = 0; c < 3; ++c) o[c] = hd[c * H + v];
-                    } else {
-                        const uint32_t before = (tag - 1) & 0xffffu;
-                        R dp[3] = {R(0), R(0), R(0)};
-                        for (int n = 0; !(XVec<R>::is(x.z, tag) && (!bon || XVec<R>::is(x.d, before))); ++n) {
-                            if (n == kTeamPoll) {
-                                ok = false;
-                                break;
-                            }
-                            x = start(v);
+                    const uint32_t before = (tag - 1) & 0xffffu;
+                    R dp[3] = {R(0), R(0), R(0)};
+                    for (int n = 0; !(XVec<R>::is(x.z, tag) && (!bon || XVec<R>::is(x.d, before))); ++n) {
+                        if (n == kTeamPoll) {
+                            ok = false;
+                            break;
                         }
-                        XVec<R>::get(x.z, o);
-                        if (bon) XVec<R>::get(x.d, dp);
-                        for (int c = 0; c < 3; ++c) o[c] = o[c] + rb * dp[c];
+                        x = start(v);
                     }
+                    XVec<R>::get(x.z, o);
+                    if (bon) XVec<R>::get(x.d, dp);
+                    for (int c = 0; c < 3; ++c) o[c] = o[c] + rb * dp[c];
                 }
-            } dir{Z, (it & 1) ? DB : DA, hd, H, tag, rb, bon, true};
+            } dir{Z, (it & 1) ? DB : DA, tag, rb, bon, true};
             contact_rows<NT, R>(Cv, Cc, clist, hrows, ncrow, tid, dir, put_c, cdot);
             ok &= dir.ok;
         };
@@ -872,15 +810,11 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             return t;
         };
         double cdq = 0.0;
-        if (!SOLO && ncrow > 0) {
+        if (ncrow > 0) {
             if (HOLD && hrows > 0 && cteam) items();
             if (hrows < ncrow) others();
         }
         __syncthreads();
-        if (SOLO && ncrow > 0) {
-            if (HOLD && hrows > 0 && cteam) items();
-            if (hrows < ncrow) others();
-        }
         // q = K d for the chunk's rows: even and odd slots in a sum each
         double dq = 0.0;
         {
@@ -936,61 +870,49 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                     dv[c] = hd[c * H + own];
                     dq += (double)dv[c] * (double)qv[c];
                 }
-                if constexpr (SOLO) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) ql[c * n + row] = qv[c];
-                } else {
-                    Q.store(row, qv, tag);
-                    if (touched) ((it & 1) ? DA : DB).store(row, dv, tag);  // for contact blocks that are not held
-                }
+                Q.store(row, qv, tag);
+                if (touched) ((it & 1) ? DA : DB).store(row, dv, tag);  // for contact blocks that are not held
             }
         }
         // per 64 rows: the two halves' sums added
-        if (!SOLO && contact && wave == 0) cdq = wave_sum(finish());
+        if (contact && wave == 0) cdq = wave_sum(finish());
         dq = RT == 2 ? wave_sum(dq) : half_wave_sum(dq);
         if (RT == 1) dq += __shfl(dq, 32, kWave);
         if (lane == 0) s_dq[wave] = dq;
-        if (!SOLO && !ok) s_ok = 0;
+        if (!ok) s_ok = 0;
         __syncthreads();
-        if (!SOLO && s_ok == 0) break;
-        if (SOLO && contact && wave == 0) cdq = wave_sum(finish());
+        if (s_ok == 0) break;
         if (tid == 0) {
             double a = 0.0;
 #pragma unroll
             for (int k = 0; k < NW; k += RT) a += RT == 2 ? s_dq[k] + s_dq[k + RT - 1] : s_dq[k];
             if (contact) a = a + cdq;
-            if constexpr (SOLO)
-                s_tot = 0.0 + a;
-            else
-                P_dq.put(w, a, (uint32_t)it);
+            P_dq.put(w, a, (uint32_t)it);
         }
         // q at the units' vertices
         typename XVec<R>::Raw qr[V], cr[V];
         auto products = [&]() {
-            if constexpr (!SOLO) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                if (vid[v] >= 0) Q.load(vid[v], qr[v]);
+                if (vtouched[v]) C.load(vid[v], cr[v]);
+            }
+            for (int k = 0;; ++k) {
+                bool all = true;
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    if (vid[v] >= 0) Q.load(vid[v], qr[v]);
-                    if (vtouched[v]) C.load(vid[v], cr[v]);
-                }
-                for (int k = 0;; ++k) {
-                    bool all = true;
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        if (vid[v] >= 0 && !XVec<R>::is(qr[v], tag)) {
-                            Q.load(vid[v], qr[v]);
-                            all = false;
-                        }
-                        if (vtouched[v] && !XVec<R>::is(cr[v], tag)) {
-                            C.load(vid[v], cr[v]);
-                            all = false;
-                        }
+                    if (vid[v] >= 0 && !XVec<R>::is(qr[v], tag)) {
+                        Q.load(vid[v], qr[v]);
+                        all = false;
                     }
-                    if (all) return true;
-                    if (k == kTeamPoll) return false;
+                    if (vtouched[v] && !XVec<R>::is(cr[v], tag)) {
+                        C.load(vid[v], cr[v]);
+                        all = false;
+                    }
                 }
+                if (all) return true;
+                if (k == kTeamPoll) return false;
             }
-            return true;
         };
         if constexpr (RT == 2) load_inverse();
         double dqt;
@@ -1003,17 +925,12 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         for (int v = 0; v < V; ++v)
             if (vid[v] >= 0) {
                 R qv[3];
-                if constexpr (SOLO) {
+                XVec<R>::get(qr[v], qv);
+                if (vtouched[v]) {
+                    R qc[3];
+                    XVec<R>::get(cr[v], qc);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) qv[c] = ql[c * n + vid[v]] + (vtouched[v] ? cl[c * n + vid[v]] : R(0));
-                } else {
-                    XVec<R>::get(qr[v], qv);
-                    if (vtouched[v]) {
-                        R qc[3];
-                        XVec<R>::get(cr[v], qc);
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) qv[c] += qc[c];
-                    }
+                    for (int c = 0; c < 3; ++c) qv[c] += qc[c];
                 }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
@@ -1060,11 +977,13 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
 
 // ---- host ------------------------------------------------------------------
 
+static PhaseKind team_phase(int variant) { return variant == 0 ? kPhTeam0 : variant == 1 ? kPhTeam1 : kPhTeam2; }
+
 template <class R>
 static void launch_variant(Batch &b, int variant, size_t lds)
 {
     const int N = team_threads(variant, sizeof(R));
-    const PhaseKind ph = (PhaseKind)(kPhTeam0 + variant);
+    const PhaseKind ph = team_phase(variant);
     const int nb = b.blocks(ph);
     if (nb == 0) return;
     b.flush_phases();
@@ -1072,8 +991,6 @@ static void launch_variant(Batch &b, int variant, size_t lds)
     switch (variant) {
     case 0: hipLaunchKernelGGL((k_pcg_team<R, 0>), dim3(nb), dim3(N), lds, b.stream, l); break;
     case 1: hipLaunchKernelGGL((k_pcg_team<R, 1>), dim3(nb), dim3(N), lds, b.stream, l); break;
-    case 2: hipLaunchKernelGGL((k_pcg_team<R, 2>), dim3(nb), dim3(N), lds, b.stream, l); break;
-    case 3: hipLaunchKernelGGL((k_pcg_team<R, 3>), dim3(nb), dim3(N), lds, b.stream, l); break;
     default:
         if constexpr (sizeof(R) == 4) hipLaunchKernelGGL((k_pcg_team<R, kTeamCompact>), dim3(nb), dim3(N), lds, b.stream, l);
     }
@@ -1097,7 +1014,7 @@ void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on)
                              team_lds_bytes(kTeamCompact, h.team_H, h.team_A, rs) <= kTeamDyn / 2;
         return compact ? kTeamCompact : h.team_variant;
     };
-    for (int v = 0; v <= kTeamCompact; ++v) {
+    for (int v : {0, 1, kTeamCompact}) {
         std::vector<int32_t> nb(ns, 0);
         size_t lds = 0;
         for (size_t i = 0; i < ns; ++i) {
@@ -1106,7 +1023,7 @@ void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on)
             nb[i] = h.team_T;
             lds = std::max(lds, team_lds_bytes(v, h.team_H, h.team_A, rs));
         }
-        b.set_phase((PhaseKind)(kPhTeam0 + v), nb);
+        b.set_phase(team_phase(v), nb);
         if (mx)
             launch_variant<float>(b, v, lds);
         else
@@ -1117,8 +1034,7 @@ void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on)
 template <class R>
 static void raise_lds()
 {
-    for (const void *f : {(const void *)k_pcg_team<R, 0>, (const void *)k_pcg_team<R, 1>, (const void *)k_pcg_team<R, 2>,
-                          (const void *)k_pcg_team<R, 3>})
+    for (const void *f : {(const void *)k_pcg_team<R, 0>, (const void *)k_pcg_team<R, 1>})
         IPC_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kTeamDyn));
     if constexpr (sizeof(R) == 4)
         IPC_HIP(hipFuncSetAttribute((const void *)k_pcg_team<R, kTeamCompact>, hipFuncAttributeMaxDynamicSharedMemorySize, kTeamDyn));

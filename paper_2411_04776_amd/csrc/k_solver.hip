@@ -1218,13 +1218,14 @@ static double pcg_bytes_b(const Scene &s, const SceneOut &o)
 void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
 {
     const size_t ns = b.sc.size();
-    std::vector<uint8_t> team(ns, 0), rest(ns, 0);
+    std::vector<uint8_t> team(ns, 0), solo(ns, 0), rest(ns, 0);
     bool any_team = false, any_rest = false;
     for (size_t i = 0; i < ns; ++i) {
         if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
         const SceneDev &h = b.sc[i]->h;
-        const bool t = h.team_fit && b.sc[i]->tune.team && chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kChunkRows;
-        (t ? team : rest)[i] = 1;
+        const bool one = solo_layout(h);  // such a scene has no other form
+        const bool t = one || (h.team_fit && b.sc[i]->tune.team && chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kChunkRows);
+        (one ? solo : t ? team : rest)[i] = 1;
         (t ? any_team : any_rest) = true;
     }
     iters.assign(ns, 0);
@@ -1233,12 +1234,13 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         hipEvent_t ev[2];
         if (b.prof()) b.prof_begin(kProfPcgA, ev);
         launch_pcg_team(b, team);
+        launch_pcg_solo(b, solo);
         const size_t timed = b.ev_pending.size();
         if (b.prof()) b.prof_end(kProfPcgA, ev);
         b.read_out();
         double bytes = 0.0, peak = 0.0;
         for (size_t i = 0; i < ns; ++i) {
-            if (!team[i]) continue;
+            if (!team[i] && !solo[i]) continue;
             const SceneOut &o = b.h_out[i];
             if (!o.pcg_done || o.pcg_fail) {
                 rest[i] = 1;

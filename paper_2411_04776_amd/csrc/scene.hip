@@ -641,7 +641,7 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
     auto chunks = [&](int v) {
         return std::max(nblocks(H.nb_rows, team_rows(v, rs) / kRowsPerBlock), nblocks(H.pcg_nvp, team_units(v, rs)));
     };
-    const int v = chunks(2) == 1 ? 2 : chunks(3) == 1 ? 3 : chunks(0) > (rs == sizeof(float) ? kTeamWide : kTeamMax) ? 1 : 0;
+    const int v = chunks(kTeamSoloPair) == 1 ? kTeamSoloPair : chunks(kTeamSolo) == 1 ? kTeamSolo : chunks(0) > (rs == sizeof(float) ? kTeamWide : kTeamMax) ? 1 : 0;
     H.team_variant = v;
     H.team_rows = team_rows(v, rs);
     H.team_units = team_units(v, rs);
@@ -649,6 +649,10 @@ static void build_team(Scene &s, const std::vector<int32_t> &slice_ptr, const st
     H.team_A = std::max(s.mas_max_aggs, 1);
     H.team_spin = s.tune.team_spin;
     H.team_fit = 0;
+    if (solo_layout(H)) {
+        solo_prepare_device();
+        return;
+    }
     int device = 0, cus = 0;
     IPC_HIP(hipGetDevice(&device));
     IPC_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
