@@ -460,7 +460,10 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             const int item = tid / kRowTeam, u = tid % kRowTeam;
             int at = 0, h = 0;
             for (; h < ncrow; ++h) {  // rows of items [at, at + k)
-                const int k = (clist[h].n + kRowTeam - 1) / kRowTeam;
+                // a row whose partners are all fixed has no block: an item of
+                // none, so that its direction and its zero product are there
+                // and there are never more rows than items
+                const int k = max((clist[h].n + kRowTeam - 1) / kRowTeam, 1);
                 if (at + k > NT / kRowTeam) break;
                 if (tid == 0) s_at[h] = at;
                 if (item >= at && item < at + k) {
