@@ -283,7 +283,7 @@ IPC_API int32_t ipc_batch_next(ipc_batch *b, double timeout_ms, ipc_ticket *t, i
  * class 0 (SpMV) per stored 3x3 block its values and column index, per vertex
  * the z and d gathers, the d and q writes and the row pointer, per merged
  * contact block (per contact row one for each other vertex that it shares a
- * pair with) its values and column; class 1 (update) per vertex q, d, p, r and
+ * pair with) its values (8 bytes each) and column; class 1 (update) per vertex q, d, p, r and
  * the 3x3 inverse read and p, r, z written, per preconditioner member 16 bytes
  * of ids, per SpMV block its d.q partial (4- or 8-byte reals by the list's
  * precision). */

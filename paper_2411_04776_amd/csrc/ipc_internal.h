@@ -22,7 +22,8 @@
 //     float atomics anywhere), and the SpMV applies the merged blocks.
 // In the mixed form the element Hessians and gradients, matrix values,
 // preconditioner, assembled gradient and PCG vectors are FP32 (dot products
-// accumulate in FP64); positions, Dm^-1, distances, CCD and energies stay FP64.
+// accumulate in FP64; merged contact blocks, their products and sums are FP64);
+// positions, Dm^-1, distances, CCD and energies stay FP64.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -179,8 +180,8 @@ struct SceneDev {
     int32_t *c_rows;               // rows with entries (in no particular order)
     int32_t *c_n;                  // blocks of a row (rows with entries)
     int32_t *c_col;                // column of a block
-    void *c_val;                   // its 9 values
-    void *c_q;                     // contact part of q (PCG), 4 values per vertex
+    double *c_val;                 // its 9 values
+    double *c_q;                   // contact part of q (PCG), 4 values per vertex
     double *pcg_cpart;             // its d.q partial per chunk
     double *c_grad, *c_diag;       // per vertex: contact gradient (3) and diagonal block (9)
     // multilevel additive preconditioner: nested aggregates of the free gel

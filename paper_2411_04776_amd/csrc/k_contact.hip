@@ -1225,7 +1225,7 @@ __global__ void __launch_bounds__(kBlock) k_contact_rows(Launch L)
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
     const R *ag = as<R>(S.act_g), *aH = as<R>(S.act_H);
-    R *cv = as<R>(S.c_val);
+    double *cv = S.c_val;
     const int64_t cap = S.act_cap;
     const int tid = (int)threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int nrow = L.out[s].n_crow, nblk = blocks_of(L, s);
@@ -1323,7 +1323,7 @@ __global__ void __launch_bounds__(kBlock) k_contact_rows(Launch L)
                     const int b = o + (o >= a ? 1 : 0);
                     acc += (double)aH[144 * (int64_t)(src >> 2) + (3 * a + c / 3) * 12 + 3 * b + c % 3];
                 }
-                cv[9 * (3 * (int64_t)e0 + out + j) + c] = (R)acc;
+                cv[9 * (3 * (int64_t)e0 + out + j) + c] = acc;
             }
             out += nu;
             __syncthreads();

@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(solo_threads(sizeof(R), PAIR), 1) k_pcg_solo(L
     const int64_t cap = S.act_cap;
     const auto cl = glob((const int32_t *)S.c_list), av = glob((const int32_t *)S.act_v);
     const auto H = glob((const R *)as<R>(S.act_H));
-    const auto Yg = glob(as<R>(S.c_val));  // products past the LDS: this solve reads no merged block
+    const auto Yg = glob(reinterpret_cast<R *>(S.c_val));  // products past the LDS: this solve reads no merged block
 
     // ---- this thread's matrix row, or its stream of one (slot k of the thread: part + RT * k)
     const int part = RT == 2 ? tid & 1 : 0;

@@ -309,11 +309,12 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
     // what the loop needs of the view, read here: after the kernel's first
     // store the compiler would read it by vector loads, a memory round trip each
     const Partials P_dq(S.team_ll, T), P_rz(S.team_ll + 2 * (size_t)T, T);
-    const XVec<R> Z(S.team_z, S.n), Q(S.team_q, S.n), C(S.c_q, S.n), DA(S.team_dA, S.n), DB(S.team_dB, S.n);
+    const XVec<R> Z(S.team_z, S.n), Q(S.team_q, S.n), DA(S.team_dA, S.n), DB(S.team_dB, S.n);
+    const XVec<double> C(S.c_q, S.n);
     R *const Mi = as<R>(S.Minv), *const Bv = as<R>(S.bval), *const Sol = as<R>(S.sol);
     uint16_t *const Lc = S.team_lcol;
     int32_t *const Hl = S.team_hlist;
-    const auto Cv = glob((const R *)as<R>(S.c_val));
+    const auto Cv = glob((const double *)S.c_val);
     const auto Cc = glob((const int32_t *)S.c_col);
     const int n = S.n, maxit = S.pcg_maxit;
     const double tol2 = S.pcg_tol2;
@@ -439,7 +440,8 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
     const bool contact = L.out[s].n_crow > 0;
     bool touched = false, vtouched[V];
     int ncrow = 0, hrows = 0;
-    R cA[9], cd[3], cown[3];
+    double cA[9];
+    R cd[3], cown[3];
     int ccol = 0, crow = 0;
     bool chas = false, cteam = false;  // the lane holds a block, an item
 #pragma unroll
@@ -447,7 +449,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
 #pragma unroll
     for (int c = 0; c < 3; ++c) cd[c] = cown[c] = R(0);
 #pragma unroll
-    for (int c = 0; c < 9; ++c) cA[c] = R(0);
+    for (int c = 0; c < 9; ++c) cA[c] = 0.0;
     if (tid == 0) {
         s_ok = 1;
     }
@@ -474,7 +476,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                     const int b = clist[h].base + (chas ? j : 0);
                     ccol = chas ? Cc[b] : crow;
 #pragma unroll
-                    for (int e = 0; e < 9; ++e) cA[e] = chas ? Cv[9 * (int64_t)b + e] : R(0);
+                    for (int e = 0; e < 9; ++e) cA[e] = chas ? Cv[9 * (int64_t)b + e] : 0.0;
                 }
                 at += k;
             }
@@ -739,7 +741,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
         }
         // contact rows: the held items, and the rows that are not held as the
         // launched form does, with directions from memory
-        auto put_c = [&](int v, const R (&y)[3]) { C.store(v, y, tag); };
+        auto put_c = [&](int v, const double (&y)[3]) { C.store(v, y, tag); };
         auto items = [&]() {
             R zv[3];
             XVec<R>::get(zc, zv);
@@ -806,9 +808,9 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                 for (int i = i0; i < i1; ++i)
 #pragma unroll
                     for (int c = 0; c < 3; ++c) a[c] += s_item[i][c];
-                const R q[3] = {(R)a[0], (R)a[1], (R)a[2]}, o[3] = {s_own[i0][0], s_own[i0][1], s_own[i0][2]};
-                put_c(clist[h].row, q);
-                t += contact_dot(o, q);
+                const R o[3] = {s_own[i0][0], s_own[i0][1], s_own[i0][2]};
+                put_c(clist[h].row, a);
+                t += contact_dot(o, a);
             }
             return t;
         };
@@ -892,30 +894,52 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             if (contact) a = a + cdq;
             P_dq.put(w, a, (uint32_t)it);
         }
-        // q at the units' vertices
-        typename XVec<R>::Raw qr[V], cr[V];
-        auto products = [&]() {
+        // q at the units' vertices and its contact part where there is one (with
+        // two vertices a thread one after the other: both held too many registers)
+        R qv[V][3];
+        auto fetch = [&](const auto &X, const bool (&on)[V], auto &x) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                if (vid[v] >= 0) Q.load(vid[v], qr[v]);
-                if (vtouched[v]) C.load(vid[v], cr[v]);
-            }
+            for (int v = 0; v < V; ++v)
+                if (on[v]) X.load(vid[v], x[v]);
+        };
+        auto there = [&](const auto &X, const bool (&on)[V], auto &x) {
             for (int k = 0;; ++k) {
                 bool all = true;
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    if (vid[v] >= 0 && !XVec<R>::is(qr[v], tag)) {
-                        Q.load(vid[v], qr[v]);
+                for (int v = 0; v < V; ++v)
+                    if (on[v] && !X.is(x[v], tag)) {
+                        X.load(vid[v], x[v]);
                         all = false;
                     }
-                    if (vtouched[v] && !XVec<R>::is(cr[v], tag)) {
-                        C.load(vid[v], cr[v]);
-                        all = false;
-                    }
-                }
                 if (all) return true;
                 if (k == kTeamPoll) return false;
             }
+        };
+        auto products = [&]() {
+            typename XVec<R>::Raw xq[V];
+            XVec<double>::Raw xc[V];
+            bool on[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) on[v] = vid[v] >= 0;
+            fetch(Q, on, xq);
+            if (V == 1 && contact) fetch(C, vtouched, xc);
+            bool all = there(Q, on, xq);
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (on[v]) XVec<R>::get(xq[v], qv[v]);
+            if (contact) {
+                if (V > 1) fetch(C, vtouched, xc);
+                all &= there(C, vtouched, xc);
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (vtouched[v]) {
+                        double qc[3];
+                        XVec<double>::get(xc[v], qc);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) qv[v][c] = (R)((double)qv[v][c] + qc[c]);
+                    }
+            }
+            return all;
         };
         if constexpr (RT == 2) load_inverse();
         double dqt;
@@ -927,14 +951,6 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
 #pragma unroll
         for (int v = 0; v < V; ++v)
             if (vid[v] >= 0) {
-                R qv[3];
-                XVec<R>::get(qr[v], qv);
-                if (vtouched[v]) {
-                    R qc[3];
-                    XVec<R>::get(cr[v], qc);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) qv[c] += qc[c];
-                }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if constexpr (PMEM) {
@@ -943,7 +959,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                     } else {
                         p[v][c] = p[v][c] + alpha * d[v][c];
                     }
-                    r[v][c] = r[v][c] - alpha * qv[c];
+                    r[v][c] = r[v][c] - alpha * qv[v][c];
                 }
             }
         precondition((uint32_t)it + 1u);

@@ -254,15 +254,14 @@ __global__ void __launch_bounds__(kRowsPerBlock * LPR) k_pcg_A(Launch L, int it,
                 for (int k = 0; k < 3; ++k) d[k] = bon ? x.z[k] + rb * x.d[k] : x.z[k];
             }
         } dir{z, dold, rb, bon};
-        auto put = [&](int v, const R (&y)[3]) {
-            for (int k = 0; k < 3; ++k) as<R>(S.c_q)[4 * (int64_t)v + k] = y[k];
+        auto put = [&](int v, const double (&y)[3]) {
+            for (int k = 0; k < 3; ++k) S.c_q[4 * (int64_t)v + k] = y[k];
         };
         double t_dq = 0.0;
         for (int skip = 0;; skip += kPassRows) {
             const int n = chunk_contact_rows<NT, kPassRows>(S, c, skip, clist, ccnt), m = min(n, kPassRows);
             const auto cc = glob((const int32_t *)S.c_col);
-            contact_rows<NT, R>(glob((const R *)as<R>(S.c_val)), cc, clist, 0, m, t, dir, put,
-                                cdot);
+            contact_rows<NT, R>(glob((const double *)S.c_val), cc, clist, 0, m, t, dir, put, cdot);
             __syncthreads();
             contact_dots(cdot, m, t_dq);
             if (n <= kPassRows) break;
@@ -327,7 +326,7 @@ __device__ __forceinline__ void pcg_vertex_load(const SceneDev &S, int i, const 
         v.r[c] = r[3 * i + c];
     }
     if (glob(S.c_ptr)[i + 1] > glob(S.c_ptr)[i])
-        for (int c = 0; c < 3; ++c) v.q[c] += glob(as<R>(S.c_q))[4 * (int64_t)i + c];
+        for (int c = 0; c < 3; ++c) v.q[c] = (R)((double)v.q[c] + glob(S.c_q)[4 * (int64_t)i + c]);
     for (int k = 0; k < 9; ++k) v.M[k] = Mi[9 * i + k];
 }
 
@@ -695,7 +694,7 @@ __global__ void __launch_bounds__(kBlock) k_spmv_rows(Launch L)
 {
     int lb, s = scene_of_block(L, lb);
     const SceneDev &S = *L.sc[s];
-    const R *v = as<R>(S.dB), *cv = as<R>(S.c_val);
+    const R *v = as<R>(S.dB);
     R *y = as<R>(S.q);
     int row = lb * kRowsPerBlock + (int)threadIdx.x;
     if (row >= S.n) return;
@@ -706,8 +705,9 @@ __global__ void __launch_bounds__(kBlock) k_spmv_rows(Launch L)
     if (S.c_ptr[row + 1] > S.c_ptr[row]) {
         const int64_t base = 3 * (int64_t)S.c_ptr[row];
         for (int j = 0; j < S.c_n[row]; ++j) {
-            const R *h = cv + 9 * (base + j), *d = v + 3 * (int64_t)S.c_col[base + j];
-            for (int i = 0; i < 3; ++i) o[i] += (double)(h[3 * i] * d[0] + h[3 * i + 1] * d[1] + h[3 * i + 2] * d[2]);
+            const double *h = S.c_val + 9 * (base + j);
+            const R *d = v + 3 * (int64_t)S.c_col[base + j];
+            for (int i = 0; i < 3; ++i) o[i] += h[3 * i] * (double)d[0] + h[3 * i + 1] * (double)d[1] + h[3 * i + 2] * (double)d[2];
         }
     }
     for (int c = 0; c < 3; ++c) y[3 * row + c] = (R)o[c];
@@ -1204,7 +1204,7 @@ static void run_pcg_launched(Batch &b, const std::vector<uint8_t> &on, std::vect
 static double pcg_bytes_a(const Scene &s, const SceneOut &o)
 {
     const double rs = s.prm.precision == IPC_MIXED ? 4.0 : 8.0;
-    return (9 * rs + 4) * ((double)s.nnzb + (double)o.n_cblk) + (12 * rs + 4) * (double)s.h.n;
+    return (9 * rs + 4) * (double)s.nnzb + (9 * 8 + 4) * (double)o.n_cblk + (12 * rs + 4) * (double)s.h.n;
 }
 // and of one B launch: per vertex q, d, p, r and the 3x3 inverse read and
 // p, r, z written (30 reals); per preconditioner member its vertex id and

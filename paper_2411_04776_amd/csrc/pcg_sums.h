@@ -91,6 +91,10 @@ __device__ __forceinline__ int chunk_contact_rows(const SceneDev &S, int c, int 
 // C_j d(col_j): kRowTeam blocks at a time (an item) summed by the xor tree of
 // kRowTeam lanes, then the row's items in order.
 //
+// The merged blocks, their products and the sums are FP64 in either precision:
+// a merged block is a sum over pairs, and rounded to FP32 it would lose what
+// the pairs' separate products keep.
+//
 // contact_rows: rows h0, h0 + 1, ... by a block of NT threads, a team of
 // kRowTeam lanes each, or a wavefront (four items at a time) for rows of more
 // than kRowLong blocks: a coarse indenter's vertex has hundreds. cv, cc: the
@@ -98,23 +102,23 @@ __device__ __forceinline__ int chunk_contact_rows(const SceneDev &S, int c, int 
 // at a vertex; put(row,
 // sums) on one lane of each row, the row's d . sums in dot[].
 template <class R>
-__device__ __forceinline__ void contact_item(bool has, const R (&A)[9], const R (&d)[3], double (&t)[3])
+__device__ __forceinline__ void contact_item(bool has, const double (&A)[9], const R (&d)[3], double (&t)[3])
 {
-    R y0 = R(0), y1 = R(0), y2 = R(0);
-    block_fma(A, d[0], d[1], d[2], y0, y1, y2);
-    t[0] = has ? (double)y0 : 0.0;
-    t[1] = has ? (double)y1 : 0.0;
-    t[2] = has ? (double)y2 : 0.0;
+    double y0 = 0.0, y1 = 0.0, y2 = 0.0;
+    block_fma(A, (double)d[0], (double)d[1], (double)d[2], y0, y1, y2);
+    t[0] = has ? y0 : 0.0;
+    t[1] = has ? y1 : 0.0;
+    t[2] = has ? y2 : 0.0;
 #pragma unroll
     for (int c = 0; c < 3; ++c) t[c] = lane_add<1>(lane_add<2>(lane_add<4>(lane_add<8>(t[c]))));
 }
 template <class R>
-__device__ __forceinline__ double contact_dot(const R (&own)[3], const R (&q)[3])
+__device__ __forceinline__ double contact_dot(const R (&own)[3], const double (&q)[3])
 {
-    return (double)own[0] * (double)q[0] + (double)own[1] * (double)q[1] + (double)own[2] * (double)q[2];
+    return (double)own[0] * q[0] + (double)own[1] * q[1] + (double)own[2] * q[2];
 }
 template <int NT, class R, class D, class P>
-__device__ __forceinline__ void contact_rows(gptr<const R> cv, gptr<const int32_t> cc, const CRow *list, int h0, int n,
+__device__ __forceinline__ void contact_rows(gptr<const double> cv, gptr<const int32_t> cc, const CRow *list, int h0, int n,
                                              int tid, D &dir, P put, double *dot)
 {
     static_assert(kRowTeam == 16, "the items' tree");
@@ -131,8 +135,8 @@ __device__ __forceinline__ void contact_rows(gptr<const R> cv, gptr<const int32_
             for (int j = u; j - u < cr.n; j += W) {
                 const bool has = j < cr.n;
                 const auto at = cv + 9 * ((int64_t)cr.base + (has ? j : 0));
-                R A[9], d[3];
-                double t[3];
+                R d[3];
+                double A[9], t[3];
 #pragma unroll
                 for (int e = 0; e < 9; ++e) A[e] = at[e];
                 auto rc = dir.start(col);
@@ -154,10 +158,9 @@ __device__ __forceinline__ void contact_rows(gptr<const R> cv, gptr<const int32_
                 }
             }
             if (u == 0) {
-                const R q[3] = {(R)acc[0], (R)acc[1], (R)acc[2]};
                 dir.end(cr.row, ro, own);
-                put(cr.row, q);
-                dot[h] = contact_dot(own, q);
+                put(cr.row, acc);
+                dot[h] = contact_dot(own, acc);
             }
         }
     };

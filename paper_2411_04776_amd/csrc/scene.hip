@@ -405,13 +405,13 @@ void grow_active(Scene &s, int64_t need)
     Staged st(s);
     int32_t *ni = st.get<int32_t>(nc), *nv = st.get<int32_t>(4 * (size_t)nc);
     void *ng = st.get_bytes(12 * (size_t)nc * rs), *nh = st.get_bytes(144 * (size_t)nc * rs);
-    void *ncv = st.get_bytes(9 * 12 * (size_t)nc * rs);
+    double *ncv = st.get<double>(9 * 12 * (size_t)nc);
     int32_t *nl = st.get<int32_t>(4 * (size_t)nc), *nr = st.get<int32_t>(4 * (size_t)nc);
     int32_t *nt = st.get<int32_t>(4 * (size_t)nc), *ncr = st.get<int32_t>(4 * (size_t)nc);
     int32_t *ncc = st.get<int32_t>(12 * (size_t)nc);
     st.commit();
     for (void *old : {(void *)H.act_idx, (void *)H.act_v, H.act_g, H.act_H, (void *)H.c_list, (void *)H.c_row,
-                      (void *)H.c_tmp, (void *)H.c_rows, (void *)H.c_col, H.c_val})
+                      (void *)H.c_tmp, (void *)H.c_rows, (void *)H.c_col, (void *)H.c_val})
         dfree(s, old);
     H.c_tmp = nt;
     H.c_rows = ncr;
@@ -1039,7 +1039,7 @@ static int32_t build_scene(Scene &s, const ipc_scene_desc &d)
     build_team(s, slice_ptr, bcol);
     H.pcg_cpart = dalloc<double>(s, H.team_T);
     H.c_n = dalloc<int32_t>(s, n);
-    H.c_q = dalloc_bytes(s, 4 * (size_t)n * rs);
+    H.c_q = dalloc<double>(s, 4 * (size_t)n);
     H.c_grad = dalloc<double>(s, 3 * (size_t)n);
     H.c_diag = dalloc<double>(s, 9 * (size_t)n);
     if (H.mas_levels > 0) {
@@ -2183,11 +2183,11 @@ int64_t ipc_scene_footprint_bytes(const ipc_scene_desc *d)
     if (!check_desc(d)) return -1;
     int64_t n = (int64_t)d->n_verts + d->n_ind_verts, m = d->n_tets;
     int64_t rs = d->precision == IPC_MIXED ? 4 : 8;
-    int64_t per_vertex = 8 * (3 * 9 + 1 + 12) + rs * (3 * 8 + 9 + 4 * 5) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers), one scalar, the contact gradient and diagonal block; the PCG vectors in R, five of them padded
+    int64_t per_vertex = 8 * (3 * 9 + 1 + 12 + 4) + rs * (3 * 8 + 9 + 4 * 4) + 4 * 4 + 1;  // nine FP64 3-vectors (the last the target multipliers), one scalar, the contact gradient and diagonal block and the contact part of q; the PCG vectors in R, four of them padded
     int64_t per_tet = 4 * 4 + 8 * 10 + rs * (12 + 90) + (4 * 16 + 4 * 4) * 4 / 3;  // the lists padded
     int64_t bell = n * 16 * (9 * rs + 4 + 2);
     int64_t surf = 4 * (int64_t)std::pow((double)d->n_verts, 2.0 / 3.0) + d->n_ind_verts + 2 * d->n_ind_tris;
-    int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * (156 + 108) + 4 * 33);
+    int64_t contact = surf * (6 * 8 * 3 + 64 * 4 * 3 + 8 * 16 + 4 * kQueryKeep * kLanesQ) + surf / 4 * (rs * 156 + 8 * 108 + 4 * 33);
     return n * per_vertex + m * per_tet + bell + contact + (8 << 20);
 }
 
