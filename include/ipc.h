@@ -356,6 +356,13 @@ IPC_API int32_t ipcx_matrix_info(const ipc_scene *s, int64_t *out);
  * of levels 0..2, out[5] the largest group's members, out[6] the largest
  * group's aggregates, out[7] members (free gel vertices). */
 IPC_API int32_t ipcx_precond_info(const ipc_scene *s, int64_t *out);
+/* Forms of the PCG solve: out[0] the scene's resident layout (0 narrow, 1 wide
+ * workgroups, 2 and 3 one workgroup with two threads or one a matrix row; -1 if
+ * it has none), out[1] its workgroups, and of the solves so far out[2] the ones
+ * that ran in one resident launch, out[3] the ones launched in the compact
+ * layout (workgroups that share CUs), out[4] the ones that their team gave up,
+ * out[5] the ones that ran iteration by iteration (given-up ones among them). */
+IPC_API int32_t ipcx_pcg_info(const ipc_scene *s, int64_t *out);
 /* The launch and grouping choices the scene took at creation from the
  * autotuner's file ($IPC_TUNING_FILE, else tuning.json beside the library;
  * built-in defaults without one): out[0] SpMV one-thread-per-row threshold

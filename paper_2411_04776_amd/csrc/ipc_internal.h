@@ -357,6 +357,9 @@ class Scene {
     int step_index = 0;
     std::atomic<bool> busy{false};  // a step, read or hook holds the scene
     int last_pcg_iters = 0;
+    // solves so far: in one resident launch (of these in the compact layout),
+    // given up by their team, and iteration by iteration (the given-up ones among them)
+    int64_t pcg_resident = 0, pcg_compact = 0, pcg_given_up = 0, pcg_launched = 0;
     Tuning tune{};         // launch and grouping choices of the scene's size class
     bool sw_ok = false;    // the swept list holds every static pair at the current x
     int64_t sw_n = 0;      // its length

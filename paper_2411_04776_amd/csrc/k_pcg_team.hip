@@ -1039,6 +1039,7 @@ void launch_pcg_team(Batch &b, const std::vector<uint8_t> &on)
         for (size_t i = 0; i < ns; ++i) {
             const SceneDev &h = b.sc[i]->h;
             if (!on[i] || variant(i) != v) continue;
+            b.sc[i]->pcg_compact += v == kTeamCompact;
             nb[i] = h.team_T;
             lds = std::max(lds, team_lds_bytes(v, h.team_H, h.team_A, rs));
         }

@@ -1243,10 +1243,12 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
             if (!team[i] && !solo[i]) continue;
             const SceneOut &o = b.h_out[i];
             if (!o.pcg_done || o.pcg_fail) {
+                b.sc[i]->pcg_given_up++;
                 rest[i] = 1;
                 any_rest = true;
                 continue;
             }
+            b.sc[i]->pcg_resident++;
             iters[i] = o.pcg_iters;
             hit_cap[i] = o.pcg_done != 1;
             b.sc[i]->last_pcg_iters = o.pcg_iters;
@@ -1425,6 +1427,7 @@ static void run_pcg_launched(Batch &b, const std::vector<uint8_t> &on, std::vect
         iters[i] = b.h_out[i].pcg_done ? b.h_out[i].pcg_iters : b.sc[i]->h.pcg_maxit;
         hit_cap[i] = b.h_out[i].pcg_done != 1;
         b.sc[i]->last_pcg_iters = iters[i];
+        b.sc[i]->pcg_launched++;
     }
 }
 

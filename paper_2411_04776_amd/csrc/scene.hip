@@ -3018,6 +3018,22 @@ int32_t ipcx_precond_info(const ipc_scene *s, int64_t *out)
     return IPC_OK;
 }
 
+int32_t ipcx_pcg_info(const ipc_scene *cs, int64_t *out)
+{
+    if (!cs || !out) return IPC_E_INVALID_ARG;
+    ipc_scene *s = const_cast<ipc_scene *>(cs);
+    IPC_HOOK_BEGIN(s)
+        const SceneDev &h = s->h;
+        out[0] = solo_layout(h) || h.team_fit ? h.team_variant : -1;
+        out[1] = h.team_T;
+        out[2] = s->pcg_resident;
+        out[3] = s->pcg_compact;
+        out[4] = s->pcg_given_up;
+        out[5] = s->pcg_launched;
+        return IPC_OK;
+    IPC_HOOK_END(s)
+}
+
 int32_t ipcx_set_state(ipc_scene *s, const double *x, const double *v)
 {
     if (!s) return IPC_E_INVALID_ARG;

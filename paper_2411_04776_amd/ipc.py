@@ -144,6 +144,7 @@ _SIGS = {
     "ipcx_struct_sizes": (C.c_int32, [C.POINTER(C.c_int64)]),
     "ipcx_matrix_info": (C.c_int32, [C.c_void_p, _I64]),
     "ipcx_precond_info": (C.c_int32, [C.c_void_p, _I64]),
+    "ipcx_pcg_info": (C.c_int32, [C.c_void_p, _I64]),
     "ipcx_set_state": (C.c_int32, [C.c_void_p, _D, _D]),
     "ipcx_get_state": (C.c_int32, [C.c_void_p, _D, _D]),
 }
@@ -595,6 +596,12 @@ class GelScene:
         _check(lib().ipcx_precond_info(self.ptr, o.ctypes.data_as(_I64)), "ipcx_precond_info")
         keys = ("levels", "groups", "aggs0", "aggs1", "aggs2", "max_group_members", "max_group_aggs", "members")
         return dict(zip(keys, map(int, o)))
+
+    def pcg_info(self):
+        """The resident layout of the scene's PCG solve (-1: none), its workgroups, and the solves so far by form."""
+        o = np.zeros(6, dtype=np.int64)
+        _check(lib().ipcx_pcg_info(self.ptr, o.ctypes.data_as(_I64)), "ipcx_pcg_info")
+        return dict(zip(("layout", "workgroups", "resident", "compact", "given_up", "launched"), map(int, o)))
 
     @property
     def x(self):
