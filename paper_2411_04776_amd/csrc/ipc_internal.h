@@ -360,6 +360,8 @@ class Scene {
     // solves so far: in one resident launch (of these in the compact layout),
     // given up by their team, and iteration by iteration (the given-up ones among them)
     int64_t pcg_resident = 0, pcg_compact = 0, pcg_given_up = 0, pcg_launched = 0;
+    // after f given-up solves in a row the next 2^f - 1 (at most 31) do not try
+    int team_fails = 0, team_rest = 0;
     Tuning tune{};         // launch and grouping choices of the scene's size class
     bool sw_ok = false;    // the swept list holds every static pair at the current x
     int64_t sw_n = 0;      // its length

@@ -1224,7 +1224,14 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
         if (b.h_off[kPhVert][i + 1] == b.h_off[kPhVert][i]) continue;
         const SceneDev &h = b.sc[i]->h;
         const bool one = solo_layout(h);  // such a scene has no other form
-        const bool t = one || (h.team_fit && b.sc[i]->tune.team && chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kChunkRows);
+        bool t = one || (h.team_fit && b.sc[i]->tune.team && chunk_rows_bound(*b.sc[i], b.h_out[i]) <= kChunkRows);
+        // a team that was given up competes for its CUs with other work (another
+        // stream's team): each try holds CUs while it waits, so it waits longer
+        // between tries
+        if (t && !one && b.sc[i]->team_rest > 0) {
+            b.sc[i]->team_rest--;
+            t = false;
+        }
         (one ? solo : t ? team : rest)[i] = 1;
         (t ? any_team : any_rest) = true;
     }
@@ -1244,11 +1251,14 @@ void run_pcg(Batch &b, std::vector<int> &iters, std::vector<int> &hit_cap)
             const SceneOut &o = b.h_out[i];
             if (!o.pcg_done || o.pcg_fail) {
                 b.sc[i]->pcg_given_up++;
+                b.sc[i]->team_fails = std::min(b.sc[i]->team_fails + 1, 5);
+                b.sc[i]->team_rest = (1 << b.sc[i]->team_fails) - 1;
                 rest[i] = 1;
                 any_rest = true;
                 continue;
             }
             b.sc[i]->pcg_resident++;
+            b.sc[i]->team_fails = 0;
             iters[i] = o.pcg_iters;
             hit_cap[i] = o.pcg_done != 1;
             b.sc[i]->last_pcg_iters = o.pcg_iters;

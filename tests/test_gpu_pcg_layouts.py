@@ -93,6 +93,18 @@ def test_resident_form_runs(ipc, monkeypatch, tmp_path, name):
     assert same(got, given_up)
 
 
+def test_given_up_teams_rest(ipc, monkeypatch, tmp_path):
+    """Each given-up solve doubles the number of solves until the next try: tries 1, 3, 7, 15, ... (a team whose
+    members all arrive at the same moment forms without waiting, and the count starts anew)."""
+    sc = gel((13, 11, 5), steps=4)
+    its, x, v, info = run(scene(ipc, monkeypatch, tmp_path, sc, False, team=1, team_spin=0))
+    newton = sum(i[1] for i in its)
+    print("given-up teams:", info, newton, "newton iterations", flush=True)
+    assert newton >= 7 and info["launched"] + info["resident"] == newton
+    tries = (newton + 1).bit_length() - 1
+    assert info["given_up"] == tries if info["resident"] == 0 else info["given_up"] <= tries * (info["resident"] + 1)
+
+
 # a scene with a resident form adds in its order, one without in a flat one
 @pytest.mark.parametrize("grid,mixed,layout", [((24, 26, 5), False, NARROW), ((40, 41, 6), True, NARROW),
                                                ((88, 90, 9), False, -1)])
