@@ -537,8 +537,9 @@ void run_narrow_phase(Batch &b);
 void launch_barrier(Batch &b);
 // friction set from the active pairs at x^t (after the narrow phase at x^t)
 void launch_friction_lag(Batch &b);
-// friction pairs appended after the barrier pairs, then n_pair for every scene
+// friction pairs appended after the barrier pairs
 void launch_friction(Batch &b);
+// n_pair of every scene, its contact rows, and per row the gradient and diagonal sums and the merged blocks
 void launch_contact_incidence(Batch &b);
 void run_ccd(Batch &b);
 void run_energy(Batch &b, bool trial);

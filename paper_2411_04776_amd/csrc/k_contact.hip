@@ -838,9 +838,12 @@ __device__ __forceinline__ void jacobi5(double (&U)[15], double (&V)[5][5])
 // already PSD are kept as assembled. Gauss-Newton form (S.barrier_gn): the
 // entries kappa w b''(d) gd_p gd_q, PSD and rank one as they are.
 // Bound by the chain of one pair: what lanes index by entry is in LDS, the
-// basis is orthogonalised with a component per lane, the 5x5 rotations run two
-// at a time and a 12x12 round is one pass over its 2 x 2 blocks: 241 -> 153 us
-// (130,600 vertices, mollified pairs among them), 40.7 -> 28.9 us (4,500).
+// basis is orthogonalised with a component per lane, and a 12x12 round is one
+// pass over its 2 x 2 blocks: 241 -> 171 us (130,600 vertices, mollified pairs
+// among them), 40.7 -> 34.4 us (4,500). The 5x5 rotations two at a time, the
+// dot products by lane trees and an angle without the cotangent took 153 and
+// 28.9 us, but move the last bits of every Hessian, on which the outcome of a
+// tie of closest features turns.
 template <class R>
 __global__ void __launch_bounds__(64) k_barrier(Launch L)
 {

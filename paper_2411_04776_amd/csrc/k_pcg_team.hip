@@ -23,7 +23,7 @@
 // spilled: 36.7 us an iteration at 130,600 vertices, not 25.3.
 //
 // Measured (us per iteration, launched form before -> this): 1,442 vertices
-// FP64 24 -> 8.7; 16,800 FP64 26 -> 11.1; 10,100 mixed 29 -> 12.9; 130,600
+// FP64 24 -> 8.5; 16,800 FP64 26 -> 10.4; 10,100 mixed 29 -> 12.3; 130,600
 // mixed 59 -> 25.3. A scene that one workgroup holds has a kernel of its own
 // (k_pcg_solo.hip).
 //
@@ -189,7 +189,8 @@ __device__ __forceinline__ void stores_arrived() { asm volatile("s_waitcnt vmcnt
 // in LDS, with its vertices' solution in memory; a longer row's other blocks are read again in each iteration. The
 // compact layout (FP32, 256 threads) has the narrow one's chunks, a thread a
 // row: two of its workgroups share a CU, for launches with more workgroups
-// than CUs, where the waits of one are the time of the other.
+// than CUs, where the waits of one are the time of the other. Entries 2 and 3
+// give the rows and units of the one-workgroup layouts (k_pcg_solo.hip).
 constexpr int kTeamRT[5] = {2, 1, 2, 1, 1}, kTeamV[5] = {1, 2, 2, 2, 2};
 constexpr int team_lds_slots(int variant) { return kTeamRT[variant] == 2 ? 0 : variant == kTeamCompact ? 5 : 4; }
 int team_contact_rows(int variant) { return variant == kTeamCompact ? kCompactRows : kChunkRows; }
@@ -894,63 +895,96 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
             if (contact) a = a + cdq;
             P_dq.put(w, a, (uint32_t)it);
         }
-        // q at the units' vertices and its contact part where there is one (with
-        // two vertices a thread one after the other: both held too many registers)
-        R qv[V][3];
-        auto fetch = [&](const auto &X, const bool (&on)[V], auto &x) {
+        // q at the units' vertices and its contact part where there is one (in
+        // the FP32 layouts with two vertices a thread one after the other: both
+        // held too many registers)
+        constexpr bool SPLIT = V > 1 && sizeof(R) == 4;
+        typename XVec<R>::Raw qr[V];
+        XVec<double>::Raw cr[V];
+        auto fetch_both = [&]() {
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (on[v]) X.load(vid[v], x[v]);
-        };
-        auto there = [&](const auto &X, const bool (&on)[V], auto &x) {
+            for (int v = 0; v < V; ++v) {
+                if (vid[v] >= 0) Q.load(vid[v], qr[v]);
+                if (vtouched[v]) C.load(vid[v], cr[v]);
+            }
             for (int k = 0;; ++k) {
                 bool all = true;
 #pragma unroll
-                for (int v = 0; v < V; ++v)
-                    if (on[v] && !X.is(x[v], tag)) {
-                        X.load(vid[v], x[v]);
+                for (int v = 0; v < V; ++v) {
+                    if (vid[v] >= 0 && !XVec<R>::is(qr[v], tag)) {
+                        Q.load(vid[v], qr[v]);
                         all = false;
                     }
+                    if (vtouched[v] && !XVec<double>::is(cr[v], tag)) {
+                        C.load(vid[v], cr[v]);
+                        all = false;
+                    }
+                }
                 if (all) return true;
                 if (k == kTeamPoll) return false;
             }
         };
-        auto products = [&]() {
-            typename XVec<R>::Raw xq[V];
-            XVec<double>::Raw xc[V];
-            bool on[V];
+        auto with_contact = [&](const XVec<double>::Raw &x, R (&q)[3]) {
+            double qc[3];
+            XVec<double>::get(x, qc);
 #pragma unroll
-            for (int v = 0; v < V; ++v) on[v] = vid[v] >= 0;
-            fetch(Q, on, xq);
-            if (V == 1 && contact) fetch(C, vtouched, xc);
-            bool all = there(Q, on, xq);
-#pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (on[v]) XVec<R>::get(xq[v], qv[v]);
-            if (contact) {
-                if (V > 1) fetch(C, vtouched, xc);
-                all &= there(C, vtouched, xc);
-#pragma unroll
-                for (int v = 0; v < V; ++v)
-                    if (vtouched[v]) {
-                        double qc[3];
-                        XVec<double>::get(xc[v], qc);
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) qv[v][c] = (R)((double)qv[v][c] + qc[c]);
-                    }
-            }
-            return all;
+            for (int c = 0; c < 3; ++c) q[c] = (R)((double)q[c] + qc[c]);
         };
         if constexpr (RT == 2) load_inverse();
         double dqt;
         if (!total(P_dq, (uint32_t)it, dqt)) break;
         if constexpr (RT == 1) load_inverse();  // not earlier: registers are short
-        if (!products()) s_ok = 0;              // seen before the next partial is published
+        // a wait that ran out is seen before the next partial is published
+        R qs[V][3];
+        if constexpr (SPLIT) {
+            auto fetch = [&](const auto &X, const bool (&on)[V], auto &x) {
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (on[v]) X.load(vid[v], x[v]);
+                for (int k = 0;; ++k) {
+                    bool all = true;
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        if (on[v] && !X.is(x[v], tag)) {
+                            X.load(vid[v], x[v]);
+                            all = false;
+                        }
+                    if (all) return true;
+                    if (k == kTeamPoll) return false;
+                }
+            };
+            auto one_by_one = [&]() {
+                typename XVec<R>::Raw xq[V];
+                XVec<double>::Raw xc[V];
+                bool on[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v) on[v] = vid[v] >= 0;
+                bool all = fetch(Q, on, xq);
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (on[v]) XVec<R>::get(xq[v], qs[v]);
+                if (contact) {
+                    all &= fetch(C, vtouched, xc);
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        if (vtouched[v]) with_contact(xc[v], qs[v]);
+                }
+                return all;
+            };
+            if (!one_by_one()) s_ok = 0;
+        } else if (!fetch_both()) {
+            s_ok = 0;
+        }
         // p += alpha d, r -= alpha q
         const R alpha = (R)(rz / dqt);
 #pragma unroll
         for (int v = 0; v < V; ++v)
             if (vid[v] >= 0) {
+                R(&qv)[3] = qs[v];
+                if constexpr (!SPLIT) {
+                    XVec<R>::get(qr[v], qv);
+                    if (vtouched[v]) with_contact(cr[v], qv);
+                }
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if constexpr (PMEM) {
@@ -959,7 +993,7 @@ __global__ void __launch_bounds__(team_threads(VARIANT, sizeof(R)), VARIANT == k
                     } else {
                         p[v][c] = p[v][c] + alpha * d[v][c];
                     }
-                    r[v][c] = r[v][c] - alpha * qv[v][c];
+                    r[v][c] = r[v][c] - alpha * qv[c];
                 }
             }
         precondition((uint32_t)it + 1u);

@@ -1,9 +1,12 @@
-// k_solver.hip -- block-Jacobi PCG, vector kernels and segmented scans, all
-// over a list of scenes (one launch per phase for every scene in the list).
+// k_solver.hip -- the launched form of PCG, vector kernels and segmented scans,
+// all over a list of scenes (one launch per phase for every scene in the list).
 //
 // PCG solves H p = -g from p = 0 and stops when the preconditioned residual
-// r^T M^-1 r reaches pcg_tol^2 times its initial value. Each iteration is two
-// kernels with every scalar kept on the device:
+// r^T M^-1 r reaches pcg_tol^2 times its initial value. A scene whose
+// workgroups fit the chip is solved in one launch (k_pcg_team.hip; k_pcg_solo.hip
+// for the smallest). The form here is for the others, and for a solve whose
+// team did not form. Each iteration is two kernels with every scalar kept on
+// the device:
 //   A(it): every wavefront of a scene reduces that scene's r.z partials of
 //          the previous iteration in a fixed order (all agree bit for bit;
 //          no block barrier before the real work) and decides the stop;
@@ -13,11 +16,8 @@
 //          d.q partial;
 //   B(it): every wavefront reduces the scene's d.q partials, alpha = rz / dq,
 //          then p += alpha d, r -= alpha q, z = M^-1 r and the r.z partials.
-// Kernel boundaries cost ~3 us on MI355X against 8-28 us for a cooperative
-// grid-wide barrier, so an iteration is two launches rather than one
-// persistent kernel. The host launches chunks of iterations and reads the
-// per-scene done flags once per chunk; finished scenes turn the remaining
-// launches into no-ops.
+// The host launches chunks of iterations and reads the per-scene done flags
+// once per chunk; finished scenes turn the remaining launches into no-ops.
 #include <algorithm>
 
 #include "device_util.h"
@@ -493,9 +493,8 @@ __device__ __forceinline__ double pcg_vertex_start(const SceneDev &S, int i, R z
     return rz;
 }
 
-// LDS of an update block: the group's members' r, contact sums and
-// corrections, the aggregate sums, the list of rows for the teams, and the
-// group's level ranges (block-uniform; read in the level loop)
+// LDS of an update block: the group's members' r, then the corrections, the
+// aggregate sums, and the group's level ranges (block-uniform)
 template <class R>
 struct BShared {
     R rm[kMasCapM][3];
@@ -575,7 +574,7 @@ __device__ void pcg_B_group(const Launch &L, const SceneDev &S, int s, int grp, 
             bsum += a1 - a0;
         }
     }
-    if (tid < kMasLevels) {  // the level loop reads these from LDS (block-uniform)
+    if (tid < kMasLevels) {  // read back block-uniform
         sh.lv[tid][0] = lvl(gbase, tid);
         sh.lv[tid][1] = lvl(ga1, tid) - lvl(ga0, tid);
         sh.first[tid] = lvl(ga0, tid);
@@ -1193,9 +1192,9 @@ void launch_hess_apply(Batch &b)
 }
 
 // PCG for every scene with blocks in the kPhVert map (the active-pair counts
-// come from the last read-back of the narrow phase): the scenes whose team
-// fits in one resident launch, the others (and a team that did not form)
-// iteration by iteration.
+// come from the last read-back of the narrow phase): the scenes that one
+// workgroup holds or whose team fits in one resident launch each, the others
+// (and a team that did not form) iteration by iteration.
 static void run_pcg_launched(Batch &b, const std::vector<uint8_t> &on, std::vector<int> &iters, std::vector<int> &hit_cap);
 
 // algorithmic bytes of one scene in one A launch: every stored 3x3 block

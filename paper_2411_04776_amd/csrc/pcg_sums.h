@@ -1,6 +1,7 @@
 // pcg_sums.h -- the order in which a PCG solve's sums over a scene are formed,
 // shared by the resident form (k_pcg_team.hip) and the launched form
-// (k_solver.hip), so a solve gives the same bits in either.
+// (k_solver.hip), so a solve gives the same bits in either. (A scene that one
+// workgroup holds has an order and a kernel of its own, k_pcg_solo.hip.)
 //
 // A scene is cut into team_T chunks: chunk c holds team_rows consecutive
 // matrix rows, team_units consecutive update units, and the contact rows

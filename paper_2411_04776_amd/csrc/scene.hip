@@ -2845,7 +2845,7 @@ int32_t ipcx_barrier(ipc_scene *s, const double *x, int64_t cap, int32_t *kind, 
                                    s->stream));
             download_real(*s, gg.data(), s->h.act_g, gg.size());
             download_real(*s, hh.data(), s->h.act_H, hh.size());
-            // component-major (component * act_cap + pair) to pair-major
+            // vertex ids and gradients from component-major (component * act_cap + pair) to pair-major
             for (int64_t k = 0; k < w; ++k) {
                 if (kind) kind[k] = type[idx[k]];
                 if (v4)
