@@ -42,14 +42,13 @@ GOLDEN = os.path.join(ROOT, "tests", "golden")
 C3_SAMPLE = tuple(range(0, 256, 16))   # the 16 scenes compared with the oracle
 
 PCG_SOURCES = ("paper_2411_04776_amd/csrc/k_solver.hip", "paper_2411_04776_amd/csrc/k_pcg_team.hip",
-               "paper_2411_04776_amd/csrc/pcg_sums.h",
+               "paper_2411_04776_amd/csrc/k_pcg_solo.hip", "paper_2411_04776_amd/csrc/pcg_sums.h",
                "paper_2411_04776_amd/csrc/device_util.h", "paper_2411_04776_amd/csrc/ipc_internal.h")
 ELASTIC_SOURCES = ("paper_2411_04776_amd/csrc/k_elastic.hip", "paper_2411_04776_amd/csrc/device_util.h",
                    "paper_2411_04776_amd/csrc/ipc_internal.h")
 TRAFFIC_PROFILES = {
-    "c3": {"k_pcg_A": "profiles/k_pcg_A_batch256_mixed_pmc.md", "k_pcg_B": "profiles/k_pcg_B_batch256_mixed_pmc.md"},
-    "c2": {"k_pcg_A": "profiles/k_pcg_A_c2_fp64_pmc.md", "k_pcg_B": "profiles/k_pcg_B_c2_fp64_pmc.md"},
-    "c5": {"k_pcg_A": "profiles/k_pcg_A_c5_mixed_pmc.md", "k_pcg_B": "profiles/k_pcg_B_c5_mixed_pmc.md"},
+    w: {k: f"profiles/{k}_{tag}_pmc.md" for k in ("k_pcg_team", "k_pcg_A", "k_pcg_B")}
+    for w, tag in (("c3", "batch256_mixed"), ("c2", "c2_fp64"), ("c5", "c5_mixed"))
 }
 VALU_PROFILE = "profiles/assembly_c5_mixed_valu.md"
 
@@ -153,23 +152,28 @@ def pct(v, q):
 
 
 def pcg_roofline(prof, workload, note):
-    """Roofline objects of the two PCG kernels from event timings: prof maps
-    kernel name -> (timed launches, summed ms, summed algorithmic bytes). A
+    """Roofline objects of the two PCG kernel classes from event timings: prof
+    maps class -> (timed launches, summed ms, summed algorithmic bytes). A
     launch of resident solves counts in the first class, with the bytes of all
-    iterations (most of which stay on the chip); where every solve is resident
-    the second class is empty."""
+    iterations; where the solves are resident, all but a few (of scenes with
+    more contact rows than a workgroup takes), the second class is all but
+    empty. A resident solve keeps most of those bytes on the chip and is bound by the
+    exchange between its workgroups, so its rate is no share of HBM's: frac is
+    None there, and the traffic that the counters read stands beside it."""
     out = {}
-    resident = prof["k_pcg_B"][3] == 0
-    for kname, what in (("k_pcg_A", "k_pcg_team: whole resident PCG solves" if resident else
-                         "PCG SpMV + direction update, whole resident solves"),
-                        ("k_pcg_B", "PCG update + multilevel preconditioner")):
-        n, ms, by, n_all, by_all = prof[kname]
+    resident = prof["k_pcg_B"][4] <= 0.01 * prof["k_pcg_A"][4]  # the second class runs for launched solves alone
+    for kname, key, what in (("k_pcg_team" if resident else "k_pcg_A", "k_pcg_A", "whole resident PCG solves" if resident
+                              else "PCG SpMV + direction update, whole resident solves"),
+                             ("k_pcg_B", "k_pcg_B", "PCG update + multilevel preconditioner")):
+        n, ms, by, n_all, by_all = prof[key]
         avg_s = ms / 1e3 / max(n, 1)
         bpl = by / max(n, 1)
         ach = bpl / avg_s / 1e9 if avg_s > 0 else 0.0
         tr, ratio = measured_traffic(TRAFFIC_PROFILES[workload][kname])
-        out[kname] = {"kernel": f"{kname} ({what})", "bound": "hbm", "achieved": round(ach, 1),
-                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
+        on_chip = kname == "k_pcg_team"
+        out[kname] = {"kernel": f"{kname} ({what})", "bound": "exchange between workgroups" if on_chip else "hbm",
+                      "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                      "frac": None if on_chip else round(ach / HBM_PEAK_GBS, 4),
                       "traffic": tr, "traffic_over_algorithmic": ratio,
                       "traffic_source": TRAFFIC_PROFILES[workload][kname], "bytes_per_launch": int(bpl),
                       "bytes_note": "algorithmic; a resident solve keeps its vectors on the chip, so its rate is "
@@ -406,10 +410,7 @@ def c5_leg(args, ipc, scenes, torch, np):
            "newton_iters_per_s": round(newton / el, 2), "pcg_iters_per_newton": round(pcg / max(newton, 1), 1),
            "latency_ms": {"p50": pct(lat, 50), "p99": pct(lat, 99)}, "statuses": {str(k): v for k, v in st_codes.items()},
            "peak_device_bytes": int(peak),
-           "pcg_hbm_gbs": {"k_pcg_A": roof["achieved"] if roof["kernel"].startswith("k_pcg_A") else
-                           roof["other_pcg_kernel"]["achieved"],
-                           "k_pcg_B": roof["achieved"] if roof["kernel"].startswith("k_pcg_B") else
-                           roof["other_pcg_kernel"]["achieved"]},
+           "pcg_algorithmic_gbs": {k["kernel"].split(" ")[0]: k["achieved"] for k in (roof, roof["other_pcg_kernel"])},
            "roofline": roof,
            "assembly_valu": valu, "assembly_valu_source": VALU_PROFILE}
     log(f"config 5: {out['env_steps_per_s']} env-steps/s, p50 {out['latency_ms']['p50']} ms")

@@ -26,7 +26,7 @@ import statistics
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PCG_SOURCES = ("paper_2411_04776_amd/csrc/k_solver.hip", "paper_2411_04776_amd/csrc/k_pcg_team.hip",
-               "paper_2411_04776_amd/csrc/pcg_sums.h",
+               "paper_2411_04776_amd/csrc/k_pcg_solo.hip", "paper_2411_04776_amd/csrc/pcg_sums.h",
                "paper_2411_04776_amd/csrc/device_util.h", "paper_2411_04776_amd/csrc/ipc_internal.h")
 
 
@@ -84,12 +84,13 @@ def pmc(args):
     line = json.load(open(args.json))
     leg = line if args.leg == "headline" else line[args.leg]
     roof = leg["roofline"]
-    k = roof if roof["kernel"].startswith(args.kernel) else roof["other_pcg_kernel"]
+    k = roof if roof["kernel"].split(" ")[0] == args.kernel else roof["other_pcg_kernel"]
     n_alg = k["all_launches"]["launches"]
     alg = k["all_launches"]["algorithmic_bytes_per_launch"]
     tf = sum(f) * 1024.0 * sf
     tw = sum(w) * 1024.0 * sw
-    per = (tf + tw) / max(len(f), 1)
+    # a launch of resident solves is a dispatch per layout that the list needs
+    per = (tf + tw) / max(n_alg if args.kernel == "k_pcg_team" else len(f), 1)
     ratio = per / alg if alg else float("nan")
     # the full-list dispatches (grid of at least 90 % of the largest): their
     # traffic over their durations in the FETCH run
@@ -114,7 +115,7 @@ def pmc(args):
              f"by {sw:.4f}.", "",
              f"{args.kernel} over {len(f)} dispatches (FETCH run) / {len(w)} (WRITE run): summed FETCH_SIZE "
              f"{sum(f):.0f} KiB, WRITE_SIZE {sum(w):.0f} KiB; scaled: {tf / 2**20:.1f} MiB read + "
-             f"{tw / 2**20:.1f} MiB written, {per / 2**20:.3f} MiB per dispatch (median FETCH "
+             f"{tw / 2**20:.1f} MiB written, {per / 2**20:.3f} MiB per launch (median per dispatch: FETCH "
              f"{statistics.median(f):.1f} KiB, WRITE {statistics.median(w):.1f} KiB).", "",
              f"Algorithmic bytes the library counted for the same launches ({n_alg} launches in the JSON line of the "
              f"FETCH run): {alg / 2**20:.3f} MiB per launch.", "",
