@@ -7,7 +7,9 @@ of closest features, and one rounding in a Newton iterate grows to 1e-9 to
 Hessians and its contact gradients are added is part of their result. The
 golden positions are those of commit 2792d08, which ran every part of a PCG
 iteration as a launch of its own and added contact pairs one by one. Equality
-is the only tolerance: the same operations in the same order.
+is the only tolerance: the same operations in the same order. What does not
+turn on the last bit is pinned to the oracle: each Newton iterate from the
+oracle's state, to 1e-9 of the scene's size.
 
 The cases: ties of several radii (90 vertices) and larger patches, at both
 layouts of each precision, with rows of more blocks than a thread holds (hub),
@@ -20,6 +22,7 @@ import os
 import numpy as np
 import pytest
 
+import oracle as O
 from paper_2411_04776_amd import scenes as S
 from test_gpu_pcg_forms import gel, hub, plate
 
@@ -95,3 +98,29 @@ def test_outcome_to_the_last_bit(ipc, name):
     want = np.load(GOLDEN)[name]
     assert len(want) <= 512
     assert np.array_equal(final_positions(ipc, name), want)
+
+
+@pytest.mark.parametrize("radius,depth", [(1.6e-3, 3e-5), (2e-3, 5e-5), (2.4e-3, 9e-5)])
+def test_iterates_from_the_oracles_states(ipc, radius, depth):
+    sc = patch(radius, depth)
+    o, g = O.OracleScene(sc), ipc.GelScene(sc)
+    worst, checked = 0.0, 0
+    for step in range(1, sc.n_steps + 1):
+        g.x, g.v = o.x, o.v
+        o.begin_step(sc.poses[step])
+        g.begin_step(sc.poses[step])
+        x = o.x.copy()
+        for _ in range(12):
+            r, nxt, _ = o.newton_iterate(x)
+            if r != 0:
+                break
+            rc, got, st = g.newton_iterate(x)
+            assert rc == 0
+            worst = max(worst, np.abs(got - nxt).max() / sc.bbox_diag)
+            checked += 1
+            x = nxt
+        o.step()  # the whole step, from the state at its start
+    print("iterates of", sc.name, radius, depth, ":", checked, "checked, worst err/L", worst, flush=True)
+    assert checked >= 8
+    assert worst <= 1e-9
+    g.close()
